@@ -447,8 +447,10 @@ int pdlpb_get_step_size(const pdlpb_ctx* ctx, double* eta, double* norm_a);
 
 /*
  * Kernel timing.  While enabled, pdlpb_solve runs without graph replay and
- * brackets every launch of the fused SpMM kernels with HIP events on the
- * context's stream.  pdlpb_kernel_times reports, per kind
+ * on the step launches at every size (small matrices otherwise run whole
+ * blocks of C iterations in one launch, with the same bits), and brackets
+ * every launch of the fused SpMM kernels with HIP events on the context's
+ * stream.  pdlpb_kernel_times reports, per kind
  * (0: A'Y + primal step, 1: A X + dual step, 2: evaluation, 3: control,
  * restarts and compaction, 4: persistent tail), the number of launches and
  * their summed duration in milliseconds since the last reset.
@@ -474,10 +476,13 @@ int pdlpb_kernel_columns(pdlpb_ctx* ctx, int64_t cols[5]);
  * took the shared start (option shared_start) keeps its base vectors,
  * (n + m)(1 + 3K) elements for K <= 2 base LPs, 196 elements per LP column,
  * and 80 (n + m) K bytes of evaluation terms; pdlpb_serve_begin releases
- * both. */
+ * both.  One whose small matrix pdlpb_solve iterates with the workgroups of
+ * an XCD per chunk of columns keeps 5 (n + 4) + 8 (m + 4) elements and
+ * 3.2 (n + m) doubles per column of its widest such batch (at most 128). */
 int64_t pdlpb_device_bytes(const pdlpb_ctx* ctx);
 
-/* Number of blocks of C iterations captured as graphs over the context's life.
+/* Number of blocks of C iterations (small matrices: launches of several
+ * blocks) captured as graphs over the context's life.
  * A captured block is replayed for every later batch or serving round with the
  * same launch shape (live column bound, row stride, tile shapes, the batch's
  * blocks or those of 16, 4, 2 or 1 columns, the result blocks written), and is

@@ -14,6 +14,8 @@
 #include <math.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 #include "pdlpb.h"
 #include "pdlpb_internal.h"
 
@@ -257,22 +259,37 @@ __device__ __forceinline__ void row_product(const StepArgs<T>& a, const RowOps<T
 // stored reflection z and the anchor x0, x~ = Pi_[lo,hi](x^k - tau (c + g)),
 // reflection 2 x~ - x^k.
 template <typename T>
+__device__ __forceinline__ T primal_iterate(int32_t k, T z, T x0) {
+#pragma clang fp contract(off)
+    return (k == 0) ? x0 : T(double(k) / double(k + 1)) * z + x0 / T(k + 1);
+}
+template <typename T>
+__device__ __forceinline__ void primal_update(T xk, T tau, T c, T lo, T hi, T g, T& xt, T& xbar) {
+#pragma clang fp contract(off)
+    xt = clampt<T>(xk - tau * (c + g), lo, hi);
+    xbar = T(2) * xt - xk;
+}
+template <typename T>
 __device__ __forceinline__ void primal_point(int32_t k, T z, T x0, T tau, double c, double lo,
                                              double hi, T g, T& xk, T& xt, T& xbar) {
-#pragma clang fp contract(off)
-    xk = (k == 0) ? x0 : T(double(k) / double(k + 1)) * z + x0 / T(k + 1);
-    xt = clampt<T>(xk - tau * (T(c) + g), T(lo), T(hi));
-    xbar = T(2) * xt - xk;
+    xk = primal_iterate<T>(k, z, x0);
+    primal_update<T>(xk, tau, T(c), T(lo), T(hi), g, xt, xbar);
 }
 // Dual (eq:main-iterate, second line, Moreau form; eq:mainiter): q = y^k / sigma + v,
 // y~ = sigma (q - Pi_[l,u](q)), y^{k+1} = wa (2 y~ - y^k) + y0 / wb.
+// yp = y^k / sigma and yh = y0 / wb
+template <typename T>
+__device__ __forceinline__ void dual_update(T yk, T yp, T yh, T sg, T wa, T l, T u, T v, T& yt,
+                                            T& ynext) {
+#pragma clang fp contract(off)
+    const T q = yp + v;
+    yt = sg * (q - clampt<T>(q, l, u));
+    ynext = wa * (T(2) * yt - yk) + yh;
+}
 template <typename T>
 __device__ __forceinline__ void dual_point(T yk, T y0, T sg, T wa, T wb, T l, T u, T v, T& yt,
                                            T& ynext) {
-#pragma clang fp contract(off)
-    const T q = yk / sg + v;
-    yt = sg * (q - clampt<T>(q, l, u));
-    ynext = wa * (T(2) * yt - yk) + y0 / wb;
+    dual_update<T>(yk, yk / sg, y0 / wb, sg, wa, l, u, v, yt, ynext);
 }
 // Last Halpern iterate of a stopped LP, rebuilt from its reflection and anchor:
 // a xbar + x0 / kp2 with a = (k+1)/(k+2), kp2 = k + 2 of its last iteration.
@@ -1727,6 +1744,1132 @@ __global__ __launch_bounds__(TAIL_THREADS) void k_tail(TailArgs<T> a) {
 }
 
 // ---------------------------------------------------------------------------
+// Persistent blocks (small matrices).  A step launch on a small matrix lasts 3-5
+// us, nearly all of it launch boundary and first loads: the operands of a row
+// come from memory anew in every launch.  Here a launch runs whole blocks of C
+// iterations with their evaluations, and everything a workgroup reads in each
+// iteration (its rows of A and A', bounds, iterates, anchors) stays in LDS.
+//   Solo: one workgroup iterates one LP whose matrix and vectors all fit in LDS;
+// the halves of an iteration are separated by workgroup barriers.
+//   Grouped: workgroups of one XCD (by the XCC_ID register) share a chunk of
+// 1 << lw columns; a member owns a slice of the x rows and of the y rows, and the
+// two vectors the products gather (X-bar, Y) are exchanged through memory, which
+// for one XCD means its L2: a store has reached it when the wave's vmcnt is 0, and
+// agent-scope loads pass the CU's own cache by.  A half ends with a barrier of the
+// group (one atomic arrival per workgroup, 0.8-1 us; a grid-wide barrier that
+// orders data across XCDs costs 16 us), and the part of the next update that needs
+// no product is computed between arrival and release.  Chunks are independent
+// LPs, so groups never wait for each other.
+//   A CU answers a gather with one cache line in about 3.7 cycles (measured: 64-byte
+// rows of a 1 MB table at 165 G rows/s on the chip), so a lone column, whose
+// gathers take 8 bytes of each line, is copied whole into every member's LDS
+// instead and gathered there ("staged"); wider chunks gather their row segments.
+//   A group is formed from workgroups that are running: each joins its XCD's
+// group on arrival, the first one closes it once enough have joined or after a
+// bounded wait, and one that comes later leaves.  Every barrier therefore waits
+// only for running workgroups, whatever else the device runs, and any group size
+// is handled: a member whose slice does not fit in LDS keeps it in memory.
+//   What bounds it now: solo the dependent chain of a half (gather from LDS, sum,
+// update, barrier: ~1000 cycles), staged two barriers and the copies of the two
+// vectors (2900 of ~9600 cycles), columns the gathers' cache lines (~3000 cycles a
+// half at 25000 nonzeros over 32 CUs) and the barriers.  Measured against the step
+// launches, FP64: one LP 50 x 100 0.87 us per iteration (5.2-6.9 us before), one LP
+// 2000 x 5000 3.8 us (8.9), 16 LPs 200 x 500 to convergence 1.9 ms (9.1), 64 LPs 2000 x
+// 5000 6.9 ms (11.4).
+//   Products, updates, terms, chains and reduction trees are those of the batched
+// kernels in the same order, and the tests are control_slot's, so an LP's results
+// are the batched path's, bit for bit.  A stopped LP keeps its column, no longer
+// iterated, until the compaction after the launch.
+// ---------------------------------------------------------------------------
+constexpr uint32_t GROUP_CLOSED = 0x80000000u;
+constexpr int JOIN_POLLS = 400;     // of the first member, ~100 us
+
+__device__ __forceinline__ uint32_t agent_load(const uint32_t* p) {
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ void agent_store(uint32_t* p, uint32_t v) {
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+template <typename T>
+__device__ __forceinline__ T agent_load_t(const T* p) {
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+// this wave's stores have reached the L2
+__device__ __forceinline__ void drain_stores() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+
+// What the workgroups of a group keep alike (LDS): the columns' states; the first
+// member also their control data.
+struct PersistShared {
+    PersistCol cs[PERSIST_W];
+    double tau[PERSIST_W], sigma[PERSIST_W], dval[PERSIST_W];
+    int32_t t_start[PERSIST_W], lp[PERSIST_W];
+    SlotCtl ctl[PERSIST_W];
+    double sums[2 * NTERM * PERSIST_W];
+    int32_t sh[4];
+};
+static_assert(sizeof(PersistShared) <= PERSIST_STATIC_LDS, "PERSIST_STATIC_LDS");
+
+// One workgroup's part: its group, its row slices.
+struct PersistPart {
+    int32_t member;            // in its group (-1: not needed)
+    uint32_t parties;          // workgroups of the group that take part
+    int32_t x0r, nxr, y0r, nyr;
+    GroupLine* line;           // null: solo
+    uint32_t target;           // arrivals after the next barrier
+};
+
+// Arrival at the group's barrier, with this workgroup's stores visible to it, and the
+// wait for the others; what lies between them must not read other members' data.
+template <bool SOLO>
+__device__ __forceinline__ void group_arrive(PersistPart& p) {
+    if constexpr (SOLO) {
+        __syncthreads();
+    } else {
+        drain_stores();
+        __syncthreads();
+        if (threadIdx.x == 0)
+            __hip_atomic_fetch_add(&p.line->arrived, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        p.target += p.parties;
+    }
+}
+template <bool SOLO>
+__device__ __forceinline__ void group_wait(PersistPart& p) {
+    if constexpr (!SOLO) {
+        if (threadIdx.x == 0) {
+            while ((int32_t)(agent_load(&p.line->arrived) - p.target) < 0) {
+            }
+        }
+        __syncthreads();
+    }
+}
+
+// Sums of a chunk in memory (solo: in LDS): panel sums [q][col][panel], x then y;
+// their reductions; the columns' states and step sizes; chain sums of members
+// without LDS.
+struct PersistSums {
+    double *panels, *red, *tau, *sigma, *chains;
+    PersistCol* cs;
+};
+__device__ __forceinline__ PersistSums persist_sums(double* w, int32_t np, int32_t W) {
+    PersistSums s;
+    s.panels = w;
+    s.red = w + (size_t)np * NTERM * W;
+    s.tau = s.red + 2 * NTERM * PERSIST_W;
+    s.sigma = s.tau + PERSIST_W;
+    s.cs = reinterpret_cast<PersistCol*>(s.sigma + PERSIST_W);
+    s.chains = s.sigma + PERSIST_W + sizeof(PersistCol) / 8 * PERSIST_W;
+    return s;
+}
+
+// The columns' states at the start of a chunk.
+template <typename T>
+__device__ __forceinline__ void persist_load_cols(const PersistArgs<T>& a, PersistShared& S, int32_t c0,
+                                                  int32_t W, int32_t ncols, bool ctl) {
+    const int tid = threadIdx.x;
+    if (tid < W) {
+        PersistCol q{};
+        if (c0 + tid < ncols) {
+            const SlotKey key = a.sl.key[c0 + tid];
+            q.t_anchor = key.t_anchor;
+            q.t_end = key.t_end;
+            q.varkind = key.varkind;
+            q.flags = key.flags;
+            S.tau[tid] = a.sl.tau[c0 + tid];
+            S.sigma[tid] = a.sl.sigma[c0 + tid];
+            S.dval[tid] = a.sl.dval[c0 + tid];
+            S.t_start[tid] = a.sl.t_start[c0 + tid];
+            S.lp[tid] = a.sl.lp[c0 + tid];
+            if (ctl) S.ctl[tid] = a.ctl[S.lp[tid]];
+        }
+        S.cs[tid] = q;
+    }
+}
+template <typename T>
+__device__ __forceinline__ void persist_store_cols(const PersistArgs<T>& a, const PersistShared& S,
+                                                   int32_t c0, int32_t W, int32_t ncols) {
+    const int tid = threadIdx.x;
+    if (tid < W && c0 + tid < ncols) {
+        const PersistCol q = S.cs[tid];
+        a.sl.key[c0 + tid] = SlotKey{q.t_anchor, q.t_end, q.varkind, q.flags};
+        a.sl.tau[c0 + tid] = S.tau[tid];
+        a.sl.sigma[c0 + tid] = S.sigma[tid];
+        a.ctl[S.lp[tid]] = S.ctl[tid];
+    }
+}
+
+// Which columns of the chunk the evaluation after iteration t reads: between full
+// evaluations only a fresh cycle, a stopping test or a last iteration is evaluated.
+__device__ __forceinline__ uint32_t persist_need(const PersistShared& S, int32_t W, bool all, int32_t t) {
+    uint32_t need = 0;
+    for (int32_t w = 0; w < W; ++w) {
+        const bool act = (S.cs[w].flags & SLOT_ACTIVE) != 0;
+        need |= (uint32_t)(act && (all || t == S.cs[w].t_anchor || t >= S.cs[w].t_end)) << w;
+    }
+    return need;
+}
+__device__ __forceinline__ uint32_t persist_flagged(const PersistShared& S, int32_t W, int32_t flags) {
+    uint32_t f = 0;
+    for (int32_t w = 0; w < W; ++w) f |= (uint32_t)((S.cs[w].flags & flags) == flags) << w;
+    return f;
+}
+
+// The tests of the columns flagged in `need` from the group's panel sums, and the new
+// states for every member.  The reductions: term q of a column, lane l adds panels
+// l, l + 64, ..., then a butterfly; over the whole group when there are many columns.
+template <typename T, bool SOLO>
+__device__ __forceinline__ void persist_tests(const PersistArgs<T>& a, PersistPart& P, PersistShared& S,
+                                              const PersistSums& ws, int32_t lw, uint32_t need, bool full,
+                                              bool stop, int32_t t, double eta) {
+    const int tid = threadIdx.x, bs = blockDim.x;
+    const int lane = tid & 63, wave = tid >> 6, nwaves = bs >> 6;
+    const int32_t W = 1 << lw;
+    group_arrive<SOLO>(P);
+    group_wait<SOLO>(P);
+    const bool spread = !SOLO && W > 2;
+    if (P.member == 0 || spread) {
+        const int32_t st = spread ? nwaves * (int32_t)P.parties : nwaves;
+        for (int32_t pr = spread ? wave * (int32_t)P.parties + P.member : wave; pr < 2 * NTERM * W; pr += st) {
+            const int32_t cc = pr & (W - 1), q = pr >> lw;
+            if (!((need >> cc) & 1u)) continue;
+            const bool xside = q < NTERM;
+            const int32_t qq = xside ? q : q - NTERM, np = xside ? a.npx : a.npy;
+            const double* p = ws.panels + (size_t)(xside ? 0 : NTERM * a.npx * W) + ((size_t)qq * W + cc) * np;
+            double acc = 0.0;
+            for (int32_t i0 = lane; i0 < np; i0 += 64 * NCH) {
+                double v[NCH];
+#pragma unroll
+                for (int u = 0; u < NCH; ++u) {
+                    const int32_t i = min(i0 + 64 * u, np - 1);
+                    if constexpr (SOLO) v[u] = p[i];
+                    else v[u] = agent_load_t(p + i);
+                }
+#pragma unroll
+                for (int u = 0; u < NCH; ++u)
+                    if (i0 + 64 * u < np) acc += v[u];
+            }
+#pragma unroll
+            for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off, 64);
+            if (lane == 0) {
+                if (spread) ws.red[pr] = acc;
+                else S.sums[pr] = acc;
+            }
+        }
+    }
+    if (spread) {
+        group_arrive<SOLO>(P);
+        group_wait<SOLO>(P);
+        if (P.member == 0)
+            for (int32_t pr = tid; pr < 2 * NTERM * W; pr += bs) S.sums[pr] = agent_load_t(ws.red + pr);
+    }
+    if (P.member == 0) {
+        __syncthreads();
+        if (tid < W && ((need >> tid) & 1u)) {
+            PersistCol q = S.cs[tid];
+            SlotKey st{q.t_anchor, q.t_end, q.varkind, q.flags};
+            ControlArgs ca = a.ca;
+            ca.sl.tau = S.tau;
+            ca.sl.sigma = S.sigma;
+            ca.sl.t_start = S.t_start;
+            double r = 0.0;
+            bool rh = false;
+            control_slot(ca, full, stop, tid, st, S.ctl[tid], a.rlog + (size_t)S.lp[tid] * RESTART_LOG,
+                         S.sums + tid, S.sums + NTERM * W + tid, W, t, eta, true, &r, &rh);
+            q.t_anchor = st.t_anchor;
+            q.flags = st.flags;
+            S.cs[tid] = q;
+            if constexpr (!SOLO) {
+                ws.cs[tid] = q;
+                ws.tau[tid] = S.tau[tid];
+                ws.sigma[tid] = S.sigma[tid];
+            }
+        }
+        if constexpr (SOLO) __syncthreads();
+    }
+    if constexpr (!SOLO) {
+        group_arrive<SOLO>(P);
+        group_wait<SOLO>(P);
+        if (P.member != 0) {
+            if (tid < W && ((need >> tid) & 1u)) {
+                S.cs[tid].t_anchor = agent_load_t(&ws.cs[tid].t_anchor);
+                S.cs[tid].flags = agent_load_t(&ws.cs[tid].flags);
+                S.tau[tid] = agent_load_t(ws.tau + tid);
+                S.sigma[tid] = agent_load_t(ws.sigma + tid);
+            }
+            __syncthreads();
+        }
+    }
+}
+
+// First quads of a slice's rows (rows padded to fours): an exclusive scan by one
+// wave; o[rows] receives the total.
+__device__ __forceinline__ void quad_scan(const int32_t* rp, int32_t rows, int32_t* o, int lane) {
+    int32_t run = 0;
+    for (int32_t r0 = 0; r0 < rows; r0 += 64) {
+        const int32_t r = r0 + lane;
+        const int32_t c = r < rows ? (rp[r + 1] - rp[r] + 3) / 4 : 0;
+        int32_t inc = c;
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1) {
+            const int32_t up = __shfl_up(inc, off, 64);
+            if (lane >= off) inc += up;
+        }
+        if (r < rows) o[r] = run + inc - c;
+        run += __shfl(inc, 63, 64);
+    }
+    if (lane == 0) o[rows] = run;
+}
+
+// A row's entries from the matrix into its quads in LDS: indices times scale, a pad's
+// `pad` (negative: the row's last index again) with value 0; eight entries in flight.
+template <typename T, typename J>
+__device__ __forceinline__ void fill_quads(const int32_t* ci, const T* av, int32_t k, int32_t ke, int32_t qb,
+                                           int32_t qe, int32_t pad, int32_t scale, J* j, T* v) {
+    for (int32_t q = qb; q < qe; q += 2) {
+        int32_t c[8];
+        T x[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            const int32_t kk = min(k + u, ke - 1);
+            c[u] = ci[kk];
+            x[u] = av[kk];
+        }
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+            if (q + u / 4 < qe) {
+                j[4 * q + u] = (J)((k + u < ke || pad < 0 ? c[u] : pad) * scale);
+                v[4 * q + u] = k + u < ke ? x[u] : T(0);
+            }
+        k += 8;
+    }
+}
+
+// Four values of a row in LDS.
+template <typename T>
+__device__ __forceinline__ void load_quad(const T* v, T* w);
+template <>
+__device__ __forceinline__ void load_quad<double>(const double* v, double* w) {
+    const double2 a = reinterpret_cast<const double2*>(v)[0], b = reinterpret_cast<const double2*>(v)[1];
+    w[0] = a.x; w[1] = a.y; w[2] = b.x; w[3] = b.y;
+}
+template <>
+__device__ __forceinline__ void load_quad<float>(const float* v, float* w) {
+    const float4 a = *reinterpret_cast<const float4*>(v);
+    w[0] = a.x; w[1] = a.y; w[2] = a.z; w[3] = a.w;
+}
+
+// ---- one column, gathered from LDS (solo and staged) -----------------------------
+// A thread owns one row: waves from 0 the x rows, the others the y rows, so each
+// half of an iteration belongs to its own waves and a row's iterate, anchor, bounds
+// and indices stay in registers.  Rows are padded to fours; a pad, like a quad
+// beyond a short row, points at the entry past the vector's end, which is 0.
+constexpr int PERSIST_XQ = 2, PERSIST_YQ = 4;   // quads of a row with indices in registers
+
+template <typename T, bool SOLO>
+__device__ __forceinline__ void persist_column(const PersistArgs<T>& a, PersistPart& P, int32_t chunk,
+                                               int32_t ncols, PersistShared& S, double* lds) {
+    const int tid = threadIdx.x, bs = blockDim.x;
+    const int lane = tid & 63, wave = tid >> 6;
+    const int32_t n = a.n, m = a.m, ld = a.ld;
+    const int32_t nxr = P.nxr, nyr = P.nyr;
+    const int32_t s = chunk;
+    const double eta = a.g->eta;
+    const int32_t t0_launch = a.g->t0;
+    const int32_t xw = (nxr + 63) & ~63;
+    const bool isx = tid < xw;
+    const int32_t li = isx ? tid : tid - xw;                  // row of the slice
+    const int32_t row = (isx ? P.x0r : P.y0r) + li;
+    const bool own = li < (isx ? nxr : nyr);
+    // vectors of the chunk in memory (grouped): X-bar, Y; the evaluation's
+    T* const wk = SOLO ? nullptr : a.work + (size_t)chunk * persist_work_rows(n, m);
+    const size_t nP = persist_stride(n), mP = persist_stride(m);
+    T *const gXb = wk, *const gY = wk + 3 * nP;
+
+    // ---- LDS ------------------------------------------------------------------------
+    char* lq = reinterpret_cast<char*>(lds);
+    auto take = [&](size_t bytes) {
+        char* r = lq;
+        lq += (bytes + 15) & ~(size_t)15;
+        return r;
+    };
+    T* const FX = (T*)take((size_t)(n + 1) * sizeof(T));      // X-bar
+    T* const FY = (T*)take((size_t)(m + 1) * sizeof(T));      // Y
+    // x~ and dx; y~, dy and its barrier projection, as the evaluation gathers them
+    T* const EXt = SOLO ? (T*)take((size_t)(n + 1) * sizeof(T)) : wk + nP;
+    T* const EDX = SOLO ? (T*)take((size_t)(n + 1) * sizeof(T)) : wk + 2 * nP;
+    T* const EYt = SOLO ? (T*)take((size_t)(m + 1) * sizeof(T)) : gY + mP;
+    T* const EDY = SOLO ? (T*)take((size_t)(m + 1) * sizeof(T)) : gY + 2 * mP;
+    T* const EDB = SOLO ? (T*)take((size_t)(m + 1) * sizeof(T)) : gY + 3 * mP;
+    const int32_t chx = (nxr + 15) / 16 * 4, chy = (nyr + 15) / 16 * 4;
+    double* const chains = (double*)take((size_t)(chx + chy) * NTERM * 8);
+    double* const wsum = SOLO ? (double*)take((size_t)(a.npx + a.npy) * NTERM * 8)
+                              : a.wsum + (size_t)chunk * persist_sum_doubles(a.npx, a.npy, 1);
+    const PersistSums ws = persist_sums(wsum, a.npx + a.npy, 1);
+    int32_t* const px = (int32_t*)take((size_t)(nxr + 1) * 4);
+    int32_t* const py = (int32_t*)take((size_t)(nyr + 1) * 4);
+    if (wave == 0) quad_scan(a.t_rp + P.x0r, nxr, px, lane);
+    if (wave == 1) quad_scan(a.a_rp + P.y0r, nyr, py, lane);
+    persist_load_cols(a, S, chunk, 1, ncols, P.member == 0);
+    __syncthreads();
+    const int32_t qx = px[nxr], qy = py[nyr];
+    uint16_t* const jx = (uint16_t*)take((size_t)(qx + qy) * 8);
+    T* const vx = (T*)take((size_t)(qx + qy + 1) * 4 * sizeof(T));   // and a quad of zeros
+    const uint16_t* const jq = jx + (isx ? 0 : 4 * qx);       // this side's quads
+    const T* const vq = vx + (isx ? 0 : 4 * (size_t)qx);
+    const int32_t zq = isx ? qx + qy : qy;
+    if (tid < 4) vx[4 * (size_t)(qx + qy) + tid] = T(0);
+    int32_t qb = 0, qe = 0;
+    if (own) {
+        qb = (isx ? px : py)[li];
+        qe = (isx ? px : py)[li + 1];
+        fill_quads<T, uint16_t>(isx ? a.t_ci : a.a_ci, isx ? a.t_v : a.a_v, (isx ? a.t_rp : a.a_rp)[row],
+                                (isx ? a.t_rp : a.a_rp)[row + 1], qb, qe, isx ? m : n, 1,
+                                jx + (isx ? 0 : 4 * qx), vx + (isx ? 0 : 4 * (size_t)qx));
+    }
+    // ---- this thread's row -------------------------------------------------------------
+    uint32_t jj[2 * PERSIST_YQ];
+#pragma unroll
+    for (int u = 0; u < PERSIST_YQ; ++u) {
+        const uint32_t pad = (uint32_t)(isx ? m : n) * 0x10001u;
+        const bool have = qb + u < qe && (u < PERSIST_XQ || !isx);
+        jj[2 * u] = have ? reinterpret_cast<const uint32_t*>(jq + 4 * (qb + u))[0] : pad;
+        jj[2 * u + 1] = have ? reinterpret_cast<const uint32_t*>(jq + 4 * (qb + u))[1] : pad;
+    }
+    T z = T(0), z0 = T(0), lo = T(0), hi = T(0), p = T(0), h = T(0), wa = T(0);
+    double dc = 0.0, dlo = 0.0, dhi = 0.0;
+    if (own) {
+        z = a.blk[isx ? 0 : 4][(size_t)row * ld + s];
+        z0 = a.blk[isx ? 1 : 5][(size_t)row * ld + s];
+        dlo = (isx ? a.xl : a.rl)[row];
+        dhi = (isx ? a.xu : a.ru)[row];
+        if (isx) {
+            const VarData d = var_data(S.cs[0].varkind, S.dval, 0, row, a.c[row], dlo, dhi);
+            dc = a.c[row];
+            lo = T(d.lo);
+            hi = T(d.hi);
+            p = T(d.c);
+        } else {
+            lo = T(dlo);
+            hi = T(dhi);
+        }
+        if constexpr (SOLO) (isx ? FX : FY)[row] = z;
+        else (isx ? gXb : gY)[row] = z;
+    }
+    if (tid == 0) {   // the entries past the ends
+        FX[n] = FY[m] = T(0);
+        if (P.member == 0) {
+            EXt[n] = EDX[n] = EYt[m] = EDY[m] = EDB[m] = T(0);
+            if constexpr (!SOLO) gXb[n] = gY[m] = T(0);
+        }
+    }
+    // what the update with inner index k needs besides its product: x^k from the
+    // reflection and the anchor; y^k/sigma, y^0/(k+2) and the Halpern weight
+    auto prepare = [&](int32_t k) {
+        if (isx) {
+            h = primal_iterate<T>(k, z, z0);
+        } else {
+            p = z / T(S.sigma[0]);
+            h = z0 / T(k + 2);
+            wa = T(halpern_a(k));
+        }
+    };
+    // A vector of the group into LDS: 16 bytes a lane straight into LDS, past the CU's
+    // cache (sc1, as agent-scope loads).  The members start at different places, so
+    // that they do not ask the same L2 channel at once.  What a last lane copies past
+    // the vector's end is the entry that is 0 and, in both places, unused space.
+    auto stage = [&](T* f, const T* g, int32_t len) {
+        if constexpr (!SOLO) {
+            const int32_t units = (int32_t)(((size_t)len * sizeof(T) + 15) / 16);   // of 16 bytes
+            const int32_t runs = (units + 63) / 64;                                 // of a wave
+            const int32_t first = (int32_t)((int64_t)runs * P.member / (int32_t)P.parties);
+            for (int32_t r0 = wave; r0 < runs; r0 += bs >> 6) {
+                int32_t r = r0 + first;
+                r -= r >= runs ? runs : 0;
+                const int32_t u0 = __builtin_amdgcn_readfirstlane(r * 64);
+                if (u0 + lane < units)
+                    __builtin_amdgcn_global_load_lds(
+                        (const __attribute__((address_space(1))) void*)(reinterpret_cast<const char*>(g) +
+                                                                        16 * (size_t)(u0 + lane)),
+                        (__attribute__((address_space(3))) void*)(reinterpret_cast<char*>(f) + 16 * (size_t)u0),
+                        16, 0, 16);
+            }
+            drain_stores();
+            __syncthreads();
+        }
+    };
+    group_arrive<SOLO>(P);
+    if (S.cs[0].flags & SLOT_ACTIVE) prepare(t0_launch + 1 - S.cs[0].t_anchor);
+    group_wait<SOLO>(P);
+    stage(FY, gY, m);
+
+    // this row's product with the vector f
+    auto product = [&](auto nqc, const T* f) -> T {
+        constexpr int NQ = decltype(nqc)::value;
+        T v[4 * NQ];
+#pragma unroll
+        for (int u = 0; u < 2 * NQ; ++u) {
+            v[2 * u] = f[jj[u] & 0xffffu];
+            v[2 * u + 1] = f[jj[u] >> 16];
+        }
+        T acc = T(0);
+#pragma unroll
+        for (int u = 0; u < NQ; ++u) {
+            T w[4];
+            load_quad<T>(vq + 4 * (size_t)(qb + u < qe ? qb + u : zq), w);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) acc = fma(w[e], v[4 * u + e], acc);
+        }
+        for (int32_t q = qb + NQ; q < qe; ++q) {
+            const ushort4 j = reinterpret_cast<const ushort4*>(jq)[q];
+            T w[4];
+            load_quad<T>(vq + 4 * (size_t)q, w);
+            const T v0 = f[j.x], v1 = f[j.y], v2 = f[j.z], v3 = f[j.w];
+            acc = fma(w[0], v0, acc);
+            acc = fma(w[1], v1, acc);
+            acc = fma(w[2], v2, acc);
+            acc = fma(w[3], v3, acc);
+        }
+        return acc;
+    };
+    auto at = [&](const T* f, int32_t i) -> T {   // an entry of an evaluation vector
+        if constexpr (SOLO) return f[i];
+        else return agent_load_t(f + i);
+    };
+
+    // ---- evaluation sums, then the tests ----------------------------------------------
+    T xt = T(0), dx = T(0);                       // z~ and the displacement, when kept
+    auto evaluate = [&](bool full, bool stop, int32_t t) {
+        double tv[NTERM];
+#pragma unroll
+        for (int q = 0; q < NTERM; ++q) tv[q] = 0.0;
+        if (own) {
+            double g = 0.0, hh = 0.0, pdy = 0.0;
+            for (int32_t q = qb; q < qe; ++q) {
+                const ushort4 j = reinterpret_cast<const ushort4*>(jq)[q];
+                const int32_t ji[4] = {j.x, j.y, j.z, j.w};
+                T w[4], v[4], d[4], b[4];
+                load_quad<T>(vq + 4 * (size_t)q, w);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    v[e] = at(isx ? EYt : EXt, ji[e]);
+                    d[e] = at(isx ? EDY : EDX, ji[e]);
+                    if (isx) b[e] = at(EDB, ji[e]);
+                }
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    g = fma((double)w[e], (double)v[e], g);
+                    hh = fma((double)w[e], (double)d[e], hh);
+                    if (isx) pdy = fma((double)w[e], (double)b[e], pdy);
+                }
+            }
+            if (isx)
+                finish_xrow(XRow{(double)xt, (double)dx, (double)z0, dc, dlo, dhi}, g, hh, pdy,
+                            S.cs[0].varkind, S.dval, 0, row, tv);
+            else
+                finish_yrow(YRow{(double)xt, (double)dx, (double)z0, dlo, dhi}, g, hh, tv);
+        }
+        // chains of four rows lie in four lanes
+#pragma unroll
+        for (int q = 0; q < NTERM; ++q) {
+            const double t1 = __shfl_down(tv[q], 1, 64), t2 = __shfl_down(tv[q], 2, 64),
+                         t3 = __shfl_down(tv[q], 3, 64);
+            const double v = (((0.0 + tv[q]) + t1) + t2) + t3;
+            if ((li & 3) == 0 && li / 4 < (isx ? chx : chy)) chains[((isx ? 0 : chx) + li / 4) * NTERM + q] = v;
+        }
+        __syncthreads();
+        // panel sums ((c0 + c1) + c2) + c3 of this workgroup's rows
+        for (int32_t idx = tid; idx < (chx + chy) / 4 * NTERM; idx += bs) {
+            const int32_t pl = idx / NTERM, q = idx % NTERM;
+            const bool xside = pl < chx / 4;
+            const int32_t pn = xside ? P.x0r / 16 + pl : P.y0r / 16 + pl - chx / 4;
+            const double* c = chains + (size_t)4 * pl * NTERM + q;
+            ws.panels[(xside ? 0 : NTERM * a.npx) + q * (xside ? a.npx : a.npy) + pn] =
+                ((c[0] + c[NTERM]) + c[2 * NTERM]) + c[3 * NTERM];
+        }
+        persist_tests<T, SOLO>(a, P, S, ws, 0, 1u, full, stop, t, eta);
+    };
+
+    // ---- blocks of C iterations ----------------------------------------------------------
+    int32_t t0 = t0_launch;
+    for (int32_t b = 0; b < a.blocks; ++b, t0 += a.C) {
+        if (!(S.cs[0].flags & SLOT_ACTIVE)) break;
+        for (int32_t it = 1; it <= a.C; ++it) {
+            const int32_t t = t0 + it;
+            const bool stop = a.S > 0 && it % a.S == 0 && it != a.C;
+            const int32_t k = t - S.cs[0].t_anchor;
+            const bool live = (S.cs[0].flags & SLOT_ACTIVE) && t <= S.cs[0].t_end;
+            // the evaluation after this iteration reads z~ and the displacement
+            const bool keep = t == S.cs[0].t_end || it == a.C || (it == 1 && k == 0) || stop;
+            if (isx && own && live) {
+                const T acc = product(std::integral_constant<int, PERSIST_XQ>{}, FY);
+                T x1, xbar;
+                primal_update<T>(h, T(S.tau[0]), p, lo, hi, acc, x1, xbar);
+                z = xbar;
+                if constexpr (SOLO) FX[row] = xbar;
+                else gXb[row] = xbar;
+                if (keep) {
+                    xt = x1;
+                    dx = x1 - h;
+                    EXt[row] = xt;
+                    EDX[row] = dx;
+                }
+            }
+            group_arrive<SOLO>(P);
+            if (isx && live) prepare(k + 1);
+            group_wait<SOLO>(P);
+            stage(FX, gXb, n);
+            if (!isx && own && live) {
+                const T acc = product(std::integral_constant<int, PERSIST_YQ>{}, FX);
+                T y1, yn;
+                dual_update<T>(z, p, h, T(S.sigma[0]), wa, lo, hi, acc, y1, yn);
+                if (keep) {
+                    xt = y1;
+                    dx = y1 - z;
+                    EYt[row] = xt;
+                    EDY[row] = dx;
+                    EDB[row] = T(barrier((double)dx, dlo, dhi));
+                }
+                z = yn;
+                if constexpr (SOLO) FY[row] = yn;
+                else gY[row] = yn;
+            }
+            group_arrive<SOLO>(P);
+            if (!isx && live) prepare(k + 1);
+            group_wait<SOLO>(P);
+            const bool full = it == a.C;
+            if (it == 1 || full || stop) {
+                if (persist_need(S, 1, full || stop, t)) evaluate(full, stop, t);
+                if (full && persist_flagged(S, 1, SLOT_ACTIVE | SLOT_FRESH)) {
+                    // restart: anchor and dual iterate become z~ (Section 4)
+                    z0 = xt;
+                    z = xt;
+                    if (!isx && own) {
+                        if constexpr (SOLO) FY[row] = z;
+                        else gY[row] = z;
+                    }
+                    prepare(0);
+                    group_arrive<SOLO>(P);
+                    group_wait<SOLO>(P);
+                }
+            }
+            stage(FY, gY, m);
+        }
+    }
+
+    // ---- copy out: the iterate; a stopped LP's last point too ----------------------------
+    if (own) {
+        const size_t o = (size_t)row * ld + s;
+        const bool stopped = (S.cs[0].flags & SLOT_ACTIVE) == 0;
+        // the reflection, or y^k (after a restart the anchor stands for both)
+        a.blk[isx ? 0 : 4][o] = z;
+        a.blk[isx ? 1 : 5][o] = z0;
+        if (stopped) a.blk[isx ? 2 : 6][o] = xt;
+    }
+    if (P.member == 0) persist_store_cols(a, S, chunk, 1, ncols);
+}
+
+// ---- several columns, gathered from memory; or a slice kept in memory ----------------
+// Items are (row, column) pairs, columns fastest, a thread keeps its column.  MEM: a
+// member whose slice does not fit in LDS (a group that closed short), from the
+// matrix itself.
+template <typename T, bool MEM>
+__device__ __forceinline__ void persist_columns(const PersistArgs<T>& a, PersistPart& P, int32_t chunk,
+                                                int32_t ncols, PersistShared& S, double* lds) {
+    const int tid = threadIdx.x, bs = blockDim.x;
+    const int lane = tid & 63, wave = tid >> 6;
+    const int32_t n = a.n, m = a.m, ld = a.ld;
+    const int32_t lw = a.lw, W = 1 << lw;
+    const int32_t nxr = P.nxr, nyr = P.nyr, x0r = P.x0r, y0r = P.y0r;
+    const int32_t c0 = chunk << lw;
+    const int32_t col = tid & (W - 1);              // of every item of this thread
+    const int32_t s = c0 + col;
+    const bool have = s < ncols;
+    const double eta = a.g->eta;
+    const int32_t t0_launch = a.g->t0;
+
+    // ---- the chunk's vectors in memory: stride W ------------------------------------
+    const size_t nW = persist_stride(n) * W, mW = persist_stride(m) * W;
+    T* const wk = a.work + (size_t)chunk * persist_work_rows(n, m) * W;
+    T *const gXb = wk, *const gXt = wk + nW, *const gDX = wk + 2 * nW, *const gY = wk + 3 * nW;
+    T *const gYt = gY + mW, *const gDY = gY + 2 * mW, *const gDB = gY + 3 * mW;
+    const PersistSums ws = persist_sums(a.wsum + (size_t)chunk * persist_sum_doubles(a.npx, a.npy, W),
+                                        a.npx + a.npy, W);
+
+    // ---- this workgroup's slice ----------------------------------------------------
+    const int32_t nxi = nxr * W, nyi = nyr * W;
+    T *XK, *X0, *YK, *Y0, *YP, *YH;                 // x^k, anchor; y^k, anchor, y^k/sigma, y^0/(k+2)
+    double *dc = nullptr, *dlo = nullptr, *dhi = nullptr, *drl = nullptr, *dru = nullptr;
+    T *vx = nullptr, *vy = nullptr;
+    int32_t *jx = nullptr, *jy = nullptr;
+    int32_t *px = nullptr, *py = nullptr;           // first quad of a row
+    double* chains;                                 // chain sums [chain][col][term]
+    const int32_t chx = (nxr + 15) / 16 * 4, chy = (nyr + 15) / 16 * 4;
+    if constexpr (MEM) {
+        XK = wk + 3 * nW + 4 * mW + (size_t)x0r * W;
+        X0 = XK + nW;
+        YK = wk + 5 * nW + 4 * mW + (size_t)y0r * W;
+        Y0 = YK + mW;
+        YP = YK + 2 * mW;
+        YH = YK + 3 * mW;
+        chains = ws.chains + (size_t)(x0r / 4 + y0r / 4) * W * NTERM;
+    } else {
+        char* q = reinterpret_cast<char*>(lds);
+        auto take = [&](size_t bytes) {
+            char* r = q;
+            q += (bytes + 15) & ~(size_t)15;
+            return r;
+        };
+        XK = (T*)take(nxi * sizeof(T));
+        X0 = (T*)take(nxi * sizeof(T));
+        YK = (T*)take(nyi * sizeof(T));
+        Y0 = (T*)take(nyi * sizeof(T));
+        YP = (T*)take(nyi * sizeof(T));
+        YH = (T*)take(nyi * sizeof(T));
+        dc = (double*)take(nxr * 8);
+        dlo = (double*)take(nxr * 8);
+        dhi = (double*)take(nxr * 8);
+        drl = (double*)take(nyr * 8);
+        dru = (double*)take(nyr * 8);
+        chains = (double*)take((size_t)(chx + chy) * W * NTERM * 8);
+        px = (int32_t*)take((nxr + 1) * 4);
+        py = (int32_t*)take((nyr + 1) * 4);
+        if (wave == 0) quad_scan(a.t_rp + x0r, nxr, px, lane);
+        if (wave == 1) quad_scan(a.a_rp + y0r, nyr, py, lane);
+        __syncthreads();
+        jx = (int32_t*)take((size_t)px[nxr] * 16);
+        vx = (T*)take((size_t)px[nxr] * 4 * sizeof(T));
+        jy = (int32_t*)take((size_t)py[nyr] * 16);
+        vy = (T*)take((size_t)py[nyr] * 4 * sizeof(T));
+        // byte offsets of the gathered rows; a pad gathers its row's last entry again
+        // (one row of zeros for all pads makes every workgroup ask one L2 channel)
+        const int32_t scale = W * (int32_t)sizeof(T);
+        for (int32_t li = tid; li < nxr + nyr; li += bs) {
+            const bool xs = li < nxr;
+            const int32_t r = xs ? li : li - nxr;
+            const int32_t* rp = xs ? a.t_rp + x0r + r : a.a_rp + y0r + r;
+            fill_quads<T, int32_t>(xs ? a.t_ci : a.a_ci, xs ? a.t_v : a.a_v, rp[0], rp[1], (xs ? px : py)[r],
+                                   (xs ? px : py)[r + 1], -1, scale, xs ? jx : jy, xs ? vx : vy);
+        }
+        for (int32_t li = tid; li < nxr; li += bs) {
+            dc[li] = a.c[x0r + li];
+            dlo[li] = a.xl[x0r + li];
+            dhi[li] = a.xu[x0r + li];
+        }
+        for (int32_t li = tid; li < nyr; li += bs) {
+            drl[li] = a.rl[y0r + li];
+            dru[li] = a.ru[y0r + li];
+        }
+    }
+
+    // ---- the parts of an update that need no product --------------------------------
+    auto primal_pre = [&](int32_t k) {              // XK: reflection -> x^k
+        for (int32_t i = tid; i < nxi; i += bs) XK[i] = primal_iterate<T>(k, XK[i], X0[i]);
+    };
+    auto dual_pre = [&](int32_t k, T sg) {
+        const T wb = T(k + 2);
+        for (int32_t i = tid; i < nyi; i += bs) {
+            YP[i] = YK[i] / sg;
+            YH[i] = Y0[i] / wb;
+        }
+    };
+
+    // ---- copy in ------------------------------------------------------------------
+    persist_load_cols(a, S, c0, W, ncols, P.member == 0);
+    for (int32_t i = tid; i < nxi; i += bs) {
+        const int32_t r = x0r + (i >> lw);
+        const size_t e = (size_t)r * ld + s;
+        const T v = have ? a.blk[0][e] : T(0);
+        XK[i] = v;
+        X0[i] = have ? a.blk[1][e] : T(0);
+        gXb[(size_t)r * W + col] = v;
+    }
+    for (int32_t i = tid; i < nyi; i += bs) {
+        const int32_t r = y0r + (i >> lw);
+        const size_t e = (size_t)r * ld + s;
+        const T v = have ? a.blk[4][e] : T(0);
+        YK[i] = v;
+        Y0[i] = have ? a.blk[5][e] : T(0);
+        gY[(size_t)r * W + col] = v;
+    }
+    group_arrive<false>(P);
+    if (S.cs[col].flags & SLOT_ACTIVE) {
+        primal_pre(t0_launch + 1 - S.cs[col].t_anchor);
+        dual_pre(t0_launch + 1 - S.cs[col].t_anchor, T(S.sigma[col]));
+    }
+    group_wait<false>(P);
+
+    // ---- products --------------------------------------------------------------------
+    // one entry of the vector at a row's gather offset (of this thread's column)
+    auto from = [&](const T* g, int32_t j) -> T {
+        if constexpr (MEM) return agent_load_t(g + ((size_t)j << lw) + col);
+        else return agent_load_t(reinterpret_cast<const T*>(reinterpret_cast<const char*>(g + col) + (uint32_t)j));
+    };
+    // NV products of row li (x side: column of A) with the vectors g, in CSR order;
+    // QF quads of gathers in flight
+    auto products = [&](auto nvc, auto qfc, auto xsc, int32_t li, const T* const* g, auto& acc) {
+        constexpr int NV = decltype(nvc)::value, QF = decltype(qfc)::value;
+        constexpr bool XS = decltype(xsc)::value;
+        using A = std::remove_reference_t<decltype(acc[0])>;
+#pragma unroll
+        for (int q = 0; q < NV; ++q) acc[q] = A(0);
+        if constexpr (MEM) {
+            const int32_t i = (XS ? x0r : y0r) + li;
+            const int32_t ke = (XS ? a.t_rp : a.a_rp)[i + 1];
+            for (int32_t k0 = (XS ? a.t_rp : a.a_rp)[i]; k0 < ke; k0 += NCH) {
+                T w[NCH], v[NV][NCH];
+#pragma unroll
+                for (int u = 0; u < NCH; ++u) {
+                    const int32_t k = min(k0 + u, ke - 1);
+                    w[u] = (XS ? a.t_v : a.a_v)[k];
+                    const int32_t j = (XS ? a.t_ci : a.a_ci)[k];
+#pragma unroll
+                    for (int q = 0; q < NV; ++q) v[q][u] = from(g[q], j);
+                }
+#pragma unroll
+                for (int u = 0; u < NCH; ++u)
+                    if (k0 + u < ke) {
+#pragma unroll
+                        for (int q = 0; q < NV; ++q) acc[q] = fma((A)w[u], (A)v[q][u], acc[q]);
+                    }
+            }
+        } else {
+            const int32_t qb = (XS ? px : py)[li], qe = (XS ? px : py)[li + 1];
+            for (int32_t q0 = qb; q0 < qe; q0 += QF) {
+                T v[NV][4 * QF];
+#pragma unroll
+                for (int u = 0; u < QF; ++u) {
+                    if (u == 0 || q0 + u < qe) {
+                        const int4 j = reinterpret_cast<const int4*>(XS ? jx : jy)[q0 + u];
+#pragma unroll
+                        for (int q = 0; q < NV; ++q) {
+                            v[q][4 * u] = from(g[q], j.x);
+                            v[q][4 * u + 1] = from(g[q], j.y);
+                            v[q][4 * u + 2] = from(g[q], j.z);
+                            v[q][4 * u + 3] = from(g[q], j.w);
+                        }
+                    }
+                }
+#pragma unroll
+                for (int u = 0; u < QF; ++u) {
+                    if (u == 0 || q0 + u < qe) {
+                        T w[4];
+                        load_quad<T>((XS ? vx : vy) + 4 * (size_t)(q0 + u), w);
+#pragma unroll
+                        for (int e = 0; e < 4; ++e)
+#pragma unroll
+                            for (int q = 0; q < NV; ++q) acc[q] = fma((A)w[e], (A)v[q][4 * u + e], acc[q]);
+                    }
+                }
+            }
+            // a pad adds 0 times an entry, which is 0 unless that is not finite: then
+            // the sum without the pads
+#pragma unroll
+            for (int q = 0; q < NV; ++q) {
+                if (!isfinite(acc[q])) {
+                    const int32_t i = (XS ? x0r : y0r) + li;
+                    const int32_t len = (XS ? a.t_rp : a.a_rp)[i + 1] - (XS ? a.t_rp : a.a_rp)[i];
+                    A x = A(0);
+                    for (int32_t k = 4 * qb; k < 4 * qb + len; ++k)
+                        x = fma((A)(XS ? vx : vy)[k], (A)from(g[q], (XS ? jx : jy)[k]), x);
+                    acc[q] = x;
+                }
+            }
+        }
+    };
+    using One = std::integral_constant<int, 1>;
+    using Two = std::integral_constant<int, 2>;
+    using Three = std::integral_constant<int, 3>;
+    using Four = std::integral_constant<int, 4>;
+
+    // ---- the halves of an iteration ------------------------------------------------
+    auto primal = [&](T tau, bool keep) {
+        const int32_t varkind = S.cs[col].varkind;
+        const int32_t kind = (int32_t)((uint32_t)varkind >> 28), var = (varkind & VAR_MASK) - x0r;
+        const double dv = S.dval[col];
+        const T* const gv[1] = {gY};
+        for (int32_t i = tid; i < nxi; i += bs) {
+            const int32_t li = i >> lw;
+            VarData d{MEM ? a.c[x0r + li] : dc[li], MEM ? a.xl[x0r + li] : dlo[li],
+                      MEM ? a.xu[x0r + li] : dhi[li]};
+            if (kind == PDLPB_OBJ_UNIT) d.c = 0.0;
+            if (li == var) {
+                if (kind == PDLPB_SET_LO) d.lo = dv;
+                else if (kind == PDLPB_SET_HI) d.hi = dv;
+                else if (kind == PDLPB_OBJ_UNIT) d.c = dv;
+            }
+            const T xk = XK[i];
+            T acc[1];
+            products(One{}, Two{}, std::true_type{}, li, gv, acc);
+            T xt, xbar;
+            primal_update<T>(xk, tau, T(d.c), T(d.lo), T(d.hi), acc[0], xt, xbar);
+            XK[i] = xbar;
+            const size_t e = (size_t)x0r * W + i;
+            gXb[e] = xbar;
+            if (keep) {
+                gXt[e] = xt;
+                gDX[e] = xt - xk;
+            }
+        }
+    };
+    auto dual = [&](T sg, T wa, bool keep) {
+        const T* const gv[1] = {gXb};
+        for (int32_t i = tid; i < nyi; i += bs) {
+            const int32_t li = i >> lw;
+            const double l = MEM ? a.rl[y0r + li] : drl[li];
+            const double u = MEM ? a.ru[y0r + li] : dru[li];
+            const T yk = YK[i], yp = YP[i], yh = YH[i];
+            T acc[1];
+            products(One{}, Four{}, std::false_type{}, li, gv, acc);
+            T yt, yn;
+            dual_update<T>(yk, yp, yh, sg, wa, T(l), T(u), acc[0], yt, yn);
+            YK[i] = yn;
+            const size_t e = (size_t)y0r * W + i;
+            gY[e] = yn;
+            if (keep) {
+                const T d = yt - yk;
+                gYt[e] = yt;
+                gDY[e] = d;
+                gDB[e] = T(barrier((double)d, l, u));
+            }
+        }
+    };
+
+    // ---- evaluation sums of the columns flagged in `need`, then the tests ----------
+    auto evaluate = [&](uint32_t need, bool full, bool stop, int32_t t) {
+        const bool mine = (need >> col) & 1u;
+        const int32_t varkind = S.cs[col].varkind;
+        const int32_t ix = (chx * 4 * W + 63) & ~63, iy = (chy * 4 * W + 63) & ~63;
+        const T* const gx[3] = {gYt, gDY, gDB};
+        const T* const gy[2] = {gXt, gDX};
+        // a lane's row of one column; chains of four rows lie W lanes apart
+        for (int32_t base = wave * 64; base < ix + iy; base += bs) {   // whole waves
+            const bool xside = base < ix;
+            const int32_t i = base - (xside ? 0 : ix) + lane, li = i >> lw;
+            double tv[NTERM];
+#pragma unroll
+            for (int q = 0; q < NTERM; ++q) tv[q] = 0.0;
+            if (mine && li < (xside ? nxr : nyr)) {
+                if (xside) {
+                    const int32_t r = x0r + li;
+                    const size_t e = (size_t)x0r * W + i;
+                    double acc[3];
+                    products(Three{}, One{}, std::true_type{}, li, gx, acc);
+                    finish_xrow(XRow{(double)gXt[e], (double)gDX[e], (double)X0[i], a.c[r], a.xl[r], a.xu[r]},
+                                acc[0], acc[1], acc[2], varkind, S.dval, col, r, tv);
+                } else {
+                    const int32_t r = y0r + li;
+                    const size_t e = (size_t)y0r * W + i;
+                    double acc[2];
+                    products(Two{}, Two{}, std::false_type{}, li, gy, acc);
+                    finish_yrow(YRow{(double)gYt[e], (double)gDY[e], (double)Y0[i], a.rl[r], a.ru[r]},
+                                acc[0], acc[1], tv);
+                }
+            }
+#pragma unroll
+            for (int q = 0; q < NTERM; ++q) {
+                const double t1 = __shfl_down(tv[q], W, 64), t2 = __shfl_down(tv[q], 2 * W, 64),
+                             t3 = __shfl_down(tv[q], 3 * W, 64);
+                const double v = (((0.0 + tv[q]) + t1) + t2) + t3;
+                const int32_t ch = li >> 2;
+                if ((li & 3) == 0 && ch < (xside ? chx : chy))
+                    chains[((size_t)((xside ? 0 : chx) + ch) * W + col) * NTERM + q] = v;
+            }
+        }
+        __syncthreads();
+        // panel sums ((c0 + c1) + c2) + c3 of this workgroup's rows
+        const int32_t npo = (chx + chy) / 4 * W * NTERM;
+        for (int32_t idx = tid; idx < npo; idx += bs) {
+            const int32_t pl = idx / (W * NTERM), cq = idx % (W * NTERM), cc = cq / NTERM, q = cq % NTERM;
+            const bool xside = pl < chx / 4;
+            const int32_t p = xside ? x0r / 16 + pl : y0r / 16 + pl - chx / 4;
+            if (!((need >> cc) & 1u)) continue;
+            const double* c = chains + (size_t)4 * pl * W * NTERM + cq;
+            const int32_t st = W * NTERM;
+            ws.panels[(size_t)(xside ? 0 : NTERM * a.npx * W) +
+                      ((size_t)q * W + cc) * (xside ? a.npx : a.npy) + p] =
+                ((c[0] + c[st]) + c[2 * st]) + c[3 * st];
+        }
+        persist_tests<T, false>(a, P, S, ws, lw, need, full, stop, t, eta);
+    };
+
+    // ---- blocks of C iterations --------------------------------------------------------
+    int32_t t0 = t0_launch;
+    for (int32_t b = 0; b < a.blocks; ++b, t0 += a.C) {
+        if (!persist_flagged(S, W, SLOT_ACTIVE)) break;
+        for (int32_t it = 1; it <= a.C; ++it) {
+            const int32_t t = t0 + it;
+            const bool stop = a.S > 0 && it % a.S == 0 && it != a.C;
+            const T tau = T(S.tau[col]), sg = T(S.sigma[col]);
+            const int32_t k = t - S.cs[col].t_anchor, t_end = S.cs[col].t_end;
+            const bool live = (S.cs[col].flags & SLOT_ACTIVE) && t <= t_end;
+            // the evaluation after this iteration reads z~ and the displacement
+            const bool keep = t == t_end || it == a.C || (it == 1 && k == 0) || stop;
+            if (live) primal(tau, keep);
+            group_arrive<false>(P);
+            if (live) primal_pre(k + 1);
+            const T wa = T(halpern_a(k));
+            group_wait<false>(P);
+            if (live) dual(sg, wa, keep);
+            group_arrive<false>(P);
+            if (live) dual_pre(k + 1, sg);
+            group_wait<false>(P);
+            const bool full = it == a.C;
+            if (it != 1 && !full && !stop) continue;
+            const uint32_t need = persist_need(S, W, full || stop, t);
+            if (!need) continue;
+            evaluate(need, full, stop, t);
+            const uint32_t fresh = full ? persist_flagged(S, W, SLOT_ACTIVE | SLOT_FRESH) : 0u;
+            if (!fresh) continue;
+            if ((fresh >> col) & 1u) {
+                // restart: anchor and dual iterate become z~ (Section 4)
+                for (int32_t i = tid; i < nxi; i += bs) {
+                    const T v = gXt[(size_t)x0r * W + i];
+                    X0[i] = v;
+                    XK[i] = v;
+                }
+                for (int32_t i = tid; i < nyi; i += bs) {
+                    const size_t e = (size_t)y0r * W + i;
+                    const T v = gYt[e];
+                    Y0[i] = v;
+                    YK[i] = v;
+                    gY[e] = v;
+                }
+                dual_pre(0, T(S.sigma[col]));
+            }
+            group_arrive<false>(P);
+            group_wait<false>(P);
+        }
+    }
+
+    // ---- copy out: the running LPs' iterates, a stopped LP's last point too ------------
+    if (have) {
+        const bool stopped = (S.cs[col].flags & SLOT_ACTIVE) == 0;
+        for (int32_t i = tid; i < nxi; i += bs) {
+            const size_t o = (size_t)(x0r + (i >> lw)) * ld + s, e = (size_t)x0r * W + i;
+            a.blk[0][o] = gXb[e];
+            a.blk[1][o] = X0[i];
+            if (stopped) a.blk[2][o] = gXt[e];
+        }
+        for (int32_t i = tid; i < nyi; i += bs) {
+            const size_t o = (size_t)(y0r + (i >> lw)) * ld + s, e = (size_t)y0r * W + i;
+            a.blk[4][o] = YK[i];
+            a.blk[5][o] = Y0[i];
+            if (stopped) a.blk[6][o] = gYt[e];
+        }
+    }
+    if (P.member == 0) persist_store_cols(a, S, c0, W, ncols);
+}
+
+template <typename T>
+__global__ __launch_bounds__(PERSIST_THREADS) void k_persist_solo(PersistArgs<T> a) {
+    extern __shared__ double persist_mem[];
+    __shared__ PersistShared S;
+    const int32_t ncols = min(a.ncols, a.g->n_cols);
+    if ((int32_t)blockIdx.x >= ncols) return;
+    PersistPart P{0, 1u, 0, a.n, 0, a.m, nullptr, 0u};
+    persist_column<T, true>(a, P, (int32_t)blockIdx.x, ncols, S, persist_mem);
+}
+
+// STAGED: chunks of one column gathered from LDS.
+template <typename T, bool STAGED>
+__global__ __launch_bounds__(STAGED ? PERSIST_STAGED_THREADS : PERSIST_THREADS)
+void k_persist_group(PersistArgs<T> a) {
+    extern __shared__ double persist_mem[];
+    __shared__ PersistShared S;
+    const int tid = threadIdx.x;
+    const int32_t n = a.n, m = a.m, W = 1 << a.lw;
+    const int32_t ncols = min(a.ncols, a.g->n_cols);
+    const int32_t nchunks = (ncols + W - 1) >> a.lw;
+    if (tid == 0) {
+        // hardware register 20 (XCC_ID), bits [3:0]
+        const int32_t x = (int32_t)__builtin_amdgcn_s_getreg((3 << 11) | 20) & (PERSIST_XCC - 1);
+        GroupLine* line = a.gc->line + x;
+        const uint32_t old = __hip_atomic_fetch_add(&line->joined, 1u, __ATOMIC_RELAXED,
+                                                    __HIP_MEMORY_SCOPE_AGENT);
+        const int32_t mem = (old & GROUP_CLOSED) || (int32_t)old >= a.members ? -1 : (int32_t)old;
+        uint32_t size = 0;
+        if (mem == 0) {
+            for (int i = 0; i < JOIN_POLLS && (int32_t)agent_load(&line->joined) < a.members; ++i)
+                __builtin_amdgcn_s_sleep(2);
+            const uint32_t v = __hip_atomic_fetch_or(&line->joined, GROUP_CLOSED, __ATOMIC_RELAXED,
+                                                     __HIP_MEMORY_SCOPE_AGENT);
+            size = (uint32_t)min((int32_t)v, a.members);
+            agent_store(&line->size, size);
+        } else if (mem > 0) {
+            // the first member is running and closes the group after a bounded wait
+            while ((size = agent_load(&line->size)) == 0) __builtin_amdgcn_s_sleep(1);
+        }
+        S.sh[0] = mem;
+        S.sh[1] = (int32_t)size;
+        S.sh[2] = x;
+    }
+    __syncthreads();
+    const int32_t nm = S.sh[1];
+    PersistPart P{S.sh[0], 0u, 0, 0, 0, 0, a.gc->line + S.sh[2], 0u};
+    if (P.member >= 0) {
+        const int32_t rx = persist_rows(n, nm), ry = persist_rows(m, nm);
+        P.parties = (uint32_t)max((n + rx - 1) / rx, (m + ry - 1) / ry);
+        if (P.member >= (int32_t)P.parties) {
+            P.member = -1;   // no rows left
+        } else {
+            P.x0r = min(P.member * rx, n);
+            P.nxr = min(rx, n - P.x0r);
+            P.y0r = min(P.member * ry, m);
+            P.nyr = min(ry, m - P.y0r);
+        }
+    }
+    if (P.member >= 0) {
+        // quads of the slice (rows padded to fours), for the size of its LDS image
+        __syncthreads();
+        if (tid == 0) S.sh[0] = S.sh[1] = 0;
+        __syncthreads();
+        int32_t qx = 0, qy = 0;
+        for (int32_t r = tid; r < P.nxr; r += blockDim.x)
+            qx += (a.t_rp[P.x0r + r + 1] - a.t_rp[P.x0r + r] + 3) / 4;
+        for (int32_t r = tid; r < P.nyr; r += blockDim.x)
+            qy += (a.a_rp[P.y0r + r + 1] - a.a_rp[P.y0r + r] + 3) / 4;
+        if (qx) atomicAdd(&S.sh[0], qx);
+        if (qy) atomicAdd(&S.sh[1], qy);
+        __syncthreads();
+        const int64_t need = STAGED ? persist_lds_column(n, m, P.nxr, P.nyr, (int64_t)S.sh[0] + S.sh[1],
+                                                         sizeof(T), 0)
+                                    : persist_lds(P.nxr, P.nyr, (int64_t)S.sh[0] + S.sh[1], W, sizeof(T));
+        const bool fits = need <= (int64_t)a.lds_bytes &&
+                          (!STAGED || persist_column_threads(P.nxr, P.nyr) <= (int32_t)blockDim.x);
+        for (;;) {
+            if (P.member == 0 && tid == 0)
+                agent_store(&P.line->chunk, __hip_atomic_fetch_add(&a.gc->next, 1u, __ATOMIC_RELAXED,
+                                                                   __HIP_MEMORY_SCOPE_AGENT));
+            group_arrive<false>(P);
+            group_wait<false>(P);
+            if (tid == 0) S.sh[3] = (int32_t)agent_load(&P.line->chunk);
+            __syncthreads();
+            const int32_t chunk = S.sh[3];
+            if (chunk >= nchunks) break;
+            if (!fits) persist_columns<T, true>(a, P, chunk, ncols, S, persist_mem);
+            else if constexpr (STAGED) persist_column<T, false>(a, P, chunk, ncols, S, persist_mem);
+            else persist_columns<T, false>(a, P, chunk, ncols, S, persist_mem);
+            __syncthreads();   // the next chunk reuses the LDS
+        }
+    }
+    // the last workgroup to leave clears the groups for the next launch
+    __syncthreads();
+    if (tid == 0) {
+        const uint32_t done = __hip_atomic_fetch_add(&a.gc->exited, 1u, __ATOMIC_RELAXED,
+                                                     __HIP_MEMORY_SCOPE_AGENT);
+        if (done == gridDim.x - 1) {
+            for (int x = 0; x < PERSIST_XCC; ++x) {
+                agent_store(&a.gc->line[x].joined, 0u);
+                agent_store(&a.gc->line[x].size, 0u);
+                agent_store(&a.gc->line[x].chunk, 0u);
+                agent_store(&a.gc->line[x].arrived, 0u);
+            }
+            agent_store(&a.gc->next, 0u);
+            agent_store(&a.gc->exited, 0u);
+        }
+    }
+}
+
+// ---------------------------------------------------------------------------
 // batch set-up
 // ---------------------------------------------------------------------------
 template <typename T>
@@ -2520,6 +3663,25 @@ hipError_t launch_tail(const TailArgs<T>& a, size_t dyn_lds, hipStream_t s) {
     return hipGetLastError();
 }
 
+template <typename T>
+hipError_t launch_persist(const PersistArgs<T>& a, int mode, int threads, hipStream_t s) {
+    const int32_t most = mode == PERSIST_STAGED ? PERSIST_STAGED_THREADS : PERSIST_THREADS;
+    if (a.ncols <= 0 || threads < 128 || threads > most || threads % 64 || a.pw_x != 4 || a.pw_y != 4)
+        return hipErrorInvalidValue;
+    if (mode != PERSIST_COLUMNS && a.lw != 0) return hipErrorInvalidValue;
+    if (mode == PERSIST_SOLO) {
+        hipLaunchKernelGGL(k_persist_solo<T>, dim3(a.ncols), dim3(threads), a.lds_bytes, s, a);
+        return hipGetLastError();
+    }
+    if ((1 << a.lw) > PERSIST_W || a.members < 1 || a.members > PERSIST_MEMBERS) return hipErrorInvalidValue;
+    const dim3 grid(PERSIST_GROUPS * a.members);
+    if (mode == PERSIST_STAGED)
+        hipLaunchKernelGGL((k_persist_group<T, true>), grid, dim3(threads), a.lds_bytes, s, a);
+    else
+        hipLaunchKernelGGL((k_persist_group<T, false>), grid, dim3(threads), a.lds_bytes, s, a);
+    return hipGetLastError();
+}
+
 hipError_t launch_reduce(const ControlArgs& a, hipStream_t s) {
     const int64_t pairs = (int64_t)2 * NTERM * a.ncols;
     if (pairs == 0) return hipSuccess;
@@ -2686,6 +3848,8 @@ template hipError_t launch_primal<double>(const StepArgs<double>&, int, int, hip
 template hipError_t launch_primal<float>(const StepArgs<float>&, int, int, hipStream_t);
 template hipError_t launch_dual<double>(const StepArgs<double>&, int, int, hipStream_t);
 template hipError_t launch_dual<float>(const StepArgs<float>&, int, int, hipStream_t);
+template hipError_t launch_persist<double>(const PersistArgs<double>&, int, int, hipStream_t);
+template hipError_t launch_persist<float>(const PersistArgs<float>&, int, int, hipStream_t);
 template hipError_t launch_tail<double>(const TailArgs<double>&, size_t, hipStream_t);
 template hipError_t launch_tail<float>(const TailArgs<float>&, size_t, hipStream_t);
 template hipError_t launch_eval<double>(const EvalArgs<double>&, hipStream_t);

@@ -81,6 +81,8 @@ constexpr int32_t TINY_LD = 4;
 constexpr double NARROW_MIN_BLOCK_BYTES = 256e6;   // one block pair (x rows + y rows)
 // largest matrix whose LPs the persistent tail iterates with one workgroup each
 constexpr int64_t TAIL_MAX_NNZ = 65536;
+// persistent blocks: iterations of one launch at most (a few milliseconds)
+constexpr int32_t PERSIST_ITERS = 1024;
 constexpr int64_t RUN_AHEAD_AFTER = 8;      // blocks of a solve before replays run ahead of the host
 constexpr double RUN_AHEAD_BYTES = 32e6;    // ... and only while one launch moves less than this
 
@@ -169,6 +171,14 @@ struct pdlpb_ctx {
     void* tail_work = nullptr;      // persistent tail: contiguous iterates of each LP
     double* tail_sum = nullptr;     //   and its evaluation chain and panel sums
     int32_t tail_cap = 0;           //   LPs the two buffers hold
+    // persistent blocks (small matrices): quads of entries (rows padded to fours) of
+    // A' and A together, and the most in a member's slices at the group sizes 16 and
+    // 32; control words; work vectors of the chunks
+    int64_t ps_q = 0, ps_q16 = 0, ps_q32 = 0;
+    GroupCtl* ps_ctl = nullptr;
+    void* ps_work = nullptr;
+    double* ps_sum = nullptr;
+    size_t cap_ps_work = 0, cap_ps_sum = 0;   // bytes
     int32_t* h_pinned = nullptr;    // n_active read-back
     // serving: the plan of the last admission's compaction (Globals, then up to
     // max_batch retire entries), read by the next serve_wait
@@ -198,12 +208,13 @@ struct pdlpb_ctx {
     // argument a captured launch holds by value is in the key or is a pointer
     // into storage that only ensure_storage replaces (and it drops the cache)
     struct GraphKey {
-        int32_t live, ld, wpb, narrow;
+        int32_t live, ld, wpb, narrow, persist;   // persist: blocks of a persistent launch, 0: one block of step launches
         int32_t tp_lanes, tp_vec, tp_blocks, td_lanes, td_vec, td_blocks;
         const void* rx;   // result blocks the compactions write (the caller's or the context's)
         const void* ry;
         bool operator==(const GraphKey& o) const {
             return live == o.live && ld == o.ld && wpb == o.wpb && narrow == o.narrow &&
+                   persist == o.persist &&
                    tp_lanes == o.tp_lanes && tp_vec == o.tp_vec && tp_blocks == o.tp_blocks &&
                    td_lanes == o.td_lanes && td_vec == o.td_vec && td_blocks == o.td_blocks &&
                    rx == o.rx && ry == o.ry;
@@ -311,9 +322,9 @@ struct pdlpb_ctx {
         for (auto& gr : graphs) (void)hipGraphExecDestroy(gr.second);
         graphs.clear();
     }
-    GraphKey graph_key() const {
-        return GraphKey{live,      ld,       wpb,    narrow ? 1 : 0, tp.lanes, tp.vec,
-                        tp.blocks, td.lanes, td.vec, td.blocks,      out(0),   out(2)};
+    GraphKey graph_key(int32_t persist) const {
+        return GraphKey{live,      ld,       wpb,    narrow ? 1 : 0, persist, tp.lanes, tp.vec,
+                        tp.blocks, td.lanes, td.vec, td.blocks,      out(0),  out(2)};
     }
 };
 
@@ -674,15 +685,174 @@ int enqueue_epoch(pdlpb_ctx* x, std::vector<std::pair<int, int>>* rec) {
     return PDLPB_OK;
 }
 
-// Launch one block of C iterations as a captured graph: the graph of the
+// ---- persistent blocks --------------------------------------------------------
+// How the live columns run in persistent blocks (launch shape `shape`).
+struct PersistPlan {
+    int mode = PERSIST_NONE;
+    int32_t lw = 0;            // chunks of 1 << lw columns
+    int32_t members = 0;       // workgroups of a group
+    int32_t threads = 0;
+    int64_t lds = 0;           // dynamic LDS of a workgroup
+};
+// Solo needs the matrix and one LP's vectors in one CU's LDS and a thread per row
+// (up to ~3000 nonzeros in FP64); grouped a member's slices, with the columns spread
+// over the XCDs: staged while every XCD has at most one column and a whole vector
+// fits, else row segments of up to 16 columns.  Where nothing fits the step launches
+// are used: they stream the matrix from the caches of the whole chip.
+PersistPlan persist_plan(const pdlpb_ctx* x, int32_t shape) {
+    PersistPlan p;
+    if (x->m < 1 || x->nnz < 1 || x->opt.restart_scope != PDLPB_RESTART_PER_LP || x->timing ||
+        x->opt.tile_lanes > 0 || x->opt.tile_vec > 0 || shape < 1 || x->pw_x != 4 || x->pw_y != 4)
+        return p;
+    const int32_t n = x->n, m = x->m;
+    const int64_t esz = x->fp32 ? sizeof(float) : sizeof(double);
+    const int64_t room = x->lds_max - PERSIST_STATIC_LDS;
+    const bool short_index = n < 65536 && m < 65536;
+    const int32_t solo_threads = persist_column_threads(n, m);
+    p.lds = persist_lds_column(n, m, n, m, x->ps_q, esz, x->npx + x->npy);
+    if (short_index && solo_threads <= PERSIST_THREADS && p.lds <= room) {
+        p.mode = PERSIST_SOLO;
+        p.threads = solo_threads;
+        return p;
+    }
+    // a grouped launch takes every CU of an XCD, and contexts that serve side by side
+    // share them; there a launch is one block, too short to repay that (640 LPs over
+    // three bases of 1000 to 10000 rows: 53 ms grouped, 45 ms with step launches)
+    if (x->serving) {
+        p.lds = 0;
+        return p;
+    }
+    // more than half of a CU's LDS below, so that a group's workgroups take a CU each
+    const int64_t half = x->lds_max / 2 + 1024;
+    if (shape <= PERSIST_GROUPS && short_index) {
+        p.members = PERSIST_STAGED_MEMBERS;
+        const int32_t rx = std::min(n, persist_rows(n, p.members)), ry = std::min(m, persist_rows(m, p.members));
+        p.lds = persist_lds_column(n, m, rx, ry, x->ps_q16, esz, 0);
+        p.threads = persist_column_threads(rx, ry);
+        if (p.threads <= PERSIST_STAGED_THREADS && p.lds <= room) {
+            p.mode = PERSIST_STAGED;
+            p.threads = PERSIST_STAGED_THREADS;   // the others help to stage
+            p.lds = std::max(p.lds, half);
+            return p;
+        }
+    }
+    while ((PERSIST_GROUPS << p.lw) < shape) p.lw += 1;
+    if ((1 << p.lw) > PERSIST_W) return p;
+    p.members = PERSIST_MEMBERS;
+    const int32_t rx = std::min(n, persist_rows(n, p.members)), ry = std::min(m, persist_rows(m, p.members));
+    p.lds = persist_lds(rx, ry, x->ps_q32, (int64_t)1 << p.lw, esz);
+    p.threads = std::max(((rx << p.lw) + 63) / 64, ((ry << p.lw) + 63) / 64) * 64;
+    p.threads = std::min(PERSIST_THREADS, std::max(256, p.threads));
+    if (p.lds > room) return p;
+    p.lds = std::max(p.lds, half);
+    p.mode = PERSIST_COLUMNS;
+    return p;
+}
+
+// Work vectors and panel sums of the chunks for `shape` columns (grouped only).
+int ensure_bytes(pdlpb_ctx* x, void** p, size_t* cap, size_t bytes);
+int ensure_persist(pdlpb_ctx* x, int32_t shape) {
+    const PersistPlan p = persist_plan(x, shape);
+    if (p.mode != PERSIST_STAGED && p.mode != PERSIST_COLUMNS) return PDLPB_OK;
+    const size_t W = (size_t)1 << p.lw, chunks = ((size_t)shape + W - 1) / W;
+    const size_t esz = x->fp32 ? sizeof(float) : sizeof(double);
+    const size_t work = chunks * W * persist_work_rows(x->n, x->m) * esz;
+    const size_t sum = chunks * persist_sum_doubles(x->npx, x->npy, (int32_t)W) * sizeof(double);
+    if (work > x->cap_ps_work || sum > x->cap_ps_sum) x->drop_graph();
+    int rc = ensure_bytes(x, &x->ps_work, &x->cap_ps_work, work);
+    if (!rc) rc = ensure_bytes(x, reinterpret_cast<void**>(&x->ps_sum), &x->cap_ps_sum, sum);
+    return rc;
+}
+
+// `blocks` blocks of C iterations of the live columns (x->live of them at most) in
+// one launch, then the compaction of the LPs that stopped.
+template <typename T>
+int enqueue_persist(pdlpb_ctx* x, int32_t blocks) {
+    const PersistPlan plan = persist_plan(x, x->live);
+    if (plan.mode == PERSIST_NONE) return x->fail(PDLPB_EDEVICE, "persistent blocks do not fit");
+    PersistArgs<T> a{};
+    a.n = x->n; a.m = x->m; a.ld = x->ld; a.C = x->opt.eval_every; a.S = stop_interval(x);
+    a.blocks = blocks;
+    a.ncols = x->live;
+    a.lw = plan.lw;
+    a.members = plan.members;
+    a.lds_bytes = (int32_t)plan.lds;
+    a.a_rp = x->a_rp; a.a_ci = x->a_ci; a.t_rp = x->t_rp; a.t_ci = x->t_ci;
+    if constexpr (sizeof(T) == 8) {
+        a.a_v = reinterpret_cast<const T*>(x->a_v64);
+        a.t_v = reinterpret_cast<const T*>(x->t_v64);
+    } else {
+        a.a_v = reinterpret_cast<const T*>(x->a_v32);
+        a.t_v = reinterpret_cast<const T*>(x->t_v32);
+    }
+    a.c = x->c; a.xl = x->xl; a.xu = x->xu; a.rl = x->rl; a.ru = x->ru;
+    a.rcode = x->rcode;
+    for (int b = 0; b < 8; ++b) a.blk[b] = static_cast<T*>(x->blk[b]);
+    a.sl = x->sl; a.ctl = x->ctl; a.rlog = x->rlog; a.g = x->g;
+    a.ca = control_args(x, 0, 1, 0);
+    a.pw_x = x->pw_x; a.pw_y = x->pw_y; a.npx = x->npx; a.npy = x->npy;
+    a.work = static_cast<T*>(x->ps_work);
+    a.wsum = x->ps_sum;
+    a.gc = x->ps_ctl;
+    HIP_TRY(x, launch_persist<T>(a, plan.mode, plan.threads, x->stream));
+    // the plan of the LPs that stopped: a control pass that tests nothing (as at an
+    // admission, every running LP counts as it is), moves t0 on and plans
+    ControlArgs c = control_args(x, 0, 1, 1, 1);
+    c.admit_plan = 1;
+    c.block = blocks * x->opt.eval_every;
+    HIP_TRY(x, launch_control(c, x->stream));
+    T* const* b = reinterpret_cast<T* const*>(x->blk);
+    T* const r[4] = {static_cast<T*>(x->out(0)), static_cast<T*>(x->out(1)),
+                     static_cast<T*>(x->out(2)), static_cast<T*>(x->out(3))};
+    HIP_TRY(x, launch_compact<T>(x->n, x->m, x->ld, x->live, b, r, x->retire, x->moves, x->fresh,
+                                 x->sl, x->g, x->stream));
+    return PDLPB_OK;
+}
+
+// Grouped launches of a device run one after another: two at once would share its
+// XCDs, each group closing with the workgroups it got.  begin() orders the
+// context's stream after the last one, end() marks this one; the lock is held in
+// between only, while the launch is queued.
+struct DeviceTurn {
+    std::mutex mu;
+    hipEvent_t ev = nullptr;   // end of the last grouped launch; lives as long as the process
+};
+DeviceTurn g_turn[MAX_DEVICES];
+
+struct GroupTurn {
+    pdlpb_ctx* x;
+    std::unique_lock<std::mutex> lk;
+    explicit GroupTurn(pdlpb_ctx* c) : x(c) {}
+    DeviceTurn* turn() const {
+        const int mode = persist_plan(x, x->live).mode;
+        const bool grouped = mode == PERSIST_STAGED || mode == PERSIST_COLUMNS;
+        return grouped && x->device >= 0 && x->device < MAX_DEVICES ? &g_turn[x->device] : nullptr;
+    }
+    int begin() {
+        DeviceTurn* t = turn();
+        if (!t) return PDLPB_OK;
+        lk = std::unique_lock<std::mutex>(t->mu);
+        if (!t->ev) HIP_TRY(x, hipEventCreateWithFlags(&t->ev, hipEventDisableTiming));
+        else HIP_TRY(x, hipStreamWaitEvent(x->stream, t->ev, 0));
+        return PDLPB_OK;
+    }
+    int end() {
+        DeviceTurn* t = turn();
+        if (t) HIP_TRY(x, hipEventRecord(t->ev, x->stream));
+        return PDLPB_OK;
+    }
+};
+
+// Launch one block of C iterations (persist = 0) or a persistent launch of `persist`
+// blocks as a captured graph: the graph of the
 // current launch configuration is reused across batches and serving rounds,
 // and captured on first use.  The cache is bounded; past the bound it starts
 // over.
 constexpr size_t MAX_GRAPHS = 64;
 
 template <typename T>
-int replay_epoch(pdlpb_ctx* x) {
-    const pdlpb_ctx::GraphKey key = x->graph_key();
+int replay_epoch(pdlpb_ctx* x, int32_t persist = 0) {
+    const pdlpb_ctx::GraphKey key = x->graph_key(persist);
     hipGraphExec_t exec = nullptr;
     for (auto& gr : x->graphs)
         if (gr.first == key) exec = gr.second;
@@ -695,7 +865,7 @@ int replay_epoch(pdlpb_ctx* x) {
         }
         hipGraph_t gr = nullptr;
         HIP_TRY(x, hipStreamBeginCapture(x->stream, hipStreamCaptureModeThreadLocal));
-        int r2 = enqueue_epoch<T>(x, nullptr);
+        int r2 = persist ? enqueue_persist<T>(x, persist) : enqueue_epoch<T>(x, nullptr);
         hipError_t e = hipStreamEndCapture(x->stream, &gr);
         if (r2) {
             if (gr) (void)hipGraphDestroy(gr);
@@ -1140,7 +1310,7 @@ int run_solve(pdlpb_ctx* x, double tol, int32_t max_iters) {
         ~Wide() { leave_narrow(x); }
     } wide{x};
     for (int64_t ep = 0; n_active > 0; ++ep) {
-        if (launched > max_epochs + 1) return x->fail(PDLPB_EDEVICE, "solve did not terminate");
+        if (launched > max_epochs + 1 + PERSIST_ITERS) return x->fail(PDLPB_EDEVICE, "solve did not terminate");
         if (tail_applies(x, n_cols)) {
             if (in_flight) {
                 // the counts of the block running ahead decide first
@@ -1186,7 +1356,23 @@ int run_solve(pdlpb_ctx* x, double tol, int32_t max_iters) {
                 tune_now = !hit && !x->timing;
             }
         }
-        const bool ahead = use_graphs && !tune_now && launched >= RUN_AHEAD_AFTER &&
+        const bool persist = persist_plan(x, x->live).mode != PERSIST_NONE;
+        if (persist && !in_flight) {
+            const int32_t blocks = std::max(1, PERSIST_ITERS / x->opt.eval_every);
+            rc = ensure_persist(x, x->live);
+            if (rc) return rc;
+            {
+                GroupTurn turn(x);
+                rc = turn.begin();
+                if (!rc) rc = use_graphs ? replay_epoch<T>(x, blocks) : enqueue_persist<T>(x, blocks);
+                if (!rc) rc = turn.end();
+            }
+            if (!rc) rc = read_counts(x, &n_active, &n_cols);
+            if (rc) return rc;
+            launched += blocks;
+            continue;
+        }
+        const bool ahead = !persist && use_graphs && !tune_now && launched >= RUN_AHEAD_AFTER &&
                            launch_bytes(x, x->live) < RUN_AHEAD_BYTES;
         if (in_flight && !ahead) {
             // a synchronous block follows: read the counts of the block ahead first
@@ -1910,6 +2096,30 @@ int pdlpb_create(pdlpb_ctx** out, int32_t m, int32_t n, int64_t nnz, const int64
         if ((e = up(&x->rcode, code.data(), (size_t)m)) != hipSuccess) return dev_fail(e, "upload rows");
     }
     if ((e = x->alloc(&x->g, sizeof(Globals))) != hipSuccess) return dev_fail(e, "alloc");
+    x->pw_x = eval_rows_per_wave(n);
+    x->pw_y = eval_rows_per_wave(m);
+    x->npx = (n + 4 * x->pw_x - 1) / (4 * x->pw_x);
+    x->npy = (m + 4 * x->pw_y - 1) / (4 * x->pw_y);
+    {   // row slices of a full group (persistent blocks)
+        auto quads = [&](int32_t members) {
+            const int32_t px = persist_rows(n, members), py = m > 0 ? persist_rows(m, members) : 1;
+            int64_t most = 0;
+            for (int32_t k = 0; k < members; ++k) {
+                int64_t q = 0;
+                for (int32_t i = std::min<int64_t>((int64_t)k * px, n); i < std::min<int64_t>((int64_t)(k + 1) * px, n); ++i)
+                    q += (h_trp[i + 1] - h_trp[i] + 3) / 4;
+                for (int32_t i = std::min<int64_t>((int64_t)k * py, m); i < std::min<int64_t>((int64_t)(k + 1) * py, m); ++i)
+                    q += (h_arp[i + 1] - h_arp[i] + 3) / 4;
+                most = std::max(most, q);
+            }
+            return most;
+        };
+        x->ps_q = quads(1);
+        x->ps_q16 = quads(PERSIST_STAGED_MEMBERS);
+        x->ps_q32 = quads(PERSIST_MEMBERS);
+        const std::vector<GroupCtl> zero(1);
+        if ((e = up(&x->ps_ctl, zero.data(), 1)) != hipSuccess) return dev_fail(e, "alloc");
+    }
 
     x->h_xl.assign(l_in, l_in + n);
     x->h_xu.assign(u_in, u_in + n);
@@ -1940,10 +2150,6 @@ int pdlpb_create(pdlpb_ctx** out, int32_t m, int32_t n, int64_t nnz, const int64
     hg.r_prev = -1.0;
     e = hipMemcpy(x->g, &hg, sizeof(Globals), hipMemcpyHostToDevice);
     if (e != hipSuccess) return dev_fail(e, "upload globals");
-    x->pw_x = eval_rows_per_wave(n);
-    x->pw_y = eval_rows_per_wave(m);
-    x->npx = (n + 4 * x->pw_x - 1) / (4 * x->pw_x);
-    x->npy = (m + 4 * x->pw_y - 1) / (4 * x->pw_y);
     *out = x;
     return PDLPB_OK;
 }
@@ -2632,8 +2838,12 @@ int serve_launch(pdlpb_ctx* x) {
         x->live = shape;
         choose_tile(x, shape);
     }
+    const int32_t persist = persist_plan(x, x->live).mode != PERSIST_NONE ? 1 : 0;
     if (x->opt.use_graphs && !x->timing) {
-        rc = replay_epoch<T>(x);
+        rc = replay_epoch<T>(x, persist);
+        if (rc) return rc;
+    } else if (persist) {
+        rc = enqueue_persist<T>(x, 1);
         if (rc) return rc;
     } else {
         rc = enqueue_epoch<T>(x, nullptr);

@@ -217,6 +217,109 @@ __host__ __device__ inline size_t tail_sum_doubles(int32_t npx, int32_t npy) {
     return (size_t)(4 * (npx + npy) + (npx + npy) + 2) * NTERM;
 }
 
+// ---- persistent blocks of small matrices -----------------------------------------
+// Several blocks of C iterations, with their evaluations, restarts and stops, in
+// one launch.  Solo: one workgroup per LP holds the matrix and the LP's vectors in
+// LDS.  Grouped: the workgroups of one XCD share a chunk of columns, each owning a
+// slice of the rows in LDS, and meet at barriers in that XCD's L2; staged: the chunk
+// is one column, whose vectors every member copies into LDS for its gathers.
+enum : int { PERSIST_NONE = 0, PERSIST_SOLO = 1, PERSIST_STAGED = 2, PERSIST_COLUMNS = 3 };
+constexpr int32_t PERSIST_THREADS = 1024;
+constexpr int32_t PERSIST_STAGED_THREADS = 512;
+constexpr int32_t PERSIST_W = 16;          // columns of a chunk at most
+constexpr int32_t PERSIST_MEMBERS = 32;    // workgroups of a group at most (CUs of an XCD)
+constexpr int32_t PERSIST_STAGED_MEMBERS = 16;
+constexpr int32_t PERSIST_GROUPS = 8;      // XCDs
+constexpr int64_t PERSIST_STATIC_LDS = 6144;   // bound on the static arrays
+constexpr int32_t PERSIST_XCC = 16;        // values of the XCC_ID register
+
+struct GroupLine {              // one group's words, a cache line of their own
+    uint32_t joined;            // workgroups that joined; the top bit closes the group
+    uint32_t size;              // members, once closed
+    uint32_t chunk;             // chunk being worked on
+    uint32_t arrived;           // arrivals at the group's barriers
+    uint32_t pad[28];
+};
+struct GroupCtl {               // all zero between launches
+    GroupLine line[PERSIST_XCC];
+    uint32_t next;              // next chunk to take
+    uint32_t exited;            // workgroups that are done
+    uint32_t pad[30];
+};
+
+// state of one column, kept in LDS by every workgroup of its group
+struct PersistCol {
+    int32_t t_anchor, t_end, varkind, flags;
+};
+
+template <typename T>
+struct PersistArgs {
+    int32_t n, m, ld, C, S;
+    int32_t blocks;            // blocks of C iterations at most
+    int32_t ncols;             // columns covered: slots [0, min(ncols, live count))
+    int32_t lw;                // a chunk holds 1 << lw columns (solo: 0)
+    int32_t members;           // workgroups wanted per group
+    int32_t lds_bytes;         // dynamic LDS of the launch
+    const int32_t* a_rp; const int32_t* a_ci; const T* a_v;    // A (m x n)
+    const int32_t* t_rp; const int32_t* t_ci; const T* t_v;    // A' (n x m)
+    const double *c, *xl, *xu, *rl, *ru;
+    const int8_t* rcode;       // per row of A: 1 if its lower bound is -inf, | 2 if its upper is +inf
+    T* blk[8];                 // Xbar, X0, Xt, DX, Y, Y0, Yt, DY (row-major, stride ld)
+    Slots sl;
+    SlotCtl* ctl;
+    int32_t* rlog;
+    Globals* g;
+    ControlArgs ca;            // stopping, infeasibility and restart parameters
+    int32_t pw_x, pw_y, npx, npy;
+    T* work;                   // grouped: per chunk persist_work_rows(n, m) x W
+    double* wsum;              // grouped: per chunk persist_sum_doubles
+    GroupCtl* gc;
+};
+
+// Rows of one side that a member of a group of `nm` owns: whole evaluation panels
+// of 16 rows.
+__host__ __device__ inline int32_t persist_rows(int32_t rows, int32_t nm) {
+    const int32_t per = (rows + nm - 1) / nm;
+    return (per + 15) / 16 * 16;
+}
+// LDS of a workgroup that owns rx x rows and ry y rows with q quads of entries (rows
+// padded to fours), at W columns: iterates and anchors and the prepared parts of the
+// updates, objective and bounds, evaluation chains, first quads, offsets and values.
+__host__ __device__ inline int64_t persist_lds(int64_t rx, int64_t ry, int64_t q, int64_t W, int64_t esz) {
+    const int64_t ch = ((rx + 15) / 16 + (ry + 15) / 16) * 4;
+    return (2 * rx + 4 * ry) * W * esz + (3 * rx + 2 * ry) * 8 + ch * W * NTERM * 8 + (rx + ry + 2) * 4 +
+           q * (16 + 4 * esz) + 24 * 16;   // each array starts at a multiple of 16 bytes
+}
+// ... of a workgroup that gathers one column's whole vectors from LDS; solo (np
+// panels) also the evaluation's vectors and the panel sums.
+__host__ __device__ inline int64_t persist_lds_column(int64_t n, int64_t m, int64_t rx, int64_t ry,
+                                                      int64_t q, int64_t esz, int64_t np) {
+    const int64_t ch = ((rx + 15) / 16 + (ry + 15) / 16) * 4;
+    int64_t b = (n + m + 2) * esz + ch * NTERM * 8 + (rx + ry + 2) * 4 + (q + 1) * (8 + 4 * esz);
+    if (np > 0) b += (2 * (n + 1) + 3 * (m + 1)) * esz + np * NTERM * 8;
+    return b + 24 * 16;
+}
+// Threads of such a workgroup: one per row, waves of one side only, at least two waves.
+__host__ __device__ inline int32_t persist_column_threads(int32_t rx, int32_t ry) {
+    const int32_t t = (rx + 63) / 64 * 64 + (ry + 63) / 64 * 64;
+    return t < 128 ? 128 : t;
+}
+// Work vectors of a chunk, rows per column, each with a row of zeros: Xbar, Xt, DX (n),
+// Y, Yt, DY, its barrier projection (m); a member's slice that does not fit in LDS
+// (2 n + 4 m)
+__host__ __device__ inline size_t persist_stride(int32_t rows) {   // with the row of zeros
+    return ((size_t)rows + 4) & ~(size_t)3;
+}
+__host__ __device__ inline size_t persist_work_rows(int32_t n, int32_t m) {
+    return 5 * persist_stride(n) + 8 * persist_stride(m);
+}
+// Sums of a chunk: panel sums, their reductions, the columns' step sizes and states,
+// the chain sums of members without LDS
+__host__ __device__ inline size_t persist_sum_doubles(int32_t npx, int32_t npy, int32_t W) {
+    return (size_t)(npx + npy) * NTERM * W + 2 * NTERM * PERSIST_W +
+           (sizeof(PersistCol) / 8 + 2) * PERSIST_W + (size_t)(npx + npy) * 4 * NTERM * W;
+}
+
 // ---- shared start ------------------------------------------------------------
 // A batch whose running LPs all start from one warm point (or from zero), with
 // the same step sizes for every LP of one base LP, makes its first iteration
@@ -280,6 +383,12 @@ hipError_t launch_control(const ControlArgs& a, hipStream_t s);
 // its results to the result blocks.
 template <typename T>
 hipError_t launch_tail(const TailArgs<T>& a, size_t dyn_lds, hipStream_t s);
+
+// Up to a.blocks blocks of C iterations of the live columns in one launch; a
+// column that stops keeps its slot, flagged SLOT_RETIRE, until the next
+// compaction.  mode: PERSIST_SOLO, PERSIST_STAGED or PERSIST_COLUMNS.
+template <typename T>
+hipError_t launch_persist(const PersistArgs<T>& a, int mode, int threads, hipStream_t s);
 
 // Shared start.  launch_sp_iterate: the first iteration (t = 0) of every base
 // LP (x^0, x~, x-bar, dx; y^0, y~, y^1, dy), then of every LP at its variable

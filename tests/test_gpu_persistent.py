@@ -1,0 +1,121 @@
+"""Blocks of iterations of small matrices in one launch (a workgroup per LP, or the
+workgroups of an XCD per chunk of columns) against the step launches, bit for bit:
+results, statuses, iteration counts, restart logs and last iterates.  Kernel timing
+runs a solve on the step launches, which is the reference here."""
+from __future__ import annotations
+
+import numpy as np
+import pytest
+
+from gpu_common import cfg2_setup, make_ctx
+from workloads import (choose_vars, make_cfg1, make_cfg2, make_facility, make_packing, make_setcover,
+                       make_tiny, obbt_deltas)
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def P():
+    import paper_2601_21990_amd.pdlpb as P
+    return P
+
+
+def _solve(ctx, D, tol, K, timing, warm=None):
+    ctx.set_kernel_timing(timing)
+    kw = {} if warm is None else dict(x_warm=warm.x, y_warm=warm.y, w_warm=np.full(len(D), warm.w))
+    ctx.set_batch(D, **kw)
+    ctx.solve(tol=tol, max_iters=K)
+    out = ctx.get_batch()
+    out["dobj"] = ctx.dual_objective()
+    return out, [ctx.get_trace(j) for j in range(len(D))]
+
+
+def _same(inst, D, tol, K, warm=None, **kw):
+    with make_ctx(inst, **kw) as ctx:
+        a, ta = _solve(ctx, D, tol, K, False, warm)
+        b, tb = _solve(ctx, D, tol, K, True, warm)
+        c, _ = _solve(ctx, D, tol, K, False, warm)     # the groups' words are clear again
+    for key in a:
+        assert np.array_equal(a[key], b[key], equal_nan=True), key
+        assert np.array_equal(a[key], c[key], equal_nan=True), key
+    for x, y in zip(ta, tb):
+        assert np.array_equal(x["x_iter"], y["x_iter"]) and np.array_equal(x["y_iter"], y["y_iter"])
+        assert x["w"] == y["w"] and x["restart_log"] == y["restart_log"]
+    return a
+
+
+@pytest.mark.parametrize("prec", ["fp64", "fp32"])
+@pytest.mark.parametrize("make, B", [
+    (lambda: make_tiny(3, m=3, n=5), 2),                # one wave a side, a few rows
+    (make_cfg1, 6),                                     # empty rows and columns
+    (lambda: make_cfg2(m=64, n=128), 5),                # whole waves
+    (lambda: make_cfg2(m=65, n=143), 3),                # remainders of panels and waves
+    (lambda: make_facility(F=6, C=24, k=4), 7),         # rows longer than the held indices
+    (lambda: make_cfg2(m=200, n=500), 300),             # more LPs than compute units
+], ids=["tiny", "empty", "64x128", "65x143", "long", "200x500"])
+def test_solo(P, make, B, prec):
+    inst = make()
+    precision = P.MIXED32 if prec == "fp32" else P.FP64
+    n = inst.n
+    D = obbt_deltas(choose_vars(n, min(n, (B + 1) // 2), seed=B))[:B]
+    _same(inst, D, 1e-5, 700, precision=precision)
+    for K in (2, 65, 100):                              # limits at, after and inside a block
+        _same(inst, D[:3], 0.0, K, precision=precision)
+
+
+@pytest.mark.parametrize("prec", ["fp64", "fp32"])
+@pytest.mark.parametrize("m, n, B", [
+    (2000, 5000, 1), (2000, 5000, 8),                   # one column per XCD
+    (1037, 2611, 3),                                    # odd rows: slices and copies with remainders
+    (2000, 5000, 9), (2000, 5000, 31), (2000, 5000, 64), (1500, 3701, 100), (1000, 2500, 128),
+])
+def test_grouped(P, m, n, B, prec):
+    inst = make_cfg2(m=m, n=n)
+    D = obbt_deltas(choose_vars(n, (B + 1) // 2, seed=B))[:B]
+    precision = P.MIXED32 if prec == "fp32" else P.FP64
+    _same(inst, D, 1e-4, 600, precision=precision, eval_every=32)
+    _same(inst, D, 0.0, 45, precision=precision, eval_every=32, stop_every=8)
+
+
+@pytest.mark.parametrize("stop", [0, 8])
+def test_grouped_converged(P, stop):
+    """Strong branching to the end: restarts, stops at every kind of test, an
+    infeasible branch, compactions between the launches."""
+    inst, lp, eta, base, D = cfg2_setup()
+    _same(inst, D, 1e-4, 20000, warm=base, step_size=eta, eval_every=32, stop_every=stop)
+    _same(inst, D[:5], 1e-6, 20000, warm=base, step_size=eta, eval_every=32, stop_every=stop)
+
+
+@pytest.mark.parametrize("make", [lambda: make_facility(F=40, C=300), lambda: make_setcover(m=2000, n=4000),
+                                  lambda: make_packing(m=400, n=900)], ids=["facility", "cover", "packing"])
+@pytest.mark.parametrize("B", [6, 40])
+def test_grouped_structured(P, make, B):
+    """Columns of over a hundred entries, 0/1 matrices, diagonal scaling."""
+    inst = make()
+    D = obbt_deltas(choose_vars(inst.n, B // 2, seed=B))
+    _same(inst, D, 1e-4, 500, scaling=1, dual_tol=1e-8)
+
+
+def test_two_contexts_at_once(P):
+    """Two threads solve on grouped launches of one device: each gets its results."""
+    import threading
+    inst = [make_cfg2(rep=r, m=2000, n=5000) for r in range(2)]
+    D = [obbt_deltas(choose_vars(5000, 12, seed=r)) for r in range(2)]
+    ref, got = [], [None, None]
+    ctx = [make_ctx(i, eval_every=32) for i in inst]
+    for r in range(2):
+        ref.append(_solve(ctx[r], D[r], 1e-4, 400, True)[0])
+
+    def work(r):
+        for _ in range(5):
+            got[r] = _solve(ctx[r], D[r], 1e-4, 400, False)[0]
+
+    th = [threading.Thread(target=work, args=(r,)) for r in range(2)]
+    for t in th:
+        t.start()
+    for t in th:
+        t.join()
+    for r in range(2):
+        for key in ref[r]:
+            assert np.array_equal(ref[r][key], got[r][key], equal_nan=True), key
+        ctx[r].close()
