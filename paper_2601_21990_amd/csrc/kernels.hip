@@ -1,10 +1,15 @@
 // gfx950 kernels of the batched restarted PDHG solver.
 //
-// Dense blocks are row-major with row stride `ld`: element (row i, LP slot s)
-// lives at i*ld + s, so one row of a block holds that row's entries of every
-// LP of the batch contiguously.  A sparse row's product with a block is then
-// a sum of contiguous row segments of the block, and a group of lanes that
-// covers consecutive slots reads each segment with unit stride.
+// Dense blocks (rows x ld, a column per LP slot) are stored as column tiles of
+// 128 bytes per row: slots [t W, t W + W) of every row lie together, row after
+// row with stride W = 128 / sizeof(T) (a last tile of fewer columns with its own
+// width; block_offset, block_stride).  A sparse row's product with a block is
+// then a sum of whole cache lines of one tile, and an XCD that works on one tile
+// gathers from rows * 128 bytes, which its L2 keeps at mid sizes: in blocks of
+// one row-major stride the same lines, ld elements apart, crowd into a part of
+// the L2's sets.  At 20k x 50k, 8 nonzeros per column, 256 LPs, the gathers and
+// streams of one primal / dual step alone take 59 / 70 us (FP64) and 30 / 36 us
+// (FP32) in tiles, 79 / 90 and 40 / 45 us row-major, each XCD on one tile in both.
 //
 // Every lane sums its row's nonzeros sequentially in CSR order, whatever the
 // tile shape, so each LP's arithmetic is independent of how many LPs share the
@@ -171,15 +176,43 @@ struct RowOps {
     Head<T, EW> h;
 };
 
+// Column tile and row block of a workgroup.  gx = 0: the launch's y and x index.
+// gx > 0: (tile, row block) pairs, tile by tile with gx row blocks each, dealt to
+// the eight XCDs as eight contiguous runs (workgroup w runs on XCD w mod 8), so
+// that an XCD gathers from one tile at a time, whatever their number; the runs
+// cover the live columns only.
+struct TileOf {
+    int32_t tile, block, blocks;
+};
+template <int W>
+__device__ __forceinline__ TileOf tile_of(int32_t gx, int32_t ncols) {
+    if (gx <= 0) return TileOf{(int32_t)blockIdx.y, (int32_t)blockIdx.x, (int32_t)gridDim.x};
+    const int32_t total = (ncols + W - 1) / W * gx, run = (total + 7) / 8;
+    const int32_t i = (int32_t)(blockIdx.x >> 3), q = (int32_t)(blockIdx.x & 7) * run + i;
+    if (i >= run || q >= total) return TileOf{-1, 0, gx};
+    return TileOf{q / gx, q % gx, gx};
+}
+
+// A lane's columns in the blocks of a step: offset of its first slot in the
+// updated and in the gathered block, and the row stride of their tile.
+struct LaneCols {
+    size_t z, g;
+    int32_t st;
+};
+template <typename T>
+__device__ __forceinline__ LaneCols lane_cols(const StepArgs<T>& a, int32_t s0) {
+    return LaneCols{block_offset<T>(a.rows, s0), block_offset<T>(a.grows, s0), block_stride<T>(a.ld, s0)};
+}
+
 template <typename T, int VEC, int EW, bool PRIMAL>
-__device__ __forceinline__ void load_row(const StepArgs<T>& a, int32_t row, int32_t s0,
+__device__ __forceinline__ void load_row(const StepArgs<T>& a, int32_t row, int32_t s0, const LaneCols& lc,
                                          RowOps<T, VEC, EW>& op) {
     op.kb = a.rp[row];
     op.ke = a.rp[row + 1];
 #pragma unroll
     for (int v = 0; v < VEC; ++v) {
         if (s0 + v < a.ncols) {
-            const size_t e = (size_t)row * a.ld + s0 + v;
+            const size_t e = lc.z + (size_t)row * lc.st + v;
             op.z[v] = a.Z[e];
             op.z0[v] = a.Z0[e];
         }
@@ -203,7 +236,7 @@ __device__ __forceinline__ void load_row(const StepArgs<T>& a, int32_t row, int3
 
 template <typename T, int VEC, int EW>
 __device__ __forceinline__ void row_product(const StepArgs<T>& a, const RowOps<T, VEC, EW>& op,
-                                            int32_t s0, T* acc) {
+                                            const LaneCols& lc, T* acc) {
 #pragma unroll
     for (int v = 0; v < VEC; ++v) acc[v] = T(0);
     if constexpr (EW > 0) {
@@ -213,7 +246,7 @@ __device__ __forceinline__ void row_product(const StepArgs<T>& a, const RowOps<T
 #pragma unroll
             for (int u = 0; u < CH; ++u) {
                 if (op.h.j[c0 + u] >= 0)
-                    VecT<T, VEC>::load(a.G + (size_t)op.h.j[c0 + u] * a.ld + s0, g[u]);
+                    VecT<T, VEC>::load(a.G + lc.g + (size_t)op.h.j[c0 + u] * lc.st, g[u]);
             }
 #pragma unroll
             for (int u = 0; u < CH; ++u) {
@@ -240,7 +273,7 @@ __device__ __forceinline__ void row_product(const StepArgs<T>& a, const RowOps<T
         T g[CH][VEC];
 #pragma unroll
         for (int u = 0; u < CH; ++u) {
-            if (k0 + u < ke) VecT<T, VEC>::load(a.G + (size_t)j[u] * a.ld + s0, g[u]);
+            if (k0 + u < ke) VecT<T, VEC>::load(a.G + lc.g + (size_t)j[u] * lc.st, g[u]);
         }
 #pragma unroll
         for (int u = 0; u < CH; ++u) {
@@ -335,10 +368,12 @@ __global__ __launch_bounds__(256) void k_primal(StepArgs<T> a) {
     const int lane = threadIdx.x & 63;
     const int wave = threadIdx.x >> 6;
     fetch_args(a, a.sl.tau);
-    const int32_t s0 = blockIdx.y * (G * VEC) + (lane % G) * VEC;
-    int32_t rw = (int32_t)blockIdx.x * a.wpb + wave;
-    if (s0 >= a.ncols || rw * RPW >= a.rows) return;
-    const int32_t wstride = (int32_t)gridDim.x * a.wpb;
+    const TileOf w = tile_of<G * VEC>(a.gx, min(a.ncols, a.gx > 0 ? a.g->n_cols : a.ncols));
+    const int32_t s0 = w.tile * (G * VEC) + (lane % G) * VEC;
+    int32_t rw = w.block * a.wpb + wave;
+    if (w.tile < 0 || s0 >= a.ncols || rw * RPW >= a.rows) return;
+    const int32_t wstride = w.blocks * a.wpb;
+    const LaneCols lc = lane_cols(a, s0);
 
     // one round of loads: batch state, slot state, first row (the batch state is
     // read through vector loads, which queue in order with the others)
@@ -358,7 +393,7 @@ __global__ __launch_bounds__(256) void k_primal(StepArgs<T> a) {
     }
     int32_t row = rw * RPW + lane / G;
     RowOps<T, VEC, EW> op;
-    if (row < a.rows) load_row<T, VEC, EW, true>(a, row, s0, op);
+    if (row < a.rows) load_row<T, VEC, EW, true>(a, row, s0, lc, op);
 
     const int32_t ncols = min(a.ncols, gcols);
     if (s0 >= ncols) return;
@@ -393,12 +428,12 @@ __global__ __launch_bounds__(256) void k_primal(StepArgs<T> a) {
 
     auto step = [&](int32_t r, const RowOps<T, VEC, EW>& o) {
         T acc[VEC];
-        row_product<T, VEC, EW>(a, o, s0, acc);
+        row_product<T, VEC, EW>(a, o, lc, acc);
 #pragma unroll
         for (int v = 0; v < VEC; ++v) {
             const int32_t s = s0 + v;
             if (!live[v]) continue;
-            const size_t e = (size_t)r * a.ld + s;
+            const size_t e = lc.z + (size_t)r * lc.st + v;
             const VarData d = var_data(varkind[v], a.sl.dval, s, r, o.c, o.lo, o.hi);
             const int32_t k = kk[v];
             T xk, xt, xbar;
@@ -415,7 +450,7 @@ __global__ __launch_bounds__(256) void k_primal(StepArgs<T> a) {
         row = rw * RPW + lane / G;
         if (row >= a.rows) continue;
         RowOps<T, VEC, EW> o;
-        load_row<T, VEC, EW, true>(a, row, s0, o);
+        load_row<T, VEC, EW, true>(a, row, s0, lc, o);
         step(row, o);
     }
 }
@@ -432,10 +467,12 @@ __global__ __launch_bounds__(256) void k_dual(StepArgs<T> a) {
     const int lane = threadIdx.x & 63;
     const int wave = threadIdx.x >> 6;
     fetch_args(a, a.sl.sigma);
-    const int32_t s0 = blockIdx.y * (G * VEC) + (lane % G) * VEC;
-    int32_t rw = (int32_t)blockIdx.x * a.wpb + wave;
-    if (s0 >= a.ncols || rw * RPW >= a.rows) return;
-    const int32_t wstride = (int32_t)gridDim.x * a.wpb;
+    const TileOf w = tile_of<G * VEC>(a.gx, min(a.ncols, a.gx > 0 ? a.g->n_cols : a.ncols));
+    const int32_t s0 = w.tile * (G * VEC) + (lane % G) * VEC;
+    int32_t rw = w.block * a.wpb + wave;
+    if (w.tile < 0 || s0 >= a.ncols || rw * RPW >= a.rows) return;
+    const int32_t wstride = w.blocks * a.wpb;
+    const LaneCols lc = lane_cols(a, s0);
 
     // one round of loads: batch state, slot state, first row (the batch state is
     // read through vector loads, which queue in order with the others)
@@ -455,7 +492,7 @@ __global__ __launch_bounds__(256) void k_dual(StepArgs<T> a) {
     }
     int32_t row = rw * RPW + lane / G;
     RowOps<T, VEC, EW> op;
-    if (row < a.rows) load_row<T, VEC, EW, false>(a, row, s0, op);
+    if (row < a.rows) load_row<T, VEC, EW, false>(a, row, s0, lc, op);
 
     const int32_t ncols = min(a.ncols, gcols);
     if (s0 >= ncols) return;
@@ -486,11 +523,11 @@ __global__ __launch_bounds__(256) void k_dual(StepArgs<T> a) {
     auto step = [&](int32_t r, const RowOps<T, VEC, EW>& o) {
         const T l = T(o.lo), u = T(o.hi);
         T acc[VEC];
-        row_product<T, VEC, EW>(a, o, s0, acc);
+        row_product<T, VEC, EW>(a, o, lc, acc);
 #pragma unroll
         for (int v = 0; v < VEC; ++v) {
             if (!live[v]) continue;
-            const size_t e = (size_t)r * a.ld + s0 + v;
+            const size_t e = lc.z + (size_t)r * lc.st + v;
             const T yk = o.z[v];
             T yt, yn;
             dual_point<T>(yk, o.z0[v], sig[v], wa[v], wb[v], l, u, acc[v], yt, yn);
@@ -506,7 +543,7 @@ __global__ __launch_bounds__(256) void k_dual(StepArgs<T> a) {
         row = rw * RPW + lane / G;
         if (row >= a.rows) continue;
         RowOps<T, VEC, EW> o;
-        load_row<T, VEC, EW, false>(a, row, s0, o);
+        load_row<T, VEC, EW, false>(a, row, s0, lc, o);
         step(row, o);
     }
 }
@@ -545,13 +582,13 @@ struct YRowIn {
 // (KKT: a stopping test alone, which reads z~ only)
 template <typename T, bool KKT = false>
 __device__ __forceinline__ XRowIn<T> load_xrow(const EvalArgs<T>& a, int32_t i, int32_t s) {
-    const size_t e = (size_t)i * a.ld + s;
+    const size_t e = block_at<T>(a.ld, a.n, i, s);
     if constexpr (KKT) return XRowIn<T>{a.Xt[e], T(0), T(0), a.c[i], a.xl[i], a.xu[i]};
     return XRowIn<T>{a.Xt[e], a.DX[e], a.X0[e], a.c[i], a.xl[i], a.xu[i]};
 }
 template <typename T, bool KKT = false>
 __device__ __forceinline__ YRowIn<T> load_yrow(const EvalArgs<T>& a, int32_t i, int32_t s) {
-    const size_t e = (size_t)i * a.ld + s;
+    const size_t e = block_at<T>(a.ld, a.m, i, s);
     if constexpr (KKT) return YRowIn<T>{a.Yt[e], T(0), T(0), a.rl[i], a.ru[i]};
     return YRowIn<T>{a.Yt[e], a.DY[e], a.Y0[e], a.rl[i], a.ru[i]};
 }
@@ -704,7 +741,7 @@ __global__ __launch_bounds__(256) void k_eval(EvalArgs<T> a) {
 #pragma unroll
                 for (int u = 0; u < CH; ++u) {
                     if (k0 + u < kend) {
-                        const size_t f = (size_t)jj[u] * a.ld + s;
+                        const size_t f = block_at<T>(a.ld, a.m, jj[u], s);
                         yv[u] = a.Yt[f];
                         if constexpr (!KKT) {
                             dv[u] = a.DY[f];
@@ -768,7 +805,7 @@ __global__ __launch_bounds__(256) void k_eval(EvalArgs<T> a) {
 #pragma unroll
                 for (int u = 0; u < CH; ++u) {
                     if (k0 + u < kend) {
-                        const size_t f = (size_t)jj[u] * a.ld + s;
+                        const size_t f = block_at<T>(a.ld, a.n, jj[u], s);
                         xv[u] = a.Xt[f];
                         if constexpr (!KKT) dv[u] = a.DX[f];
                     }
@@ -869,7 +906,7 @@ __global__ __launch_bounds__(256) void k_eval_narrow(EvalArgs<T> a) {
 #pragma unroll
                     for (int u = 0; u < NCH; ++u) {
                         if (k0 + u < ke) {
-                            const size_t f = (size_t)jj[u] * a.ld + s;
+                            const size_t f = block_at<T>(a.ld, a.m, jj[u], s);
                             yv[u] = a.Yt[f];
                             if constexpr (!KKT) {
                                 dv[u] = a.DY[f];
@@ -911,7 +948,7 @@ __global__ __launch_bounds__(256) void k_eval_narrow(EvalArgs<T> a) {
 #pragma unroll
                     for (int u = 0; u < NCH; ++u) {
                         if (k0 + u < ke) {
-                            const size_t f = (size_t)jj[u] * a.ld + s;
+                            const size_t f = block_at<T>(a.ld, a.n, jj[u], s);
                             xv[u] = a.Xt[f];
                             if constexpr (!KKT) dv[u] = a.DX[f];
                         }
@@ -1303,7 +1340,7 @@ __global__ __launch_bounds__(1024) void k_control(ControlArgs a) {
 // A workgroup owns TR consecutive rows (x rows first, then y rows) and takes
 // the plan entries 64 at a time; its threads take the (entry, row) pairs of
 // the tile, entries fastest, so a few retiring LPs still occupy every thread
-// and issue the tile's loads at once.  Reads and writes of the row-major
+// and issue the tile's loads at once.  Reads and writes of the
 // blocks run along slots, and the entries of one row tile share its lines, so
 // one workgroup walking all of them reads each line once; the results pass
 // through LDS so that each LP's TR values of a result block are written as one
@@ -1333,7 +1370,7 @@ __global__ __launch_bounds__(256) void k_compact(int32_t n, int32_t m, int32_t l
     // (slot, row) pairs of the restarted slots that stay in place, slots fastest
     for (int32_t idx = threadIdx.x; idx < nf * rcount; idx += 256) {
         const int32_t q = idx % nf, rr = idx / nf;
-        const size_t e = (size_t)(r0 + rr) * ld + fresh[q];
+        const size_t e = block_at<T>(ld, rows, r0 + rr, fresh[q]);
         if (xside) {
             B.b[1][e] = B.b[2][e];
         } else {
@@ -1351,8 +1388,7 @@ __global__ __launch_bounds__(256) void k_compact(int32_t n, int32_t m, int32_t l
         for (int32_t idx = threadIdx.x; idx < nq * rcount; idx += 256) {
             const int32_t qq = idx % nq, rr = idx / nq;
             const RetireEntry& re = ent[qq];
-            const size_t base = (size_t)(r0 + rr) * ld;
-            const size_t e = base + re.slot;
+            const size_t e = block_at<T>(ld, rows, r0 + rr, re.slot);
             if (xside) {
                 const T xb = B.b[0][e], x0 = B.b[1][e], xt = B.b[2][e];
                 res_t[qq][rr] = xt;
@@ -1366,7 +1402,7 @@ __global__ __launch_bounds__(256) void k_compact(int32_t n, int32_t m, int32_t l
                 // when it restarted at this evaluation); its z~ and
                 // displacement are written again by the iteration before any
                 // later evaluation reads them
-                const size_t f = base + re.src;
+                const size_t f = block_at<T>(ld, rows, r0 + rr, re.src);
                 if (xside) {
                     const T v0 = B.b[0][f];
                     const T v1 = re.src_fresh ? B.b[2][f] : B.b[1][f];
@@ -1599,14 +1635,14 @@ __global__ __launch_bounds__(TAIL_THREADS) void k_tail(TailArgs<T> a) {
     v.yt = v.y0 + m;
     v.dy = v.yt + m;
     for (int32_t i = tid; i < n; i += TAIL_THREADS) {
-        const size_t e = (size_t)i * ld + s;
+        const size_t e = block_at<T>(ld, n, i, s);
         v.xb[i] = a.blk[0][e];
         v.x0[i] = a.blk[1][e];
         v.xt[i] = a.blk[2][e];
         v.dx[i] = a.blk[3][e];
     }
     for (int32_t i = tid; i < m; i += TAIL_THREADS) {
-        const size_t e = (size_t)i * ld + s;
+        const size_t e = block_at<T>(ld, m, i, s);
         v.y[i] = a.blk[4][e];
         v.y0[i] = a.blk[5][e];
         v.yt[i] = a.blk[6][e];
@@ -2137,8 +2173,9 @@ __device__ __forceinline__ void persist_column(const PersistArgs<T>& a, PersistP
     T z = T(0), z0 = T(0), lo = T(0), hi = T(0), p = T(0), h = T(0), wa = T(0);
     double dc = 0.0, dlo = 0.0, dhi = 0.0;
     if (own) {
-        z = a.blk[isx ? 0 : 4][(size_t)row * ld + s];
-        z0 = a.blk[isx ? 1 : 5][(size_t)row * ld + s];
+        const size_t e = block_at<T>(ld, isx ? n : m, row, s);
+        z = a.blk[isx ? 0 : 4][e];
+        z0 = a.blk[isx ? 1 : 5][e];
         dlo = (isx ? a.xl : a.rl)[row];
         dhi = (isx ? a.xu : a.ru)[row];
         if (isx) {
@@ -2357,7 +2394,7 @@ __device__ __forceinline__ void persist_column(const PersistArgs<T>& a, PersistP
 
     // ---- copy out: the iterate; a stopped LP's last point too ----------------------------
     if (own) {
-        const size_t o = (size_t)row * ld + s;
+        const size_t o = block_at<T>(ld, isx ? n : m, row, s);
         const bool stopped = (S.cs[0].flags & SLOT_ACTIVE) == 0;
         // the reflection, or y^k (after a restart the anchor stands for both)
         a.blk[isx ? 0 : 4][o] = z;
@@ -2476,7 +2513,7 @@ __device__ __forceinline__ void persist_columns(const PersistArgs<T>& a, Persist
     persist_load_cols(a, S, c0, W, ncols, P.member == 0);
     for (int32_t i = tid; i < nxi; i += bs) {
         const int32_t r = x0r + (i >> lw);
-        const size_t e = (size_t)r * ld + s;
+        const size_t e = block_at<T>(ld, n, r, s);
         const T v = have ? a.blk[0][e] : T(0);
         XK[i] = v;
         X0[i] = have ? a.blk[1][e] : T(0);
@@ -2484,7 +2521,7 @@ __device__ __forceinline__ void persist_columns(const PersistArgs<T>& a, Persist
     }
     for (int32_t i = tid; i < nyi; i += bs) {
         const int32_t r = y0r + (i >> lw);
-        const size_t e = (size_t)r * ld + s;
+        const size_t e = block_at<T>(ld, m, r, s);
         const T v = have ? a.blk[4][e] : T(0);
         YK[i] = v;
         Y0[i] = have ? a.blk[5][e] : T(0);
@@ -2744,13 +2781,13 @@ __device__ __forceinline__ void persist_columns(const PersistArgs<T>& a, Persist
     if (have) {
         const bool stopped = (S.cs[col].flags & SLOT_ACTIVE) == 0;
         for (int32_t i = tid; i < nxi; i += bs) {
-            const size_t o = (size_t)(x0r + (i >> lw)) * ld + s, e = (size_t)x0r * W + i;
+            const size_t o = block_at<T>(ld, n, x0r + (i >> lw), s), e = (size_t)x0r * W + i;
             a.blk[0][o] = gXb[e];
             a.blk[1][o] = X0[i];
             if (stopped) a.blk[2][o] = gXt[e];
         }
         for (int32_t i = tid; i < nyi; i += bs) {
-            const size_t o = (size_t)(y0r + (i >> lw)) * ld + s, e = (size_t)y0r * W + i;
+            const size_t o = block_at<T>(ld, m, y0r + (i >> lw), s), e = (size_t)y0r * W + i;
             a.blk[4][o] = YK[i];
             a.blk[5][o] = Y0[i];
             if (stopped) a.blk[6][o] = gYt[e];
@@ -2879,7 +2916,8 @@ __global__ void k_init_blocks(int32_t n, int32_t m, int32_t ld, int32_t ncols, S
     const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     const int64_t nx = (int64_t)n * ld, ny = (int64_t)m * ld;
     if (idx < nx) {
-        const int32_t i = (int32_t)(idx / ld), s = (int32_t)(idx % ld);
+        int32_t i, s;
+        block_element<T>(ld, n, idx, i, s);
         T x = T(0);
         if (s < ncols) {
             const VarData d = var_data(sl.key[s].varkind, sl.dval, s, i, 0.0, xl[i], xu[i]);
@@ -2892,7 +2930,8 @@ __global__ void k_init_blocks(int32_t n, int32_t m, int32_t ld, int32_t ncols, S
         X0[idx] = x;
     } else if (idx < nx + ny) {
         const int64_t e = idx - nx;
-        const int32_t i = (int32_t)(e / ld), s = (int32_t)(e % ld);
+        int32_t i, s;
+        block_element<T>(ld, m, e, i, s);
         T y = T(0);
         if (s < ncols) {
             if (mode == PDLPB_WARM_SHARED) y = T(yw[i]);
@@ -2941,7 +2980,7 @@ __global__ void k_init_columns(int32_t n, int32_t m, int32_t ld, int32_t c0, int
         const int32_t i = (int32_t)(idx / cnt), s = c0 + (int32_t)(idx % cnt);
         const VarData d = var_data(sl.key[s].varkind, sl.dval, s, i, 0.0, xl[i], xu[i]);
         const T x = T(clampd(mode == PDLPB_WARM_BASE ? xw[i] : 0.0, d.lo, d.hi));
-        const size_t e = (size_t)i * ld + s;
+        const size_t e = block_at<T>(ld, n, i, s);
         B.b[0][e] = x;
         B.b[1][e] = x;
         B.b[2][e] = x;
@@ -2952,7 +2991,7 @@ __global__ void k_init_columns(int32_t n, int32_t m, int32_t ld, int32_t c0, int
         // objective changes start from the base primal point with y = 0
         const bool objective = (sl.key[s].varkind >> 28) == PDLPB_OBJ_UNIT;
         const T y = (mode == PDLPB_WARM_BASE && !objective) ? T(yw[i]) : T(0);
-        const size_t e = (size_t)i * ld + s;
+        const size_t e = block_at<T>(ld, m, i, s);
         B.b[4][e] = y;
         B.b[5][e] = y;
         B.b[6][e] = y;
@@ -3457,12 +3496,12 @@ __global__ __launch_bounds__(256) void k_sp_dense(SharedArgs<T> a) {
         for (int32_t e = threadIdx.x; e < nc; e += blockDim.x) {
             const int32_t K = a.map[a.nslots + e];
             if (row < a.n) {
-                const size_t o = (size_t)row * a.ld + e;
+                const size_t o = block_at<T>(a.ld, a.n, row, e);
                 a.blk[0][o] = a.xbar[(size_t)K * a.n + row];
                 a.blk[1][o] = a.x0[row];
             } else {
                 const int32_t r = row - a.n;
-                const size_t o = (size_t)r * a.ld + e;
+                const size_t o = block_at<T>(a.ld, a.m, r, e);
                 a.blk[4][o] = a.yn[(size_t)K * a.m + r];
                 a.blk[5][o] = a.y0[r];
             }
@@ -3532,11 +3571,12 @@ __global__ __launch_bounds__(256) void k_sp_patch(SharedArgs<T> a) {
     const int32_t nv = min(a.t_rp[v + 1] - kb, SP_MAX_COL);
     if (live) {
         if (lane == 0) {
-            a.blk[0][(size_t)v * a.ld + e] = side[2];
-            a.blk[1][(size_t)v * a.ld + e] = side[0];
+            const size_t o = block_at<T>(a.ld, a.n, v, e);
+            a.blk[0][o] = side[2];
+            a.blk[1][o] = side[0];
         }
         for (int32_t q = lane; q < nv; q += 64)
-            a.blk[4][(size_t)a.t_ci[kb + q] * a.ld + e] = side[4 + 3 * q + 1];
+            a.blk[4][block_at<T>(a.ld, a.m, a.t_ci[kb + q], e)] = side[4 + 3 * q + 1];
     } else {
         const size_t lp = (size_t)re.lp;
         if (lane == 0) {
@@ -3579,13 +3619,17 @@ hipError_t launch_step_gve(const StepArgs<T>& a, hipStream_t s) {
         const uint32_t cap = (uint32_t)max(1, a.max_blocks / (int32_t)gy);
         gx = min(gx, cap);
     }
-    const dim3 grid(gx, gy);
+    if (gx == 0 || gy == 0) return hipSuccess;
+    StepArgs<T> b = a;
+    // one XCD to a tile while the gathered part of a tile stays in its L2
+    if (gy > 1 && (int64_t)a.grows * (G * VEC) * (int64_t)sizeof(T) <= TILE_XCD_BYTES && (int64_t)gx * gy < 0x70000000)
+        b.gx = (int32_t)gx;
+    const dim3 grid = b.gx > 0 ? dim3((gx * gy + 7) / 8 * 8) : dim3(gx, gy);
     const dim3 block(64 * a.wpb);
-    if (grid.x == 0 || grid.y == 0) return hipSuccess;
     if (PRIMAL)
-        hipLaunchKernelGGL((k_primal<T, G, VEC, EW>), grid, block, 0, s, a);
+        hipLaunchKernelGGL((k_primal<T, G, VEC, EW>), grid, block, 0, s, b);
     else
-        hipLaunchKernelGGL((k_dual<T, G, VEC, EW>), grid, block, 0, s, a);
+        hipLaunchKernelGGL((k_dual<T, G, VEC, EW>), grid, block, 0, s, b);
     return hipGetLastError();
 }
 

@@ -127,7 +127,7 @@ struct pdlpb_ctx {
     // tile shapes chosen by timing, per (live column shape, ld)
     std::vector<std::pair<int64_t, std::pair<Tile, Tile>>> tuned;
     size_t cap_block_bytes = 0;     // bytes of each of the 8 dense blocks per row (ld * element size)
-    void* blk[8] = {};              // Xbar, X0, Xt, DX, Y, Y0, Yt, DY (row-major, stride ld)
+    void* blk[8] = {};              // Xbar, X0, Xt, DX, Y, Y0, Yt, DY (column tiles, block_at)
     // Narrow storage: once at most NARROW_LD columns of a wide batch still run,
     // run_solve copies them into blocks of stride NARROW_LD and works there
     // until it returns (blk and ld point at them meanwhile).
@@ -424,11 +424,10 @@ int compute_opnorm(pdlpb_ctx* x, double* out) {
     return PDLPB_OK;
 }
 
-// default tile for `ncols` live columns: a row group covers W = lanes * vec
-// consecutive slots with W = 64 (fewer when the batch is narrower), 2 FP64 or
-// 4 FP32 slots per lane once the batch is that wide -- the fastest shape of
-// the 200k x 500k sweeps at B = 64 ... 512 in both precisions; vec never
-// exceeds the width ld was padded for
+// default tile for `ncols` live columns: a row group covers the W = lanes * vec
+// slots of one storage tile (128 bytes of a row; fewer when the batch is
+// narrower), 16 bytes per lane once the batch is that wide; vec never exceeds
+// the width ld was padded for
 Tile heuristic_tile(const pdlpb_ctx* x, int32_t ncols) {
     if (x->narrow && x->ld <= TINY_LD) {
         // blocks of stride 4, 2 or 1: one lane per row covers every column
@@ -438,8 +437,9 @@ Tile heuristic_tile(const pdlpb_ctx* x, int32_t ncols) {
         t.blocks = x->opt.max_blocks > 0 ? x->opt.max_blocks : DEFAULT_MAX_BLOCKS;
         return t;
     }
-    const int32_t w = std::min<int32_t>(64, next_pow2(ncols > 0 ? ncols : 1));
-    int vec = w >= 64 ? (x->fp32 ? 4 : 2) : 1;
+    const int32_t tile = x->fp32 ? block_tile<float>() : block_tile<double>();
+    const int32_t w = std::min<int32_t>(tile, next_pow2(ncols > 0 ? ncols : 1));
+    int vec = w >= tile ? (x->fp32 ? 4 : 2) : 1;
     if (x->opt.tile_vec > 0) vec = x->opt.tile_vec;
     if (vec > x->vec_ld) vec = x->vec_ld;
     // at least 8 lanes per row group: a narrow batch (few live LPs) still spreads
@@ -467,11 +467,12 @@ double launch_bytes(const pdlpb_ctx* x, int32_t ncols) {
     return (double)x->nnz * (s + 4) + s * ncols * ((double)x->m + 3.0 * x->n);
 }
 
-// tile shapes worth timing: widths 16..256 (not beyond the next power of two
+// tile shapes worth timing: widths 16..64, one to four storage tiles (wider rows
+// of a tile lie in more of them and none was faster; not beyond the next power of two
 // above the live columns), every vector width the padding allows
 std::vector<Tile> tile_candidates(const pdlpb_ctx* x, int32_t ncols) {
     std::vector<Tile> out;
-    const int32_t wmax = std::min<int32_t>(256, next_pow2(ncols));
+    const int32_t wmax = std::min<int32_t>(64, next_pow2(ncols));
     for (int vec = 1; vec <= x->vec_ld; vec *= 2)
         for (int32_t w = 16; w <= wmax; w *= 2) {
             const int lanes = w / vec;
@@ -507,6 +508,7 @@ StepArgs<T> step_args(pdlpb_ctx* x, bool primal, int32_t it, int32_t eval, int32
     if constexpr (sizeof(T) == 8) a.ev = reinterpret_cast<const T*>(primal ? x->t_ev64 : x->a_ev64);
     else a.ev = reinterpret_cast<const T*>(primal ? x->t_ev32 : x->a_ev32);
     a.rows = primal ? x->n : x->m;
+    a.grows = primal ? x->m : x->n;
     a.ld = x->ld;
     a.ncols = x->live;
     a.wpb = x->wpb;
@@ -1035,11 +1037,11 @@ int run_tail(pdlpb_ctx* x, int32_t n_cols, std::vector<std::pair<int, int>>* rec
     return PDLPB_OK;
 }
 
-// Narrow storage.  In the batch's blocks the live columns of a row sit at
-// stride ld, so once few LPs run every gathered segment and every streamed row
-// lies in its own ld-wide row: at 200k x 500k, 8 running LPs cost 67 / 55 us
-// per primal / dual launch in blocks of stride 512 and 48 / 46 us in blocks of
-// stride 8.  Once at most NARROW_LD columns of a batch at least four times as
+// Narrow storage.  In the batch's blocks the live columns of a row lie in a
+// whole 128-byte line, so once few LPs run every gathered segment and every
+// streamed row costs that line for a part of it: at 200k x 500k, 8 running LPs
+// cost 67 / 55 us per primal / dual launch at a line per row and 48 / 46 us in
+// blocks of stride 8.  Once at most NARROW_LD columns of a batch at least four times as
 // wide still run, and its blocks exceed the last-level cache, run_solve copies
 // those columns into blocks of stride NARROW_LD and works there until it
 // returns; once at most 4, 2 or 1 run, into blocks of that stride, where one
@@ -1061,19 +1063,20 @@ int32_t narrow_target(const pdlpb_ctx* x, int32_t n_cols) {
     int32_t want = NARROW_LD;
     if (!fixed) want = n_cols <= 1 ? 1 : n_cols <= 2 ? 2 : n_cols <= TINY_LD ? TINY_LD : NARROW_LD;
     if (want == NARROW_LD && NARROW_LD % x->vec_ld != 0) return 0;
-    return want < x->ld ? want : 0;
+    return want < (x->fp32 ? block_stride<float>(x->ld, 0) : block_stride<double>(x->ld, 0)) ? want : 0;
 }
 
 int enter_narrow(pdlpb_ctx* x, int32_t ld) {
     const size_t esz = x->fp32 ? sizeof(float) : sizeof(double);
+    // the live columns lie in the first tile
+    const size_t stride = (size_t)(x->fp32 ? block_stride<float>(x->ld, 0) : block_stride<double>(x->ld, 0));
     void** dst = ld == NARROW_LD ? x->nblk : x->tblk[ld == TINY_LD ? 0 : ld == 2 ? 1 : 2];
     for (int q = 0; q < 8; ++q) {
         const int32_t rows = q < 4 ? x->n : x->m;
         if (!dst[q]) HIP_TRY(x, x->alloc(&dst[q], (size_t)rows * ld * esz));
         if (rows > 0)
-            HIP_TRY(x, hipMemcpy2DAsync(dst[q], (size_t)ld * esz, x->blk[q], (size_t)x->ld * esz,
-                                        (size_t)ld * esz, (size_t)rows, hipMemcpyDeviceToDevice,
-                                        x->stream));
+            HIP_TRY(x, hipMemcpy2DAsync(dst[q], (size_t)ld * esz, x->blk[q], stride * esz, (size_t)ld * esz,
+                                        (size_t)rows, hipMemcpyDeviceToDevice, x->stream));
     }
     if (!x->narrow) {
         for (int q = 0; q < 8; ++q) x->wblk[q] = x->blk[q];
@@ -1568,7 +1571,7 @@ int32_t ld_for(const pdlpb_ctx* x, int32_t cols) {
 }
 
 // Device storage for `cols` LP columns and `lps` LP result rows (grows, reused
-// for smaller requests).  Sets vec_ld and returns the row stride ld.
+// for smaller requests).  Sets vec_ld and returns the block width ld.
 int ensure_storage(pdlpb_ctx* x, int32_t cols, int32_t lps, int32_t* ld_out) {
     const int32_t n = x->n, m = x->m;
     // pad for 4-wide vectors when the batch is large enough to be tuned
@@ -1651,7 +1654,7 @@ int ensure_storage(pdlpb_ctx* x, int32_t cols, int32_t lps, int32_t* ld_out) {
 // Device bytes of an allocation of `bytes` (the allocator rounds zero up).
 int64_t alloc_bytes(size_t bytes) { return (int64_t)(bytes == 0 ? 256 : bytes); }
 
-// Device bytes of the batch storage for `cols` columns (stride ld) and `rows`
+// Device bytes of the batch storage for `cols` columns (padded to ld) and `rows`
 // result rows: the eight iterate blocks, the per-slot arrays, the compaction
 // plan and admission staging, the evaluation partial sums, the four result
 // blocks and the per-LP control rows.  Mirrors resize_storage.
@@ -1706,10 +1709,16 @@ int resize_storage(pdlpb_ctx* x, int32_t cols, int32_t rows, int32_t keep_cols) 
         for (int q = 0; q < 8; ++q) {
             const int32_t r = q < 4 ? n : m;
             HIP_TRY(x, x->alloc(&nb[q], (size_t)r * ld * esz));
-            if (keep_cols > 0 && r > 0 && x->blk[q])
-                HIP_TRY(x, hipMemcpy2DAsync(nb[q], (size_t)ld * esz, x->blk[q], (size_t)old_ld * esz,
-                                            (size_t)keep_cols * esz, (size_t)r,
+            if (r <= 0 || !x->blk[q]) continue;
+            // tile by tile (a tile starts at the same offset whatever the column count)
+            const int32_t tile = x->fp32 ? block_tile<float>() : block_tile<double>();
+            for (int32_t c = 0; c < keep_cols; c += tile) {
+                const size_t off = (size_t)c * r * esz;
+                const size_t to = (size_t)std::min(tile, ld - c) * esz, from = (size_t)std::min(tile, old_ld - c) * esz;
+                HIP_TRY(x, hipMemcpy2DAsync(static_cast<char*>(nb[q]) + off, to, static_cast<char*>(x->blk[q]) + off,
+                                            from, (size_t)std::min(tile, keep_cols - c) * esz, (size_t)r,
                                             hipMemcpyDeviceToDevice, x->stream));
+            }
         }
         auto regrow = [&](auto*& p, size_t elem, bool copy) -> int {
             using E = std::remove_pointer_t<std::remove_reference_t<decltype(p)>>;

@@ -107,6 +107,40 @@ constexpr int NTERM = 10;
 // (dy_B = Pi_B[l,u](dy), dr = Pi_B[xl,xu](r~ - r^k), the displacement vectors of the
 // infeasibility tests)
 
+// Layout of a dense block of `rows` rows and ld columns: tiles of block_tile
+// columns (128 bytes per row), a tile's rows one after another; the last tile
+// holds the columns that are left.  A block of at most one tile is row-major.
+template <typename T>
+constexpr int32_t block_tile() { return 128 / (int32_t)sizeof(T); }
+// gathered bytes of a column tile up to which each XCD takes its own tiles
+constexpr int64_t TILE_XCD_BYTES = 16 << 20;
+// row stride of the tile that holds column s
+template <typename T>
+__host__ __device__ inline int32_t block_stride(int32_t ld, int32_t s) {
+    const int32_t left = ld - (s & ~(block_tile<T>() - 1));
+    return left < block_tile<T>() ? left : block_tile<T>();
+}
+// index of (row 0, column s)
+template <typename T>
+__host__ __device__ inline size_t block_offset(int32_t rows, int32_t s) {
+    constexpr int32_t W = block_tile<T>();
+    return (size_t)(s & ~(W - 1)) * (size_t)rows + (size_t)(s & (W - 1));
+}
+template <typename T>
+__host__ __device__ inline size_t block_at(int32_t ld, int32_t rows, int32_t i, int32_t s) {
+    return block_offset<T>(rows, s) + (size_t)i * block_stride<T>(ld, s);
+}
+// (row, column) of index e
+template <typename T>
+__host__ __device__ inline void block_element(int32_t ld, int32_t rows, int64_t e, int32_t& i, int32_t& s) {
+    constexpr int32_t W = block_tile<T>();
+    const int32_t t = (int32_t)(e / ((int64_t)W * rows));
+    const int64_t q = e - (int64_t)t * W * rows;
+    const int32_t w = block_stride<T>(ld, t * W);
+    i = (int32_t)(q / w);
+    s = t * W + (int32_t)(q % w);
+}
+
 template <typename T>
 struct StepArgs {
     const int32_t* rp;   // CSR row pointers of the matrix whose rows this kernel walks
@@ -116,7 +150,8 @@ struct StepArgs {
     const T*       ev;   // ELL head values (0 pads)
     int32_t ew;          // ELL head width: 16, or 0 when the rows are walked in CSR alone
     int32_t rows;        // rows walked (n for the primal step, m for the dual step)
-    int32_t ld;          // row stride of every dense block (>= ncols)
+    int32_t grows;       // rows of the gathered block (m, n)
+    int32_t ld;          // columns of every dense block (>= ncols)
     int32_t ncols;       // columns covered by the grid (the live count g->n_cols never exceeds it)
     int32_t wpb;         // waves per block
     const T* G;          // block gathered by the product (Y for primal, Xbar for dual)
@@ -133,6 +168,7 @@ struct StepArgs {
     int32_t eval;        // 2: every running LP writes z~ and its displacement; 1: only the LPs
                          //    that the following evaluation of fresh cycles reads; 0: none
     int32_t admit;       // 1: only LPs flagged SLOT_NEW iterate (their first iteration)
+    int32_t gx;          // row blocks per column tile when tiles are dealt to XCDs (set at launch), 0: grid y is the tile
     int32_t max_blocks;  // > 0: cap on the workgroups of the launch (waves then loop over rows)
 };
 
@@ -197,7 +233,7 @@ struct TailArgs {
     const int32_t* t_rp; const int32_t* t_ci; const T* t_v;    // A' (n x m)
     const int32_t* a_e8ci; const T* a_e8v;   // the first 8 entries of every row of A (-1 pads)
     const int32_t* t_e8ci; const T* t_e8v;   // ... and of A'
-    T* blk[8];                 // Xbar, X0, Xt, DX, Y, Y0, Yt, DY (row-major, stride ld)
+    T* blk[8];                 // Xbar, X0, Xt, DX, Y, Y0, Yt, DY (column tiles, block_at)
     T* res[4];                 // Rx, Rxi (B x n), Ry, Ryi (B x m): LP-major results
     const double *c, *xl, *xu, *rl, *ru;
     Slots sl;
@@ -264,7 +300,7 @@ struct PersistArgs {
     const int32_t* t_rp; const int32_t* t_ci; const T* t_v;    // A' (n x m)
     const double *c, *xl, *xu, *rl, *ru;
     const int8_t* rcode;       // per row of A: 1 if its lower bound is -inf, | 2 if its upper is +inf
-    T* blk[8];                 // Xbar, X0, Xt, DX, Y, Y0, Yt, DY (row-major, stride ld)
+    T* blk[8];                 // Xbar, X0, Xt, DX, Y, Y0, Yt, DY (column tiles, block_at)
     Slots sl;
     SlotCtl* ctl;
     int32_t* rlog;
@@ -363,7 +399,7 @@ struct SharedArgs {
     const MoveEntry* moves;
     int32_t* map;              // [2][nslots]: slot whose LP a live column holds after the
                                // compaction, and that LP's base LP
-    T* blk[8];                 // Xbar, X0, Xt, DX, Y, Y0, Yt, DY (row-major, stride ld)
+    T* blk[8];                 // Xbar, X0, Xt, DX, Y, Y0, Yt, DY (column tiles, block_at)
     T* res[4];                 // Rx, Rxi (B x n), Ry, Ryi (B x m): LP-major results
 };
 
@@ -424,7 +460,7 @@ hipError_t launch_init_blocks(int32_t n, int32_t m, int32_t ld, int32_t ncols, S
 // Halpern iterate are copied into the LP-major result blocks, and running LPs
 // beyond the new column count move into the freed slots.  ncols bounds the
 // plan's entries (the live column count of the launches).
-// blk: Xbar, X0, Xt, DX, Y, Y0, Yt, DY (row-major, stride ld).
+// blk: Xbar, X0, Xt, DX, Y, Y0, Yt, DY (column tiles, block_at).
 // res: Rx (B x n), Rxi (B x n), Ry (B x m), Ryi (B x m), LP-major.
 template <typename T>
 hipError_t launch_compact(int32_t n, int32_t m, int32_t ld, int32_t ncols, T* const* blk,

@@ -1,0 +1,59 @@
+"""Batches whose blocks end inside, at and past a column tile (128 bytes per row):
+every LP's results are, bit for bit, those it has in a batch of at most four LPs,
+whose blocks are one narrow tile."""
+from __future__ import annotations
+
+import numpy as np
+import pytest
+
+from gpu_common import make_ctx
+from workloads import choose_vars, make_cfg1, make_cfg2, make_facility, obbt_deltas
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def P():
+    import paper_2601_21990_amd.pdlpb as P
+    return P
+
+
+def _solve(ctx, D, K):
+    ctx.set_batch(D)
+    ctx.solve(tol=1e-9, max_iters=K)
+    out = ctx.get_batch()
+    out["dobj"] = ctx.dual_objective()
+    return out
+
+
+def _pieces(inst, D, K, **kw):
+    """The batch as a whole and in pieces of four, on the step launches."""
+    with make_ctx(inst, **kw) as ctx:
+        ctx.set_kernel_timing(True)
+        whole = _solve(ctx, D, K)
+        for i in range(0, len(D), 4):
+            part = _solve(ctx, D[i:i + 4], K)
+            for key in whole:
+                assert np.array_equal(whole[key][i:i + 4], part[key], equal_nan=True), (key, i)
+
+
+def _deltas(n, B):
+    return obbt_deltas(choose_vars(n, min(n, (B + 1) // 2), seed=B))[:B]
+
+
+@pytest.mark.parametrize("prec", ["fp64", "fp32"])
+@pytest.mark.parametrize("B", [15, 16, 17, 31, 32, 33, 48, 65, 151])
+def test_widths(P, B, prec):
+    inst = make_cfg2(m=300, n=700)
+    _pieces(inst, _deltas(inst.n, B), 130, precision=P.MIXED32 if prec == "fp32" else P.FP64, eval_every=32)
+
+
+@pytest.mark.parametrize("prec", ["fp64", "fp32"])
+@pytest.mark.parametrize("make, B", [
+    (make_cfg1, 20),                                    # empty rows and columns
+    (lambda: make_facility(F=6, C=24, k=4), 37),        # rows of very different lengths
+], ids=["empty", "long"])
+def test_shapes(P, make, B, prec):
+    inst = make()
+    D = _deltas(inst.n, B)
+    _pieces(inst, D, 130, precision=P.MIXED32 if prec == "fp32" else P.FP64, eval_every=32)
