@@ -291,10 +291,15 @@ __device__ __forceinline__ void row_product(const StepArgs<T>& a, const RowOps<T
 // Primal (eq:main-iterate, first line; eq:mainiter): x^k rebuilt from the
 // stored reflection z and the anchor x0, x~ = Pi_[lo,hi](x^k - tau (c + g)),
 // reflection 2 x~ - x^k.
+// (wa = k/(k+1), wb = k+1)
+template <typename T>
+__device__ __forceinline__ T primal_iterate(int32_t k, T wa, T wb, T z, T x0) {
+#pragma clang fp contract(off)
+    return (k == 0) ? x0 : wa * z + x0 / wb;
+}
 template <typename T>
 __device__ __forceinline__ T primal_iterate(int32_t k, T z, T x0) {
-#pragma clang fp contract(off)
-    return (k == 0) ? x0 : T(double(k) / double(k + 1)) * z + x0 / T(k + 1);
+    return primal_iterate<T>(k, T(double(k) / double(k + 1)), T(k + 1), z, x0);
 }
 template <typename T>
 __device__ __forceinline__ void primal_update(T xk, T tau, T c, T lo, T hi, T g, T& xt, T& xbar) {
@@ -545,6 +550,244 @@ __global__ __launch_bounds__(256) void k_dual(StepArgs<T> a) {
         RowOps<T, VEC, EW> o;
         load_row<T, VEC, EW, false>(a, row, s0, lc, o);
         step(row, o);
+    }
+}
+
+// ---------------------------------------------------------------------------
+// The same two steps on rows of moderate length: a wave takes ROWS rows of one
+// column tile.  It loads their entries (contiguous in the CSR arrays) with one
+// coalesced load per 64 and hands them around through its own part of LDS, so a
+// gather costs one vector instruction and one LDS read and the chain of
+// dependent loads is row pointers, entries, gathers; row bounds and entries are
+// read once per wave instead of once per lane group.  G lanes of 16 bytes cover
+// a 128-byte line of the tile, 64 / G rows are in flight at a time.  Offsets are
+// 32 bits (buffer loads): a slot past the row's end reads as zero without
+// touching memory and adds -0 * 0, which changes no sum.  No wave waits for
+// another.
+//
+// Bound by the gathered lines (one L2 line per CU and about 3.7 clocks) together
+// with the streams of the updated block; a kernel that only gathers and streams
+// the same bytes, alternating both steps, takes 79 / 77 us (FP64) and 36 / 40 us
+// (FP32) at 20k x 50k, 8 nonzeros per column, 256 LPs.  This one takes 97 / 93 and
+// 41 / 46 us there; k_primal / k_dual, whose every lane loads indices and values
+// and whose per-entry branches keep few gathers in flight, 141 / 120 and
+// 75 / 57 us.  16 rows per wave spread the slot state over two passes; 8 where
+// that leaves fewer than ROWS_WAVES waves (1000 x 2500, 64 LPs, FP64: 5.0 / 5.2 us
+// with 8, 5.6 / 6.7 with 16, 5.6 / 6.1 with k_primal / k_dual).
+// ---------------------------------------------------------------------------
+constexpr int ROWS_CH = 8;                    // entries of a row gathered together
+constexpr uint32_t ROWS_NONE = 0x80000000u;   // a buffer offset past every tile
+constexpr int64_t ROWS_WAVES = 2048;          // waves that 16 rows each have to give
+
+template <typename T, int VEC>
+__device__ __forceinline__ void buffer_load(__amdgpu_buffer_rsrc_t r, uint32_t off, T* v) {
+    constexpr int B = VEC * (int)sizeof(T);
+    if constexpr (B == 4) {
+        const auto q = __builtin_amdgcn_raw_buffer_load_b32(r, off, 0, 0);
+        __builtin_memcpy(v, &q, B);
+    } else if constexpr (B == 8) {
+        const auto q = __builtin_amdgcn_raw_buffer_load_b64(r, off, 0, 0);
+        __builtin_memcpy(v, &q, B);
+    } else {
+        static_assert(B == 16, "at most 16 bytes per lane");
+        const auto q = __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, 0);
+        __builtin_memcpy(v, &q, B);
+    }
+}
+template <typename T, int VEC>
+__device__ __forceinline__ void buffer_store(__amdgpu_buffer_rsrc_t r, uint32_t off, const T* v) {
+    constexpr int B = VEC * (int)sizeof(T);
+    if constexpr (B == 4) {
+        uint32_t q;
+        __builtin_memcpy(&q, v, B);
+        __builtin_amdgcn_raw_buffer_store_b32(q, r, off, 0, 0);
+    } else if constexpr (B == 8) {
+        typedef uint32_t u2 __attribute__((ext_vector_type(2)));
+        u2 q;
+        __builtin_memcpy(&q, v, B);
+        __builtin_amdgcn_raw_buffer_store_b64(q, r, off, 0, 0);
+    } else {
+        static_assert(B == 16, "at most 16 bytes per lane");
+        typedef uint32_t u4 __attribute__((ext_vector_type(4)));
+        u4 q;
+        __builtin_memcpy(&q, v, B);
+        __builtin_amdgcn_raw_buffer_store_b128(q, r, off, 0, 0);
+    }
+}
+
+template <typename T, int G, int VEC, int ROWS, bool PRIMAL>
+__global__ __launch_bounds__(256, 4) void k_step_rows(StepArgs<T> a) {
+    constexpr int RPW = 64 / G, E = ROWS / 2, ENT = 64 * E;   // 32 entries per row of the wave
+    __shared__ T val_[4][ENT + ROWS_CH];
+    __shared__ uint32_t off_[4][ENT + ROWS_CH];
+    __shared__ T rd_[4][3 * ROWS];
+    __shared__ int32_t rp_[4][ROWS + 1];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int32_t ncols = min(a.ncols, a.g->n_cols);
+    const TileOf w = tile_of<G * VEC>(a.gx, ncols);
+    const int32_t rb = (w.block * 4 + wave) * ROWS, re = min(a.rows, rb + ROWS);
+    const int32_t c0 = w.tile * (G * VEC);
+    if (w.tile < 0 || c0 >= ncols || rb >= re) return;
+    T* const val = val_[wave];
+    uint32_t* const off = off_[wave];
+    T* const rd = rd_[wave];
+    int32_t* const rp = rp_[wave];
+    const int32_t cl = (lane % G) * VEC, s0 = c0 + cl;
+    const uint32_t ldb = (uint32_t)block_stride<T>(a.ld, c0) * (uint32_t)sizeof(T);
+    const uint32_t lb = (uint32_t)cl * (uint32_t)sizeof(T);
+
+    // the rows' entries, bounds and objective, on their way to LDS
+    const int32_t rpv = a.rp[min(rb + min(lane, ROWS), re)];
+    const int32_t kb = __builtin_amdgcn_readfirstlane(rpv), ke = __builtin_amdgcn_readlane(rpv, ROWS);
+    int32_t ci[E];
+    T av[E], rc = T(0);
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+        if (kb + e * 64 < ke) {
+            const int32_t k = min(kb + e * 64 + lane, ke - 1);
+            ci[e] = a.ci[k];
+            av[e] = a.av[k];
+        }
+    }
+    const int32_t ri = min(rb + min(lane, ROWS - 1), re - 1);
+    if constexpr (PRIMAL) rc = T(a.c[ri]);
+    const T rlo = T(a.lo[ri]), rhi = T(a.hi[ri]);
+
+    // this lane's slots, the same for every row it visits
+    const int32_t t = a.g->t0 + a.it;
+    bool live[VEC], keep[VEC], first[VEC], any = false, all = true, keeps = false;
+    int32_t vk[VEC];
+    T st[VEC], wa[VEC], wb[VEC];
+#pragma unroll
+    for (int v = 0; v < VEC; ++v) {
+        const int32_t s = min(s0 + v, ncols - 1);
+        const SlotKey key = a.sl.key[s];
+        live[v] = s0 + v < ncols && (key.flags & SLOT_ACTIVE) && t <= key.t_end &&
+                  (!a.admit || (key.flags & SLOT_NEW));
+        const int32_t k = t - key.t_anchor;
+        first[v] = k == 0;
+        // z~ and the displacement are stored for the evaluation that reads them
+        keep[v] = t == key.t_end || a.eval == 2 || (a.eval == 1 && k == 0);
+        st[v] = T((PRIMAL ? a.sl.tau : a.sl.sigma)[s]);
+        wa[v] = PRIMAL ? T(double(k) / double(k + 1)) : T(halpern_a(k));
+        wb[v] = PRIMAL ? T(k + 1) : T(k + 2);
+        vk[v] = key.varkind;
+        any = any || live[v];
+        all = all && live[v];
+        keeps = keeps || (live[v] && keep[v]);
+    }
+    if (__ballot(any) == 0) return;
+#pragma unroll
+    for (int e = 0; e < E; ++e)
+        if (kb + e * 64 < ke) {
+            off[e * 64 + lane] = (uint32_t)ci[e] * ldb;
+            val[e * 64 + lane] = av[e];
+        }
+    if (lane <= ROWS) rp[lane] = rpv - kb;
+    if (lane < ROWS) {
+        rd[lane] = rc;
+        rd[ROWS + lane] = rlo;
+        rd[2 * ROWS + lane] = rhi;
+    }
+    // a wave's LDS accesses stay in order
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    if (!any) return;
+    const size_t zb = block_offset<T>(a.rows, c0);
+    auto tile = [&](const T* p, int32_t rows) {
+        return __builtin_amdgcn_make_buffer_rsrc(const_cast<T*>(p), 0, (int32_t)((uint32_t)rows * ldb), 0x00020000);
+    };
+    const __amdgpu_buffer_rsrc_t gr = tile(a.G + block_offset<T>(a.grows, c0), a.grows);
+    const __amdgpu_buffer_rsrc_t zr = tile(a.Z + zb, a.rows), z0r = tile(a.Z0 + zb, a.rows);
+#pragma unroll 1
+    for (int32_t li = lane / G; li < re - rb; li += RPW) {
+        const int32_t row = rb + li;
+        const uint32_t e = (uint32_t)row * ldb + lb;
+        T z[VEC], z0[VEC], acc[VEC];
+        buffer_load<T, VEC>(zr, e, z);
+        buffer_load<T, VEC>(z0r, e, z0);
+#pragma unroll
+        for (int v = 0; v < VEC; ++v) acc[v] = T(0);
+        const int32_t pb = rp[li], pe = rp[li + 1];
+        const bool staged = pe <= ENT;   // else: from memory
+        for (int32_t k0 = pb; k0 < pe; k0 += ROWS_CH) {
+            uint32_t o[ROWS_CH];
+            T x[ROWS_CH], g[ROWS_CH][VEC];
+            if (staged) {
+#pragma unroll
+                for (int u = 0; u < ROWS_CH; ++u) {
+                    o[u] = off[k0 + u];
+                    x[u] = val[k0 + u];
+                }
+            } else {
+#pragma unroll
+                for (int u = 0; u < ROWS_CH; ++u) {
+                    const int32_t k = kb + min(k0 + u, pe - 1);
+                    o[u] = (uint32_t)a.ci[k] * ldb;
+                    x[u] = a.av[k];
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < ROWS_CH; ++u) {
+                o[u] = k0 + u < pe ? o[u] + lb : ROWS_NONE;
+                x[u] = k0 + u < pe ? x[u] : T(-0.0);
+            }
+#pragma unroll
+            for (int u = 0; u < ROWS_CH; ++u) buffer_load<T, VEC>(gr, o[u], g[u]);
+#pragma unroll
+            for (int u = 0; u < ROWS_CH; ++u)
+#pragma unroll
+                for (int v = 0; v < VEC; ++v) acc[v] = fma(x[u], g[u][v], acc[v]);
+        }
+        const T c = PRIMAL ? rd[li] : T(0), lo = rd[ROWS + li], hi = rd[2 * ROWS + li];
+        T out[VEC], zt[VEC], dz[VEC];
+        if constexpr (PRIMAL) {
+            bool hit = false;
+            T xk[VEC];
+            // row v's own bound or objective entry of a slot is rare: first without
+#pragma unroll
+            for (int v = 0; v < VEC; ++v) {
+                const uint32_t kind = (uint32_t)vk[v] >> 28;
+                xk[v] = first[v] ? z0[v] : primal_iterate<T>(1, wa[v], wb[v], z[v], z0[v]);
+                primal_update<T>(xk[v], st[v], kind == PDLPB_OBJ_UNIT ? T(0) : c, lo, hi, acc[v], zt[v], out[v]);
+                hit = hit || (live[v] && row == (vk[v] & VAR_MASK));
+            }
+            if (hit) {
+#pragma unroll
+                for (int v = 0; v < VEC; ++v)
+                    if (live[v] && row == (vk[v] & VAR_MASK)) {
+                        const uint32_t kind = (uint32_t)vk[v] >> 28;
+                        const T own = T(a.sl.dval[s0 + v]);
+                        primal_update<T>(xk[v], st[v], kind == PDLPB_OBJ_UNIT ? own : c,
+                                         kind == PDLPB_SET_LO ? own : lo, kind == PDLPB_SET_HI ? own : hi, acc[v],
+                                         zt[v], out[v]);
+                    }
+            }
+#pragma unroll
+            for (int v = 0; v < VEC; ++v) dz[v] = zt[v] - xk[v];
+        } else {
+#pragma unroll
+            for (int v = 0; v < VEC; ++v) {
+                dual_point<T>(z[v], z0[v], st[v], wa[v], wb[v], lo, hi, acc[v], zt[v], out[v]);
+                dz[v] = zt[v] - z[v];
+            }
+        }
+        if (all) {
+            buffer_store<T, VEC>(zr, e, out);
+        } else {
+#pragma unroll
+            for (int v = 0; v < VEC; ++v)
+                if (live[v]) buffer_store<T, 1>(zr, e + v * (uint32_t)sizeof(T), out + v);
+        }
+        if (keeps) {
+            const size_t q = zb + (size_t)row * (ldb / sizeof(T)) + cl;
+#pragma unroll
+            for (int v = 0; v < VEC; ++v)
+                if (live[v] && keep[v]) {
+                    a.Zt[q + v] = zt[v];
+                    a.DZ[q + v] = dz[v];
+                }
+        }
     }
 }
 
@@ -3608,6 +3851,15 @@ __global__ __launch_bounds__(1024) void k_sp_finish(Slots sl, const MoveEntry* m
     if (threadIdx.x == 0) g->n_cols = g->n_cols_next;
 }
 
+// one XCD to a tile while the gathered part of a tile stays in its L2: sets gx
+template <typename T>
+dim3 step_grid(StepArgs<T>& a, int32_t width, uint32_t gx, uint32_t gy) {
+    const bool own = gy > 1 && (int64_t)a.grows * width * (int64_t)sizeof(T) <= TILE_XCD_BYTES &&
+                     (int64_t)gx * gy < 0x70000000;
+    a.gx = own ? (int32_t)gx : 0;
+    return own ? dim3((gx * gy + 7) / 8 * 8) : dim3(gx, gy);
+}
+
 template <typename T, int G, int VEC, int EW, bool PRIMAL>
 hipError_t launch_step_gve(const StepArgs<T>& a, hipStream_t s) {
     constexpr int RPW = 64 / G;
@@ -3621,10 +3873,7 @@ hipError_t launch_step_gve(const StepArgs<T>& a, hipStream_t s) {
     }
     if (gx == 0 || gy == 0) return hipSuccess;
     StepArgs<T> b = a;
-    // one XCD to a tile while the gathered part of a tile stays in its L2
-    if (gy > 1 && (int64_t)a.grows * (G * VEC) * (int64_t)sizeof(T) <= TILE_XCD_BYTES && (int64_t)gx * gy < 0x70000000)
-        b.gx = (int32_t)gx;
-    const dim3 grid = b.gx > 0 ? dim3((gx * gy + 7) / 8 * 8) : dim3(gx, gy);
+    const dim3 grid = step_grid(b, G * VEC, gx, gy);
     const dim3 block(64 * a.wpb);
     if (PRIMAL)
         hipLaunchKernelGGL((k_primal<T, G, VEC, EW>), grid, block, 0, s, b);
@@ -3656,8 +3905,33 @@ hipError_t launch_step_v(const StepArgs<T>& a, int lanes, hipStream_t s) {
     }
 }
 
+template <typename T, int G, int VEC, bool PRIMAL>
+hipError_t launch_rows_gv(StepArgs<T> a, hipStream_t s) {
+    const int64_t tiles = ((int64_t)a.ncols + G * VEC - 1) / (G * VEC);
+    if (a.rows <= 0 || tiles <= 0) return hipSuccess;
+    const bool few = ((int64_t)a.rows + 15) / 16 * tiles < ROWS_WAVES;
+    const int32_t per = 4 * (few ? 8 : 16);
+    const dim3 grid = step_grid(a, G * VEC, (uint32_t)((a.rows + per - 1) / per), (uint32_t)tiles);
+    if (few) hipLaunchKernelGGL((k_step_rows<T, G, VEC, 8, PRIMAL>), grid, dim3(256), 0, s, a);
+    else hipLaunchKernelGGL((k_step_rows<T, G, VEC, 16, PRIMAL>), grid, dim3(256), 0, s, a);
+    return hipGetLastError();
+}
+
+template <typename T, bool PRIMAL>
+hipError_t launch_rows(const StepArgs<T>& a, int lanes, int vec, hipStream_t s) {
+    constexpr int V = 16 / (int)sizeof(T);
+    if (lanes == 8 && vec == 1) return launch_rows_gv<T, 8, 1, PRIMAL>(a, s);
+    if (lanes == 8 && vec == 2) return launch_rows_gv<T, 8, 2, PRIMAL>(a, s);
+    if (lanes == 8 && vec == V) return launch_rows_gv<T, 8, V, PRIMAL>(a, s);
+    if (lanes == 4 * V && vec == 2) return launch_rows_gv<T, 4 * V, 2, PRIMAL>(a, s);
+    if (lanes == 8 * V && vec == 1) return launch_rows_gv<T, 8 * V, 1, PRIMAL>(a, s);
+    if (lanes == 16 && vec == 1) return launch_rows_gv<T, 16, 1, PRIMAL>(a, s);
+    return hipErrorInvalidValue;
+}
+
 template <typename T, bool PRIMAL>
 hipError_t launch_step(const StepArgs<T>& a, int lanes, int vec, hipStream_t s) {
+    if (a.rows_kernel) return a.ld % vec == 0 ? launch_rows<T, PRIMAL>(a, lanes, vec, s) : hipErrorInvalidValue;
     if (a.wpb < 1 || a.wpb > 4) return hipErrorInvalidValue;
     if (a.ld % vec != 0) return hipErrorInvalidValue;
     switch (vec) {

@@ -71,6 +71,7 @@ struct Tile {
     int lanes = 64;     // lanes per row group
     int vec = 1;        // consecutive LPs per lane
     int blocks = 0;     // workgroup cap of the launch (0: one wave per row group)
+    bool rows = false;  // the row kernel (k_step_rows); else k_primal / k_dual
 };
 
 constexpr int32_t DEFAULT_MAX_BLOCKS = 16384;
@@ -209,7 +210,7 @@ struct pdlpb_ctx {
     // into storage that only ensure_storage replaces (and it drops the cache)
     struct GraphKey {
         int32_t live, ld, wpb, narrow, persist;   // persist: blocks of a persistent launch, 0: one block of step launches
-        int32_t tp_lanes, tp_vec, tp_blocks, td_lanes, td_vec, td_blocks;
+        int32_t tp_lanes, tp_vec, tp_blocks, tp_rows, td_lanes, td_vec, td_blocks, td_rows;
         const void* rx;   // result blocks the compactions write (the caller's or the context's)
         const void* ry;
         bool operator==(const GraphKey& o) const {
@@ -217,6 +218,7 @@ struct pdlpb_ctx {
                    persist == o.persist &&
                    tp_lanes == o.tp_lanes && tp_vec == o.tp_vec && tp_blocks == o.tp_blocks &&
                    td_lanes == o.td_lanes && td_vec == o.td_vec && td_blocks == o.td_blocks &&
+                   tp_rows == o.tp_rows && td_rows == o.td_rows &&
                    rx == o.rx && ry == o.ry;
         }
     };
@@ -323,8 +325,8 @@ struct pdlpb_ctx {
         graphs.clear();
     }
     GraphKey graph_key(int32_t persist) const {
-        return GraphKey{live,      ld,       wpb,    narrow ? 1 : 0, persist, tp.lanes, tp.vec,
-                        tp.blocks, td.lanes, td.vec, td.blocks,      out(0),  out(2)};
+        return GraphKey{live,        ld,       wpb,    narrow ? 1 : 0, persist,         tp.lanes, tp.vec, tp.blocks,
+                        tp.rows ? 1 : 0, td.lanes, td.vec, td.blocks,  td.rows ? 1 : 0, out(0),   out(2)};
     }
 };
 
@@ -424,11 +426,24 @@ int compute_opnorm(pdlpb_ctx* x, double* out) {
     return PDLPB_OK;
 }
 
+// The row kernel holds 32 entries per row in LDS, wave by wave, and walks the rest
+// from memory: it serves rows of up to 24 entries on average.  At 5000 rows and
+// columns, 64 LPs, FP64, the primal / dual step takes 7.2 / 8.0 us at 16 entries
+// (k_primal / k_dual 8.7 / 10.4) and 9.0 / 15.7 at 32 (12.3 / 14.6), where many
+// waves spill.  Its offsets within a tile are 32 bits.  A launch shape or a
+// workgroup cap of the caller keeps the kernels that take any.
+constexpr int64_t ROWS_MEAN = 24;
+bool rows_kernel_serves(const pdlpb_ctx* x, bool primal) {
+    if (x->opt.tile_lanes > 0 || x->opt.tile_vec > 0 || x->opt.max_blocks > 0) return false;
+    const int64_t rows = primal ? x->n : x->m;
+    return x->nnz <= ROWS_MEAN * rows && std::max<int64_t>(x->n, x->m) * 128 < ((int64_t)1 << 31);
+}
+
 // default tile for `ncols` live columns: a row group covers the W = lanes * vec
 // slots of one storage tile (128 bytes of a row; fewer when the batch is
 // narrower), 16 bytes per lane once the batch is that wide; vec never exceeds
 // the width ld was padded for
-Tile heuristic_tile(const pdlpb_ctx* x, int32_t ncols) {
+Tile heuristic_tile(const pdlpb_ctx* x, int32_t ncols, bool primal) {
     if (x->narrow && x->ld <= TINY_LD) {
         // blocks of stride 4, 2 or 1: one lane per row covers every column
         Tile t;
@@ -439,6 +454,16 @@ Tile heuristic_tile(const pdlpb_ctx* x, int32_t ncols) {
     }
     const int32_t tile = x->fp32 ? block_tile<float>() : block_tile<double>();
     const int32_t w = std::min<int32_t>(tile, next_pow2(ncols > 0 ? ncols : 1));
+    if (rows_kernel_serves(x, primal)) {
+        // 16 bytes per lane where the width and the padding allow it, 8 lanes at least
+        Tile t;
+        t.rows = true;
+        t.vec = std::max(1, std::min<int>(w / 8, x->fp32 ? 4 : 2));
+        while (x->ld % t.vec != 0) t.vec /= 2;
+        t.lanes = std::max(8, w / t.vec);
+        t.blocks = DEFAULT_MAX_BLOCKS;
+        return t;
+    }
     int vec = w >= tile ? (x->fp32 ? 4 : 2) : 1;
     if (x->opt.tile_vec > 0) vec = x->opt.tile_vec;
     if (vec > x->vec_ld) vec = x->vec_ld;
@@ -456,7 +481,8 @@ Tile heuristic_tile(const pdlpb_ctx* x, int32_t ncols) {
 }
 
 void choose_tile(pdlpb_ctx* x, int32_t ncols) {
-    x->tp = x->td = heuristic_tile(x, ncols);
+    x->tp = heuristic_tile(x, ncols, true);
+    x->td = heuristic_tile(x, ncols, false);
     x->wpb = 4;
 }
 
@@ -513,6 +539,7 @@ StepArgs<T> step_args(pdlpb_ctx* x, bool primal, int32_t it, int32_t eval, int32
     a.ncols = x->live;
     a.wpb = x->wpb;
     a.max_blocks = primal ? x->tp.blocks : x->td.blocks;
+    a.rows_kernel = (primal ? x->tp.rows : x->td.rows) ? 1 : 0;
     if (primal) {
         a.G = b[4];   // Y
         a.Z = b[0]; a.Z0 = b[1]; a.Zt = b[2]; a.DZ = b[3];
@@ -903,7 +930,8 @@ int tune_epoch(pdlpb_ctx* x) {
         int c = -1;
         if (!ev && nc > 0) {
             c = (it - 2) % nc;
-            x->tp = x->td = cand[c];
+            x->tp = keep_p.rows ? keep_p : cand[c];
+            x->td = keep_d.rows ? keep_d : cand[c];
         } else {
             x->tp = keep_p;
             x->td = keep_d;
@@ -942,8 +970,8 @@ int tune_epoch(pdlpb_ctx* x) {
             (bd < 0 || ms[2 * c + 1] / cnt[2 * c + 1] < ms[2 * bd + 1] / cnt[2 * bd + 1]))
             bd = c;
     }
-    x->tp = bp >= 0 ? cand[bp] : keep_p;
-    x->td = bd >= 0 ? cand[bd] : keep_d;
+    x->tp = bp >= 0 && !keep_p.rows ? cand[bp] : keep_p;
+    x->td = bd >= 0 && !keep_d.rows ? cand[bd] : keep_d;
     x->tuned.push_back({(int64_t)x->live | ((int64_t)x->ld << 32), {x->tp, x->td}});
     return PDLPB_OK;
 }
@@ -1356,7 +1384,7 @@ int run_solve(pdlpb_ctx* x, double tol, int32_t max_iters) {
                         x->td = e.second.second;
                         hit = true;
                     }
-                tune_now = !hit && !x->timing;
+                tune_now = !hit && !x->timing && !(x->tp.rows && x->td.rows);
             }
         }
         const bool persist = persist_plan(x, x->live).mode != PERSIST_NONE;

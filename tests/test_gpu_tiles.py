@@ -1,6 +1,8 @@
 """Batches whose blocks end inside, at and past a column tile (128 bytes per row):
 every LP's results are, bit for bit, those it has in a batch of at most four LPs,
-whose blocks are one narrow tile."""
+whose blocks are one narrow tile.  The row kernel of the steps against the kernels
+that take any launch shape, bit for bit: every width it has, rows that fill, miss
+and spill the entries a wave holds, 16 and 8 rows per wave."""
 from __future__ import annotations
 
 import numpy as np
@@ -57,3 +59,25 @@ def test_shapes(P, make, B, prec):
     inst = make()
     D = _deltas(inst.n, B)
     _pieces(inst, D, 130, precision=P.MIXED32 if prec == "fp32" else P.FP64, eval_every=32)
+
+
+@pytest.mark.parametrize("prec", ["fp64", "fp32"])
+@pytest.mark.parametrize("make, B", [
+    (make_cfg1, 3),                                     # empty rows, a part of a wave
+    (lambda: make_cfg2(m=97, n=211), 16),               # half a tile (FP32), a whole one (FP64)
+    (lambda: make_cfg2(m=97, n=211), 31),               # odd widths: one slot per lane
+    (lambda: make_cfg2(m=97, n=211), 34),               # two slots per lane in both
+    (lambda: make_facility(F=4, C=600, k=4), 33),       # columns and rows of 600 entries among short ones
+    (lambda: make_cfg2(m=3000, n=7000), 151),           # enough waves for 16 rows each
+], ids=["empty", "16", "31", "34", "spill", "many"])
+def test_row_kernel(P, make, B, prec):
+    inst = make()
+    D = _deltas(inst.n, B)
+    kw = dict(precision=P.MIXED32 if prec == "fp32" else P.FP64, eval_every=32)
+    out = []
+    for shape in ({}, dict(tile_lanes=8, tile_vec=1)):
+        with make_ctx(inst, **kw, **shape) as ctx:
+            ctx.set_kernel_timing(True)
+            out.append(_solve(ctx, D, 70))
+    for key in out[0]:
+        assert np.array_equal(out[0][key], out[1][key], equal_nan=True), key
