@@ -573,7 +573,10 @@ __global__ __launch_bounds__(256) void k_dual(StepArgs<T> a) {
 // and whose per-entry branches keep few gathers in flight, 141 / 120 and
 // 75 / 57 us.  16 rows per wave spread the slot state over two passes; 8 where
 // that leaves fewer than ROWS_WAVES waves (1000 x 2500, 64 LPs, FP64: 5.0 / 5.2 us
-// with 8, 5.6 / 6.7 with 16, 5.6 / 6.1 with k_primal / k_dual).
+// with 8, 5.6 / 6.7 with 16, 5.6 / 6.1 with k_primal / k_dual).  Batches of one to
+// four columns over many rows take a lane (FP64, four columns: two) per row, so a
+// wave has 64 (32); then a gather is a line per lane and row, and that rate bounds
+// it (one FP64 LP at 200k x 500k: 14 us per step for 2M lines, 18 / 22 taken).
 // ---------------------------------------------------------------------------
 constexpr int ROWS_CH = 8;                    // entries of a row gathered together
 constexpr uint32_t ROWS_NONE = 0x80000000u;   // a buffer offset past every tile
@@ -615,9 +618,9 @@ __device__ __forceinline__ void buffer_store(__amdgpu_buffer_rsrc_t r, uint32_t 
     }
 }
 
-template <typename T, int G, int VEC, int ROWS, bool PRIMAL>
+template <typename T, int G, int VEC, int ROWS, int E, bool PRIMAL>
 __global__ __launch_bounds__(256, 4) void k_step_rows(StepArgs<T> a) {
-    constexpr int RPW = 64 / G, E = ROWS / 2, ENT = 64 * E;   // 32 entries per row of the wave
+    constexpr int RPW = 64 / G, ENT = 64 * E;   // E entries per lane held in LDS
     __shared__ T val_[4][ENT + ROWS_CH];
     __shared__ uint32_t off_[4][ENT + ROWS_CH];
     __shared__ T rd_[4][3 * ROWS];
@@ -637,8 +640,8 @@ __global__ __launch_bounds__(256, 4) void k_step_rows(StepArgs<T> a) {
     const uint32_t lb = (uint32_t)cl * (uint32_t)sizeof(T);
 
     // the rows' entries, bounds and objective, on their way to LDS
-    const int32_t rpv = a.rp[min(rb + min(lane, ROWS), re)];
-    const int32_t kb = __builtin_amdgcn_readfirstlane(rpv), ke = __builtin_amdgcn_readlane(rpv, ROWS);
+    const int32_t rpv = a.rp[min(rb + lane, re)];
+    const int32_t kb = a.rp[rb], ke = a.rp[re];
     int32_t ci[E];
     T av[E], rc = T(0);
 #pragma unroll
@@ -683,8 +686,9 @@ __global__ __launch_bounds__(256, 4) void k_step_rows(StepArgs<T> a) {
             off[e * 64 + lane] = (uint32_t)ci[e] * ldb;
             val[e * 64 + lane] = av[e];
         }
-    if (lane <= ROWS) rp[lane] = rpv - kb;
+    if (lane == 0) rp[ROWS] = ke - kb;
     if (lane < ROWS) {
+        rp[lane] = rpv - kb;
         rd[lane] = rc;
         rd[ROWS + lane] = rlo;
         rd[2 * ROWS + lane] = rhi;
@@ -3909,17 +3913,31 @@ template <typename T, int G, int VEC, bool PRIMAL>
 hipError_t launch_rows_gv(StepArgs<T> a, hipStream_t s) {
     const int64_t tiles = ((int64_t)a.ncols + G * VEC - 1) / (G * VEC);
     if (a.rows <= 0 || tiles <= 0) return hipSuccess;
-    const bool few = ((int64_t)a.rows + 15) / 16 * tiles < ROWS_WAVES;
-    const int32_t per = 4 * (few ? 8 : 16);
-    const dim3 grid = step_grid(a, G * VEC, (uint32_t)((a.rows + per - 1) / per), (uint32_t)tiles);
-    if (few) hipLaunchKernelGGL((k_step_rows<T, G, VEC, 8, PRIMAL>), grid, dim3(256), 0, s, a);
-    else hipLaunchKernelGGL((k_step_rows<T, G, VEC, 16, PRIMAL>), grid, dim3(256), 0, s, a);
-    return hipGetLastError();
+    auto go = [&](auto kernel, int32_t per) {
+        const dim3 grid = step_grid(a, G * VEC, (uint32_t)((a.rows + 4 * per - 1) / (4 * per)), (uint32_t)tiles);
+        hipLaunchKernelGGL(kernel, grid, dim3(256), 0, s, a);
+        return hipGetLastError();
+    };
+    if constexpr (G < 8) {
+        // one pass; LDS for 8 entries per row where the mean is below, which leaves
+        // more waves per CU (primal step of one FP64 LP, 500k rows of 4 entries:
+        // 18.4 us, 20.4 with 16 per row)
+        if (G == 1 && a.short_rows) return go(k_step_rows<T, G, VEC, 64 / G, 8, PRIMAL>, 64 / G);
+        return go(k_step_rows<T, G, VEC, 64 / G, 16, PRIMAL>, 64 / G);
+    } else {
+        const bool few = ((int64_t)a.rows + 15) / 16 * tiles < ROWS_WAVES;
+        if (few) return go(k_step_rows<T, G, VEC, 8, 4, PRIMAL>, 8);
+        return go(k_step_rows<T, G, VEC, 16, 8, PRIMAL>, 16);
+    }
 }
 
 template <typename T, bool PRIMAL>
 hipError_t launch_rows(const StepArgs<T>& a, int lanes, int vec, hipStream_t s) {
     constexpr int V = 16 / (int)sizeof(T);
+    if (lanes == 1 && vec == 1) return launch_rows_gv<T, 1, 1, PRIMAL>(a, s);
+    if (lanes == 1 && vec == 2) return launch_rows_gv<T, 1, 2, PRIMAL>(a, s);
+    if (lanes == 1 && vec == V) return launch_rows_gv<T, 1, V, PRIMAL>(a, s);
+    if (lanes == 4 / V && vec == V) return launch_rows_gv<T, 4 / V, V, PRIMAL>(a, s);
     if (lanes == 8 && vec == 1) return launch_rows_gv<T, 8, 1, PRIMAL>(a, s);
     if (lanes == 8 && vec == 2) return launch_rows_gv<T, 8, 2, PRIMAL>(a, s);
     if (lanes == 8 && vec == V) return launch_rows_gv<T, 8, V, PRIMAL>(a, s);

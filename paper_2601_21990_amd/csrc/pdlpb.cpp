@@ -439,12 +439,26 @@ bool rows_kernel_serves(const pdlpb_ctx* x, bool primal) {
     return x->nnz <= ROWS_MEAN * rows && std::max<int64_t>(x->n, x->m) * 128 < ((int64_t)1 << 31);
 }
 
+// Batches of up to four columns: a lane takes a row's columns (16 bytes at most),
+// a wave 64 or 32 rows, instead of 8 lanes per row of which most idle.  The rows
+// have to be many enough to fill the waves, LANE_ROWS for each column.  Steps of
+// one FP64 LP, a lane per row against 8: 50k rows of 6 entries 5.4 / 7.4 us, 500k
+// of 4 entries 18.4 / 31.1, but 7k rows of 5 4.7 / 5.0 and 3k rows of 12 6.2 / 5.3.
+// The wave's LDS holds 16 entries for each of 64 rows, which means of up to 14 fit.
+constexpr int64_t LANE_ROWS = 16384, LANE_MEAN = 14;
+bool lane_rows_serve(const pdlpb_ctx* x, bool primal, int32_t w, int lanes) {
+    const int64_t rows = primal ? x->n : x->m;
+    return w <= 4 && rows >= LANE_ROWS * w && (lanes > 1 || x->nnz <= LANE_MEAN * rows);
+}
+
 // default tile for `ncols` live columns: a row group covers the W = lanes * vec
 // slots of one storage tile (128 bytes of a row; fewer when the batch is
 // narrower), 16 bytes per lane once the batch is that wide; vec never exceeds
 // the width ld was padded for
 Tile heuristic_tile(const pdlpb_ctx* x, int32_t ncols, bool primal) {
-    if (x->narrow && x->ld <= TINY_LD) {
+    const int v = x->fp32 ? 4 : 2;   // values in 16 bytes
+    if (x->narrow && x->ld <= TINY_LD &&
+        !(rows_kernel_serves(x, primal) && lane_rows_serve(x, primal, x->ld, x->ld / std::min(x->ld, v)))) {
         // blocks of stride 4, 2 or 1: one lane per row covers every column
         Tile t;
         t.lanes = 1;
@@ -455,12 +469,18 @@ Tile heuristic_tile(const pdlpb_ctx* x, int32_t ncols, bool primal) {
     const int32_t tile = x->fp32 ? block_tile<float>() : block_tile<double>();
     const int32_t w = std::min<int32_t>(tile, next_pow2(ncols > 0 ? ncols : 1));
     if (rows_kernel_serves(x, primal)) {
-        // 16 bytes per lane where the width and the padding allow it, 8 lanes at least
+        // 16 bytes per lane where the width and the padding allow it, 8 lanes at
+        // least unless a lane takes a row
         Tile t;
         t.rows = true;
-        t.vec = std::max(1, std::min<int>(w / 8, x->fp32 ? 4 : 2));
+        t.vec = std::max(1, std::min<int>(w / 8, v));
         while (x->ld % t.vec != 0) t.vec /= 2;
         t.lanes = std::max(8, w / t.vec);
+        const int fit = std::min<int>(w, v);
+        if (x->ld % fit == 0 && lane_rows_serve(x, primal, w, w / fit)) {
+            t.vec = fit;
+            t.lanes = w / fit;
+        }
         t.blocks = DEFAULT_MAX_BLOCKS;
         return t;
     }
@@ -540,6 +560,7 @@ StepArgs<T> step_args(pdlpb_ctx* x, bool primal, int32_t it, int32_t eval, int32
     a.wpb = x->wpb;
     a.max_blocks = primal ? x->tp.blocks : x->td.blocks;
     a.rows_kernel = (primal ? x->tp.rows : x->td.rows) ? 1 : 0;
+    a.short_rows = x->nnz <= 6 * (int64_t)(primal ? x->n : x->m) ? 1 : 0;
     if (primal) {
         a.G = b[4];   // Y
         a.Z = b[0]; a.Z0 = b[1]; a.Zt = b[2]; a.DZ = b[3];
@@ -1583,11 +1604,12 @@ double default_weight(const pdlpb_ctx* x, const pdlpb_delta& q) {
     return (cn > 1e-10 && x->norm_b > 1e-10) ? cn / x->norm_b : 1.0;
 }
 
-// Vector width the row stride of a `cols`-column storage is padded for: 4 when
-// the launches are large enough to be tuned over every shape, else the width
-// the default tile uses.
+// Vector width the row stride of a `cols`-column storage is padded for: 4 (for one
+// or two columns no more than those) when the launches are large enough to be
+// tuned over every shape, else the width the default tile uses.
 int32_t vec_for(const pdlpb_ctx* x, int32_t cols) {
-    if (x->opt.autotune && x->opt.tile_vec == 0 && launch_bytes(x, cols) >= 32e6) return 4;
+    if (x->opt.autotune && x->opt.tile_vec == 0 && launch_bytes(x, cols) >= 32e6)
+        return std::min<int32_t>(4, next_pow2(cols > 0 ? cols : 1));
     const int32_t w = std::min<int32_t>(64, next_pow2(cols > 0 ? cols : 1));
     int32_t vec = w >= 64 ? (x->fp32 ? 4 : 2) : 1;
     if (x->opt.tile_vec > 0) vec = x->opt.tile_vec;

@@ -69,7 +69,11 @@ def test_shapes(P, make, B, prec):
     (lambda: make_cfg2(m=97, n=211), 34),               # two slots per lane in both
     (lambda: make_facility(F=4, C=600, k=4), 33),       # columns and rows of 600 entries among short ones
     (lambda: make_cfg2(m=3000, n=7000), 151),           # enough waves for 16 rows each
-], ids=["empty", "16", "31", "34", "spill", "many"])
+    (lambda: make_cfg2(m=16385, n=32770), 1),           # a lane per row, a remainder of a wave
+    (lambda: make_cfg2(m=16385, n=32770), 2),           # a lane per row on one side
+    (lambda: make_cfg2(m=30000, n=65537), 3),           # four columns, two lanes per row (FP64)
+    (lambda: make_facility(F=4, C=4500, k=4), 1),       # a lane per row, rows of 4500 entries
+], ids=["empty", "16", "31", "34", "spill", "many", "one", "two", "three", "one-spill"])
 def test_row_kernel(P, make, B, prec):
     inst = make()
     D = _deltas(inst.n, B)
