@@ -1085,6 +1085,67 @@ __global__ __launch_bounds__(256) void k_eval(EvalArgs<T> a) {
     }
 }
 
+// Terms of row i of one side for slot s.  N nonzeros at a time: their indices, then
+// their gathers, are in flight together, without a branch (past the row's end the
+// last one again, whose products are dropped); the sums add them in CSR order.
+template <typename T, bool KKT, int N>
+__device__ __forceinline__ void eval_row(const EvalArgs<T>& a, bool xside, int32_t i, int32_t s, int32_t varkind,
+                                         double* tq) {
+    const int32_t* const ci = xside ? a.t_ci : a.a_ci;
+    const T* const av = xside ? a.t_v : a.a_v;
+    const int32_t kb = (xside ? a.t_rp : a.a_rp)[i], ke = (xside ? a.t_rp : a.a_rp)[i + 1];
+    const int32_t grows = xside ? a.m : a.n;
+    const size_t go = block_offset<T>(grows, s);
+    const int32_t gs = block_stride<T>(a.ld, s);
+    const T* const zt = (xside ? a.Yt : a.Xt) + go;
+    const T* const dz = (xside ? a.DY : a.DX) + go;
+    XRowIn<T> rx{};
+    YRowIn<T> ry{};
+    if (xside) rx = load_xrow<T, KKT>(a, i, s);
+    else ry = load_yrow<T, KKT>(a, i, s);
+    // x side: (A' y~)_i, (A' dy)_i, (A' Pi_B[l,u](dy))_i; y side: (A x~)_i, (A dx)_i
+    double g = 0.0, h = 0.0, pdy = 0.0;
+    for (int32_t k0 = kb; k0 < ke; k0 += N) {
+        int32_t jj[N], cd[N];
+        T vv[N], zv[N], dv[N];
+#pragma unroll
+        for (int u = 0; u < N; ++u) {
+            const int32_t k = min(k0 + u, ke - 1);
+            jj[u] = ci[k];
+            vv[u] = av[k];
+        }
+#pragma unroll
+        for (int u = 0; u < N; ++u) {
+            const size_t f = (size_t)jj[u] * gs;
+            zv[u] = zt[f];
+            if constexpr (!KKT) {
+                dv[u] = dz[f];
+                cd[u] = xside ? a.rcode[jj[u]] : 0;
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < N; ++u) {
+            const bool in = k0 + u < ke;
+            const double w = (double)vv[u];
+            const double g1 = fma(w, (double)zv[u], g);
+            g = in ? g1 : g;
+            if constexpr (!KKT) {
+                const double d = (double)dv[u];
+                const double h1 = fma(w, d, h), p1 = fma(w, barrier_code(d, cd[u]), pdy);
+                h = in ? h1 : h;
+                pdy = in ? p1 : pdy;
+            }
+        }
+    }
+    if (xside) {
+        if constexpr (KKT) finish_xrow_kkt(rx.wide(), g, varkind, a.sl.dval, s, i, tq);
+        else finish_xrow(rx.wide(), g, h, pdy, varkind, a.sl.dval, s, i, tq);
+    } else {
+        if constexpr (KKT) finish_yrow_kkt(ry.wide(), g, tq);
+        else finish_yrow(ry.wide(), g, h, tq);
+    }
+}
+
 // ---------------------------------------------------------------------------
 // Evaluation for narrow batches: the same sums as k_eval, bit for bit, with
 // the lanes spread over rows instead of slots.  A block owns one panel and one
@@ -1132,86 +1193,7 @@ __global__ __launch_bounds__(256) void k_eval_narrow(EvalArgs<T> a) {
         const int32_t i = rb + lane;
         if (i < r1) {
             double tq[NTERM];
-            if (xside) {
-                const XRowIn<T> r = load_xrow<T, KKT>(a, i, s);
-                double g = 0.0, h = 0.0, pdy = 0.0;
-                const int32_t kb = a.t_rp[i], ke = a.t_rp[i + 1];
-                // NCH nonzeros at a time: their indices, then their gathers, are
-                // in flight together; the sums still add them in CSR order
-                for (int32_t k0 = kb; k0 < ke; k0 += NCH) {
-                    int32_t jj[NCH], cd[NCH];
-                    T vv[NCH], yv[NCH], dv[NCH];
-#pragma unroll
-                    for (int u = 0; u < NCH; ++u) {
-                        jj[u] = 0;
-                        vv[u] = T(0);
-                        if (k0 + u < ke) {
-                            jj[u] = a.t_ci[k0 + u];
-                            vv[u] = a.t_v[k0 + u];
-                        }
-                    }
-#pragma unroll
-                    for (int u = 0; u < NCH; ++u) {
-                        if (k0 + u < ke) {
-                            const size_t f = block_at<T>(a.ld, a.m, jj[u], s);
-                            yv[u] = a.Yt[f];
-                            if constexpr (!KKT) {
-                                dv[u] = a.DY[f];
-                                cd[u] = a.rcode[jj[u]];
-                            }
-                        }
-                    }
-#pragma unroll
-                    for (int u = 0; u < NCH; ++u) {
-                        if (k0 + u < ke) {
-                            const double w = (double)vv[u];
-                            g = fma(w, (double)yv[u], g);
-                            if constexpr (!KKT) {
-                                const double d = (double)dv[u];
-                                h = fma(w, d, h);
-                                pdy = fma(w, barrier_code(d, cd[u]), pdy);
-                            }
-                        }
-                    }
-                }
-                if constexpr (KKT) finish_xrow_kkt(r.wide(), g, varkind, a.sl.dval, s, i, tq);
-                else finish_xrow(r.wide(), g, h, pdy, varkind, a.sl.dval, s, i, tq);
-            } else {
-                const YRowIn<T> r = load_yrow<T, KKT>(a, i, s);
-                double ax = 0.0, adx = 0.0;
-                const int32_t kb = a.a_rp[i], ke = a.a_rp[i + 1];
-                for (int32_t k0 = kb; k0 < ke; k0 += NCH) {
-                    int32_t jj[NCH];
-                    T vv[NCH], xv[NCH], dv[NCH];
-#pragma unroll
-                    for (int u = 0; u < NCH; ++u) {
-                        jj[u] = 0;
-                        vv[u] = T(0);
-                        if (k0 + u < ke) {
-                            jj[u] = a.a_ci[k0 + u];
-                            vv[u] = a.a_v[k0 + u];
-                        }
-                    }
-#pragma unroll
-                    for (int u = 0; u < NCH; ++u) {
-                        if (k0 + u < ke) {
-                            const size_t f = block_at<T>(a.ld, a.n, jj[u], s);
-                            xv[u] = a.Xt[f];
-                            if constexpr (!KKT) dv[u] = a.DX[f];
-                        }
-                    }
-#pragma unroll
-                    for (int u = 0; u < NCH; ++u) {
-                        if (k0 + u < ke) {
-                            const double w = (double)vv[u];
-                            ax = fma(w, (double)xv[u], ax);
-                            if constexpr (!KKT) adx = fma(w, (double)dv[u], adx);
-                        }
-                    }
-                }
-                if constexpr (KKT) finish_yrow_kkt(r.wide(), ax, tq);
-                else finish_yrow(r.wide(), ax, adx, tq);
-            }
+            eval_row<T, KKT, NCH>(a, xside, i, s, varkind, tq);
 #pragma unroll
             for (int q = 0; q < NTERM; ++q) terms[wave][lane][q] = tq[q];
         }
@@ -1228,6 +1210,65 @@ __global__ __launch_bounds__(256) void k_eval_narrow(EvalArgs<T> a) {
         double* out = (xside ? a.part_x : a.part_y) + (size_t)panel * NTERM * a.ld + s;
         const double v = ((red[0][lane] + red[1][lane]) + red[2][lane]) + red[3][lane];
         out[(size_t)lane * a.ld] = v;
+    }
+}
+
+// The same for small panels (4 pw <= 64 rows, both sides of a matrix up to 131072
+// rows), where a wave of k_eval_narrow has pw rows for its 64 lanes.  A wave owns 64
+// consecutive rows, 64 / (4 pw) whole panels, of one slot, a lane per row; the
+// chains, four per panel, then add their rows' terms in order, every lane another
+// (chain, term), and the panels add their four chains.  Bound by the chain of
+// dependent loads (row pointers, entries, gathers) and, with more columns, by their
+// number.  12011 x 30011, FP64, all LPs evaluated,
+// 1 / 4 / 8 / 16 LPs: 9 / 18 / 33 / 54 us (k_eval_narrow 17 / 47 / 89 / 176).
+constexpr int EVAL_RCH = 8;   // nonzeros of a row loaded together
+template <typename T, bool KKT>
+__global__ __launch_bounds__(256) void k_eval_rows(EvalArgs<T> a) {
+    __shared__ double terms_[4][64][NTERM + 1];
+    __shared__ double chain_[4][16 * NTERM];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int32_t gx = (a.n + 63) / 64, groups = gx + (a.m + 63) / 64;
+    // four columns of a row group per workgroup, its workgroups on one XCD as in
+    // k_eval_narrow
+    const int32_t cg = (a.ncols + 3) / 4;
+    const int32_t q8 = (int32_t)(blockIdx.x >> 3);
+    const int32_t s = q8 % cg * 4 + wave, grp = q8 / cg * 8 + (int32_t)(blockIdx.x & 7);
+    if (grp >= groups || s >= a.ncols) return;
+    if (!a.full && a.g->quiet) return;
+    if (s >= a.g->n_cols) return;
+    const SlotKey key = a.sl.key[s];
+    const int32_t t = a.g->t0 + a.it;
+    if (!(a.full || t == key.t_anchor || t >= key.t_end)) return;
+    const bool xside = grp < gx;
+    const int32_t r0 = (xside ? grp : grp - gx) * 64, rows = xside ? a.n : a.m;
+    const int32_t pw = xside ? a.pw_x : a.pw_y;
+    double(*const terms)[NTERM + 1] = terms_[wave];
+    double* const chain = chain_[wave];
+    const int32_t cnt = min(64, rows - r0);
+    if (lane < cnt) {
+        double tq[NTERM];
+        eval_row<T, KKT, EVAL_RCH>(a, xside, r0 + lane, s, key.varkind, tq);
+#pragma unroll
+        for (int q = 0; q < NTERM; ++q) terms[lane][q] = tq[q];
+    }
+    // a wave's LDS accesses stay in order
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    const int32_t chains = 64 / pw;
+    for (int32_t i = lane; i < chains * NTERM; i += 64) {
+        const int32_t c = i / NTERM, q = i % NTERM;
+        double acc = 0.0;
+        for (int32_t j = c * pw; j < min((c + 1) * pw, cnt); ++j) acc += terms[j][q];
+        chain[i] = acc;
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    const int32_t p0 = r0 / (4 * pw), np = min(chains / 4, (xside ? a.npx : a.npy) - p0);
+    if (lane < np * NTERM) {
+        const int32_t p = lane / NTERM, q = lane % NTERM;
+        const double* c = chain + p * 4 * NTERM + q;
+        double* out = (xside ? a.part_x : a.part_y) + (size_t)(p0 + p) * NTERM * a.ld + s;
+        out[(size_t)q * a.ld] = ((c[0] + c[NTERM]) + c[2 * NTERM]) + c[3 * NTERM];
     }
 }
 
@@ -3971,12 +4012,30 @@ hipError_t launch_dual(const StepArgs<T>& a, int lanes, int vec, hipStream_t s) 
     return launch_step<T, false>(a, lanes, vec, s);
 }
 
-// batches this narrow use k_eval_narrow (rows across the lanes)
+// Batches this narrow are evaluated with rows across the lanes, a gather a line of
+// its own for each LP, where k_eval gathers 64 slots' lines and leaves the lanes of
+// absent ones idle.  From 9 columns on k_eval_rows serves while rows times columns
+// stay below 2^18, or where only some LPs are evaluated (the others' waves leave at
+// once).  All LPs, FP64, k_eval_rows / k_eval: 12011 x 30011, 8 LPs 33 / 47 us,
+// 16 LPs 54 / 47; 5000 x 12000, 16 LPs 28 / 28; 1000 x 2500, 16 LPs 14 / 19.  Larger
+// panels (k_eval_narrow): strong branching of 512 LPs at 200k x 500k takes 29.5 ms
+// with it up to 16 columns, 30.0 up to 8.
 constexpr int32_t EVAL_NARROW_COLS = 16;
 
 template <typename T>
 hipError_t launch_eval(const EvalArgs<T>& a, hipStream_t s) {
-    if (a.ncols <= EVAL_NARROW_COLS) {
+    const bool small = a.pw_x <= 16 && a.pw_y <= 16;
+    const bool narrow = a.ncols <= EVAL_NARROW_COLS / 2 ||
+                        (a.ncols <= EVAL_NARROW_COLS &&
+                         (!small || !a.full || ((int64_t)a.n + a.m) * a.ncols <= (1 << 18)));
+    if (narrow && small) {
+        const int64_t groups = (((int64_t)a.n + 63) / 64 + ((int64_t)a.m + 63) / 64 + 7) / 8 * 8 * ((a.ncols + 3) / 4);
+        if (groups <= 0) return hipSuccess;
+        if (a.kkt_only) hipLaunchKernelGGL((k_eval_rows<T, true>), dim3((uint32_t)groups), dim3(256), 0, s, a);
+        else hipLaunchKernelGGL((k_eval_rows<T, false>), dim3((uint32_t)groups), dim3(256), 0, s, a);
+        return hipGetLastError();
+    }
+    if (narrow) {
         const int64_t groups = ((int64_t)a.npx + a.npy + 7) / 8 * 8 * a.ncols;
         if (groups <= 0) return hipSuccess;
         if (a.kkt_only)

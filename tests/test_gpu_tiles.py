@@ -85,3 +85,19 @@ def test_row_kernel(P, make, B, prec):
             out.append(_solve(ctx, D, 70))
     for key in out[0]:
         assert np.array_equal(out[0][key], out[1][key], equal_nan=True), key
+
+
+@pytest.mark.parametrize("prec", ["fp64", "fp32"])
+@pytest.mark.parametrize("m, n", [(63, 143), (64, 129), (1000, 2500), (33000, 66000)])
+def test_row_evaluations(P, m, n, prec):
+    """Evaluations with a lane per row (4 and 8 rows per chain, groups that end inside
+    a panel) against the 64-slot kernel, which a batch of 40 takes."""
+    inst = make_cfg2(m=m, n=n)
+    D = _deltas(inst.n, 40)
+    with make_ctx(inst, precision=P.MIXED32 if prec == "fp32" else P.FP64, eval_every=8) as ctx:
+        ctx.set_kernel_timing(True)
+        whole = _solve(ctx, D, 33)
+        for i, j in ((0, 1), (1, 7), (7, 18)):
+            part = _solve(ctx, D[i:j], 33)
+            for key in whole:
+                assert np.array_equal(whole[key][i:j], part[key], equal_nan=True), (key, i)
