@@ -110,7 +110,8 @@ typedef struct pdlpb_options {
     int32_t tile_lanes;       /* 0 = automatic; else lanes per row group of the fused SpMM kernels (1..64, power of 2) */
     int32_t tile_vec;         /* 0 = automatic; else columns per lane (1, 2 or 4) */
     int32_t autotune;         /* 1 (default): time tile shapes on the first block of C iterations of
-                                 a large batch and keep the fastest per kernel; 0: fixed heuristic */
+                                 a large batch and keep the fastest per kernel, where the step kernels
+                                 of any launch shape serve it; 0: fixed heuristic */
     int32_t shared_start;     /* first iteration of a batch whose running LPs all start from one point
                                  (PDLPB_WARM_NONE or PDLPB_WARM_SHARED), the objective changes with
                                  one primal weight and the other LPs with one primal weight
@@ -128,8 +129,11 @@ typedef struct pdlpb_options {
     double  dual_tol;         /* eps of the dual-feasibility test of eq:stopping: < 0 (default -1) uses the
                                  stopping tolerance; >= 0 as given.  The bound-tightening experiments of
                                  Section 6 check dual feasibility at 1e-8 before trusting a dual bound */
-    int32_t max_blocks;       /* cap on the workgroups of one step launch; their waves loop over the rows.
-                                 0 (default): 16384 (64 4-wave workgroups per compute unit) */
+    int32_t max_blocks;       /* cap on the workgroups of one step launch; their waves loop over the rows
+                                 (a cap, like tile_lanes or tile_vec, selects the step kernels that take
+                                 any launch shape).  0 (default): the row kernels uncapped where rows have
+                                 at most 24 entries on average, else 16384 (64 4-wave workgroups per
+                                 compute unit) */
     int32_t scaling;          /* diagonal preconditioning of A at create: 0 (default) none; 1 ten Ruiz
                                  equilibration passes then one Pock-Chambolle pass (alpha = 1).  The
                                  solver then works on D_r A D_c (the stopping and infeasibility tests

@@ -619,7 +619,7 @@ __device__ __forceinline__ void buffer_store(__amdgpu_buffer_rsrc_t r, uint32_t 
 }
 
 template <typename T, int G, int VEC, int ROWS, int E, bool PRIMAL>
-__global__ __launch_bounds__(256, 4) void k_step_rows(StepArgs<T> a) {
+__device__ __forceinline__ void step_rows(const StepArgs<T>& a) {
     constexpr int RPW = 64 / G, ENT = 64 * E;   // E entries per lane held in LDS
     __shared__ T val_[4][ENT + ROWS_CH];
     __shared__ uint32_t off_[4][ENT + ROWS_CH];
@@ -793,6 +793,15 @@ __global__ __launch_bounds__(256, 4) void k_step_rows(StepArgs<T> a) {
                 }
         }
     }
+}
+
+template <typename T, int G, int VEC, int ROWS, int E>
+__global__ __launch_bounds__(256, 4) void k_primal_rows(StepArgs<T> a) {
+    step_rows<T, G, VEC, ROWS, E, true>(a);
+}
+template <typename T, int G, int VEC, int ROWS, int E>
+__global__ __launch_bounds__(256, 4) void k_dual_rows(StepArgs<T> a) {
+    step_rows<T, G, VEC, ROWS, E, false>(a);
 }
 
 // ---------------------------------------------------------------------------
@@ -1273,26 +1282,39 @@ __global__ __launch_bounds__(256) void k_eval_rows(EvalArgs<T> a) {
 }
 
 // sums[q][s] = sum over panels of part[panel][q][s]; q < NTERM: x side, else y side.
-// One wave per (term, slot): lane l adds panels l, l+64, ... in order, then a
-// butterfly over the 64 lanes (every lane ends with the same bits, since each
+// Of each (term, slot), chain l of 64 adds panels l, l+64, ... in order, then a
+// butterfly over the 64 chains (every lane ends with the same bits, since each
 // level adds the same pair in either order).  The tree depends on the panel
-// count only, not on the batch.
-__global__ __launch_bounds__(256) void k_reduce(ControlArgs a) {
-    const int32_t lane = threadIdx.x & 63;
-    const int32_t pair = blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (pair >= 2 * NTERM * a.ncols) return;
+// count only, not on the batch.  A workgroup owns one term and RED_SLOTS slots, so
+// that a panel's row of slots is read as whole lines: its threads take the (chain,
+// slot) pairs, slots fastest, and its waves then a slot each.  Bound by its loads
+// in flight: 15 us at 20k x 50k, 256 LPs, where a wave per (term, slot), which reads
+// every line of slots once per slot, takes 49.
+constexpr int RED_SLOTS = 16;   // a 128-byte line
+__global__ __launch_bounds__(64 * RED_SLOTS) void k_reduce(ControlArgs a) {
+    __shared__ double chain[RED_SLOTS][65];
     if (!a.full && !a.admit && !a.stop_only && a.g->quiet) return;
-    const int32_t q = pair / a.ncols, s = pair % a.ncols;
+    const int tid = threadIdx.x;
+    const int32_t q = blockIdx.y, s0 = blockIdx.x * RED_SLOTS;
     const bool xside = q < NTERM;
     const int32_t qq = xside ? q : q - NTERM;
     const int32_t np = xside ? a.npx : a.npy;
-    const double* p = (xside ? a.part_x : a.part_y) + (size_t)qq * a.ld + s;
     const size_t stride = (size_t)NTERM * a.ld;
-    double acc = 0.0;
-    for (int32_t i = lane; i < np; i += 64) acc += p[(size_t)i * stride];
+    {
+        const int32_t l = tid / RED_SLOTS, s = min(s0 + tid % RED_SLOTS, a.ncols - 1);
+        const double* p = (xside ? a.part_x : a.part_y) + (size_t)qq * a.ld + s;
+        double acc = 0.0;
+#pragma unroll 8
+        for (int32_t i = l; i < np; i += 64) acc += p[(size_t)i * stride];
+        chain[tid % RED_SLOTS][l] = acc;
+    }
+    __syncthreads();
+    const int32_t lane = tid & 63, w = tid >> 6;
+    if (s0 + w >= a.ncols) return;
+    double acc = chain[w][lane];
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off, 64);
-    if (lane == 0) a.sums[(size_t)q * a.ld + s] = acc;
+    if (lane == 0) a.sums[(size_t)q * a.ld + s0 + w] = acc;
 }
 
 // ---------------------------------------------------------------------------
@@ -3954,21 +3976,22 @@ template <typename T, int G, int VEC, bool PRIMAL>
 hipError_t launch_rows_gv(StepArgs<T> a, hipStream_t s) {
     const int64_t tiles = ((int64_t)a.ncols + G * VEC - 1) / (G * VEC);
     if (a.rows <= 0 || tiles <= 0) return hipSuccess;
-    auto go = [&](auto kernel, int32_t per) {
+    auto go = [&](auto primal, auto dual, int32_t per) {
         const dim3 grid = step_grid(a, G * VEC, (uint32_t)((a.rows + 4 * per - 1) / (4 * per)), (uint32_t)tiles);
-        hipLaunchKernelGGL(kernel, grid, dim3(256), 0, s, a);
+        if constexpr (PRIMAL) hipLaunchKernelGGL(primal, grid, dim3(256), 0, s, a);
+        else hipLaunchKernelGGL(dual, grid, dim3(256), 0, s, a);
         return hipGetLastError();
     };
     if constexpr (G < 8) {
         // one pass; LDS for 8 entries per row where the mean is below, which leaves
         // more waves per CU (primal step of one FP64 LP, 500k rows of 4 entries:
         // 18.4 us, 20.4 with 16 per row)
-        if (G == 1 && a.short_rows) return go(k_step_rows<T, G, VEC, 64 / G, 8, PRIMAL>, 64 / G);
-        return go(k_step_rows<T, G, VEC, 64 / G, 16, PRIMAL>, 64 / G);
+        if (G == 1 && a.short_rows) return go(k_primal_rows<T, G, VEC, 64 / G, 8>, k_dual_rows<T, G, VEC, 64 / G, 8>, 64 / G);
+        return go(k_primal_rows<T, G, VEC, 64 / G, 16>, k_dual_rows<T, G, VEC, 64 / G, 16>, 64 / G);
     } else {
         const bool few = ((int64_t)a.rows + 15) / 16 * tiles < ROWS_WAVES;
-        if (few) return go(k_step_rows<T, G, VEC, 8, 4, PRIMAL>, 8);
-        return go(k_step_rows<T, G, VEC, 16, 8, PRIMAL>, 16);
+        if (few) return go(k_primal_rows<T, G, VEC, 8, 4>, k_dual_rows<T, G, VEC, 8, 4>, 8);
+        return go(k_primal_rows<T, G, VEC, 16, 8>, k_dual_rows<T, G, VEC, 16, 8>, 16);
     }
 }
 
@@ -4078,9 +4101,9 @@ hipError_t launch_persist(const PersistArgs<T>& a, int mode, int threads, hipStr
 }
 
 hipError_t launch_reduce(const ControlArgs& a, hipStream_t s) {
-    const int64_t pairs = (int64_t)2 * NTERM * a.ncols;
-    if (pairs == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_reduce, dim3((uint32_t)((pairs + 3) / 4)), dim3(256), 0, s, a);
+    if (a.ncols <= 0) return hipSuccess;
+    const dim3 grid((uint32_t)((a.ncols + RED_SLOTS - 1) / RED_SLOTS), 2 * NTERM);
+    hipLaunchKernelGGL(k_reduce, grid, dim3(64 * RED_SLOTS), 0, s, a);
     return hipGetLastError();
 }
 

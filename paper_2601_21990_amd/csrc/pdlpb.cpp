@@ -71,7 +71,7 @@ struct Tile {
     int lanes = 64;     // lanes per row group
     int vec = 1;        // consecutive LPs per lane
     int blocks = 0;     // workgroup cap of the launch (0: one wave per row group)
-    bool rows = false;  // the row kernel (k_step_rows); else k_primal / k_dual
+    bool rows = false;  // the row kernel (k_primal_rows, k_dual_rows); else k_primal / k_dual
 };
 
 constexpr int32_t DEFAULT_MAX_BLOCKS = 16384;

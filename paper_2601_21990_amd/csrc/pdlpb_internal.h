@@ -169,7 +169,7 @@ struct StepArgs {
                          //    that the following evaluation of fresh cycles reads; 0: none
     int32_t admit;       // 1: only LPs flagged SLOT_NEW iterate (their first iteration)
     int32_t gx;          // row blocks per column tile when tiles are dealt to XCDs (set at launch), 0: grid y is the tile
-    int32_t rows_kernel; // 1: k_step_rows
+    int32_t rows_kernel; // 1: k_primal_rows / k_dual_rows
     int32_t short_rows;  // 1: at most 6 entries per row on average
     int32_t max_blocks;  // > 0: cap on the workgroups of the launch (waves then loop over rows)
 };
