@@ -1810,6 +1810,7 @@ int resize_storage(pdlpb_ctx* x, int32_t cols, int32_t rows, int32_t keep_cols) 
         x->cap_slots = cols;
         x->cap_block_bytes = (size_t)ld * esz;
         x->ld = ld;
+        x->live = -1;   // shape the launches for the new width, also where the live columns stay
     }
     if (rows != old_rows || x->ctl == nullptr) {
         void* nr[4] = {};
