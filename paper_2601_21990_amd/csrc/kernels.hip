@@ -1631,7 +1631,10 @@ __global__ __launch_bounds__(1024) void k_control(ControlArgs a) {
     }
     if (threadIdx.x == 0) {
         g->n_active = n_run;
-        if (a.advance) g->t0 += a.block;
+        if (a.advance) {
+            if (!g->held) g->t0 += a.block;
+            g->held = 0;
+        }
     }
 }
 
@@ -2113,8 +2116,10 @@ __global__ __launch_bounds__(TAIL_THREADS) void k_tail(TailArgs<T> a) {
 //   A group is formed from workgroups that are running: each joins its XCD's
 // group on arrival, the first one closes it once enough have joined or after a
 // bounded wait, and one that comes later leaves.  Every barrier therefore waits
-// only for running workgroups, whatever else the device runs, and any group size
-// is handled: a member whose slice does not fit in LDS keeps it in memory.
+// only for running workgroups, whatever else the device runs.  A group that closed
+// short works if its larger slices fit in LDS, else it leaves its chunks to the other
+// groups; where no group works the launch iterates nothing (Globals::held), and the
+// host goes on with step launches.
 //   What bounds it now: solo the dependent chain of a half (gather from LDS, sum,
 // update, barrier: ~1000 cycles), staged two barriers and the copies of the two
 // vectors (2900 of ~9600 cycles), columns the gathers' cache lines (~3000 cycles a
@@ -2190,10 +2195,9 @@ __device__ __forceinline__ void group_wait(PersistPart& p) {
 }
 
 // Sums of a chunk in memory (solo: in LDS): panel sums [q][col][panel], x then y;
-// their reductions; the columns' states and step sizes; chain sums of members
-// without LDS.
+// their reductions; the columns' states and step sizes.
 struct PersistSums {
-    double *panels, *red, *tau, *sigma, *chains;
+    double *panels, *red, *tau, *sigma;
     PersistCol* cs;
 };
 __device__ __forceinline__ PersistSums persist_sums(double* w, int32_t np, int32_t W) {
@@ -2203,7 +2207,6 @@ __device__ __forceinline__ PersistSums persist_sums(double* w, int32_t np, int32
     s.tau = s.red + 2 * NTERM * PERSIST_W;
     s.sigma = s.tau + PERSIST_W;
     s.cs = reinterpret_cast<PersistCol*>(s.sigma + PERSIST_W);
-    s.chains = s.sigma + PERSIST_W + sizeof(PersistCol) / 8 * PERSIST_W;
     return s;
 }
 
@@ -2714,11 +2717,9 @@ __device__ __forceinline__ void persist_column(const PersistArgs<T>& a, PersistP
     if (P.member == 0) persist_store_cols(a, S, chunk, 1, ncols);
 }
 
-// ---- several columns, gathered from memory; or a slice kept in memory ----------------
-// Items are (row, column) pairs, columns fastest, a thread keeps its column.  MEM: a
-// member whose slice does not fit in LDS (a group that closed short), from the
-// matrix itself.
-template <typename T, bool MEM>
+// ---- several columns, gathered from memory -------------------------------------------
+// Items are (row, column) pairs, columns fastest, a thread keeps its column.
+template <typename T>
 __device__ __forceinline__ void persist_columns(const PersistArgs<T>& a, PersistPart& P, int32_t chunk,
                                                 int32_t ncols, PersistShared& S, double* lds) {
     const int tid = threadIdx.x, bs = blockDim.x;
@@ -2743,68 +2744,53 @@ __device__ __forceinline__ void persist_columns(const PersistArgs<T>& a, Persist
 
     // ---- this workgroup's slice ----------------------------------------------------
     const int32_t nxi = nxr * W, nyi = nyr * W;
-    T *XK, *X0, *YK, *Y0, *YP, *YH;                 // x^k, anchor; y^k, anchor, y^k/sigma, y^0/(k+2)
-    double *dc = nullptr, *dlo = nullptr, *dhi = nullptr, *drl = nullptr, *dru = nullptr;
-    T *vx = nullptr, *vy = nullptr;
-    int32_t *jx = nullptr, *jy = nullptr;
-    int32_t *px = nullptr, *py = nullptr;           // first quad of a row
-    double* chains;                                 // chain sums [chain][col][term]
     const int32_t chx = (nxr + 15) / 16 * 4, chy = (nyr + 15) / 16 * 4;
-    if constexpr (MEM) {
-        XK = wk + 3 * nW + 4 * mW + (size_t)x0r * W;
-        X0 = XK + nW;
-        YK = wk + 5 * nW + 4 * mW + (size_t)y0r * W;
-        Y0 = YK + mW;
-        YP = YK + 2 * mW;
-        YH = YK + 3 * mW;
-        chains = ws.chains + (size_t)(x0r / 4 + y0r / 4) * W * NTERM;
-    } else {
-        char* q = reinterpret_cast<char*>(lds);
-        auto take = [&](size_t bytes) {
-            char* r = q;
-            q += (bytes + 15) & ~(size_t)15;
-            return r;
-        };
-        XK = (T*)take(nxi * sizeof(T));
-        X0 = (T*)take(nxi * sizeof(T));
-        YK = (T*)take(nyi * sizeof(T));
-        Y0 = (T*)take(nyi * sizeof(T));
-        YP = (T*)take(nyi * sizeof(T));
-        YH = (T*)take(nyi * sizeof(T));
-        dc = (double*)take(nxr * 8);
-        dlo = (double*)take(nxr * 8);
-        dhi = (double*)take(nxr * 8);
-        drl = (double*)take(nyr * 8);
-        dru = (double*)take(nyr * 8);
-        chains = (double*)take((size_t)(chx + chy) * W * NTERM * 8);
-        px = (int32_t*)take((nxr + 1) * 4);
-        py = (int32_t*)take((nyr + 1) * 4);
-        if (wave == 0) quad_scan(a.t_rp + x0r, nxr, px, lane);
-        if (wave == 1) quad_scan(a.a_rp + y0r, nyr, py, lane);
-        __syncthreads();
-        jx = (int32_t*)take((size_t)px[nxr] * 16);
-        vx = (T*)take((size_t)px[nxr] * 4 * sizeof(T));
-        jy = (int32_t*)take((size_t)py[nyr] * 16);
-        vy = (T*)take((size_t)py[nyr] * 4 * sizeof(T));
-        // byte offsets of the gathered rows; a pad gathers its row's last entry again
-        // (one row of zeros for all pads makes every workgroup ask one L2 channel)
-        const int32_t scale = W * (int32_t)sizeof(T);
-        for (int32_t li = tid; li < nxr + nyr; li += bs) {
-            const bool xs = li < nxr;
-            const int32_t r = xs ? li : li - nxr;
-            const int32_t* rp = xs ? a.t_rp + x0r + r : a.a_rp + y0r + r;
-            fill_quads<T, int32_t>(xs ? a.t_ci : a.a_ci, xs ? a.t_v : a.a_v, rp[0], rp[1], (xs ? px : py)[r],
-                                   (xs ? px : py)[r + 1], -1, scale, xs ? jx : jy, xs ? vx : vy);
-        }
-        for (int32_t li = tid; li < nxr; li += bs) {
-            dc[li] = a.c[x0r + li];
-            dlo[li] = a.xl[x0r + li];
-            dhi[li] = a.xu[x0r + li];
-        }
-        for (int32_t li = tid; li < nyr; li += bs) {
-            drl[li] = a.rl[y0r + li];
-            dru[li] = a.ru[y0r + li];
-        }
+    char* q = reinterpret_cast<char*>(lds);
+    auto take = [&](size_t bytes) {
+        char* r = q;
+        q += (bytes + 15) & ~(size_t)15;
+        return r;
+    };
+    // x^k, anchor; y^k, anchor, y^k/sigma, y^0/(k+2)
+    T* const XK = (T*)take(nxi * sizeof(T));
+    T* const X0 = (T*)take(nxi * sizeof(T));
+    T* const YK = (T*)take(nyi * sizeof(T));
+    T* const Y0 = (T*)take(nyi * sizeof(T));
+    T* const YP = (T*)take(nyi * sizeof(T));
+    T* const YH = (T*)take(nyi * sizeof(T));
+    double* const dc = (double*)take(nxr * 8);
+    double* const dlo = (double*)take(nxr * 8);
+    double* const dhi = (double*)take(nxr * 8);
+    double* const drl = (double*)take(nyr * 8);
+    double* const dru = (double*)take(nyr * 8);
+    double* const chains = (double*)take((size_t)(chx + chy) * W * NTERM * 8);   // [chain][col][term]
+    int32_t* const px = (int32_t*)take((nxr + 1) * 4);   // first quad of a row
+    int32_t* const py = (int32_t*)take((nyr + 1) * 4);
+    if (wave == 0) quad_scan(a.t_rp + x0r, nxr, px, lane);
+    if (wave == 1) quad_scan(a.a_rp + y0r, nyr, py, lane);
+    __syncthreads();
+    int32_t* const jx = (int32_t*)take((size_t)px[nxr] * 16);
+    T* const vx = (T*)take((size_t)px[nxr] * 4 * sizeof(T));
+    int32_t* const jy = (int32_t*)take((size_t)py[nyr] * 16);
+    T* const vy = (T*)take((size_t)py[nyr] * 4 * sizeof(T));
+    // byte offsets of the gathered rows; a pad gathers its row's last entry again
+    // (one row of zeros for all pads makes every workgroup ask one L2 channel)
+    const int32_t scale = W * (int32_t)sizeof(T);
+    for (int32_t li = tid; li < nxr + nyr; li += bs) {
+        const bool xs = li < nxr;
+        const int32_t r = xs ? li : li - nxr;
+        const int32_t* rp = xs ? a.t_rp + x0r + r : a.a_rp + y0r + r;
+        fill_quads<T, int32_t>(xs ? a.t_ci : a.a_ci, xs ? a.t_v : a.a_v, rp[0], rp[1], (xs ? px : py)[r],
+                               (xs ? px : py)[r + 1], -1, scale, xs ? jx : jy, xs ? vx : vy);
+    }
+    for (int32_t li = tid; li < nxr; li += bs) {
+        dc[li] = a.c[x0r + li];
+        dlo[li] = a.xl[x0r + li];
+        dhi[li] = a.xu[x0r + li];
+    }
+    for (int32_t li = tid; li < nyr; li += bs) {
+        drl[li] = a.rl[y0r + li];
+        dru[li] = a.ru[y0r + li];
     }
 
     // ---- the parts of an update that need no product --------------------------------
@@ -2847,8 +2833,7 @@ __device__ __forceinline__ void persist_columns(const PersistArgs<T>& a, Persist
     // ---- products --------------------------------------------------------------------
     // one entry of the vector at a row's gather offset (of this thread's column)
     auto from = [&](const T* g, int32_t j) -> T {
-        if constexpr (MEM) return agent_load_t(g + ((size_t)j << lw) + col);
-        else return agent_load_t(reinterpret_cast<const T*>(reinterpret_cast<const char*>(g + col) + (uint32_t)j));
+        return agent_load_t(reinterpret_cast<const T*>(reinterpret_cast<const char*>(g + col) + (uint32_t)j));
     };
     // NV products of row li (x side: column of A) with the vectors g, in CSR order;
     // QF quads of gathers in flight
@@ -2858,67 +2843,45 @@ __device__ __forceinline__ void persist_columns(const PersistArgs<T>& a, Persist
         using A = std::remove_reference_t<decltype(acc[0])>;
 #pragma unroll
         for (int q = 0; q < NV; ++q) acc[q] = A(0);
-        if constexpr (MEM) {
-            const int32_t i = (XS ? x0r : y0r) + li;
-            const int32_t ke = (XS ? a.t_rp : a.a_rp)[i + 1];
-            for (int32_t k0 = (XS ? a.t_rp : a.a_rp)[i]; k0 < ke; k0 += NCH) {
-                T w[NCH], v[NV][NCH];
+        const int32_t qb = (XS ? px : py)[li], qe = (XS ? px : py)[li + 1];
+        for (int32_t q0 = qb; q0 < qe; q0 += QF) {
+            T v[NV][4 * QF];
 #pragma unroll
-                for (int u = 0; u < NCH; ++u) {
-                    const int32_t k = min(k0 + u, ke - 1);
-                    w[u] = (XS ? a.t_v : a.a_v)[k];
-                    const int32_t j = (XS ? a.t_ci : a.a_ci)[k];
+            for (int u = 0; u < QF; ++u) {
+                if (u == 0 || q0 + u < qe) {
+                    const int4 j = reinterpret_cast<const int4*>(XS ? jx : jy)[q0 + u];
 #pragma unroll
-                    for (int q = 0; q < NV; ++q) v[q][u] = from(g[q], j);
-                }
-#pragma unroll
-                for (int u = 0; u < NCH; ++u)
-                    if (k0 + u < ke) {
-#pragma unroll
-                        for (int q = 0; q < NV; ++q) acc[q] = fma((A)w[u], (A)v[q][u], acc[q]);
-                    }
-            }
-        } else {
-            const int32_t qb = (XS ? px : py)[li], qe = (XS ? px : py)[li + 1];
-            for (int32_t q0 = qb; q0 < qe; q0 += QF) {
-                T v[NV][4 * QF];
-#pragma unroll
-                for (int u = 0; u < QF; ++u) {
-                    if (u == 0 || q0 + u < qe) {
-                        const int4 j = reinterpret_cast<const int4*>(XS ? jx : jy)[q0 + u];
-#pragma unroll
-                        for (int q = 0; q < NV; ++q) {
-                            v[q][4 * u] = from(g[q], j.x);
-                            v[q][4 * u + 1] = from(g[q], j.y);
-                            v[q][4 * u + 2] = from(g[q], j.z);
-                            v[q][4 * u + 3] = from(g[q], j.w);
-                        }
-                    }
-                }
-#pragma unroll
-                for (int u = 0; u < QF; ++u) {
-                    if (u == 0 || q0 + u < qe) {
-                        T w[4];
-                        load_quad<T>((XS ? vx : vy) + 4 * (size_t)(q0 + u), w);
-#pragma unroll
-                        for (int e = 0; e < 4; ++e)
-#pragma unroll
-                            for (int q = 0; q < NV; ++q) acc[q] = fma((A)w[e], (A)v[q][4 * u + e], acc[q]);
+                    for (int q = 0; q < NV; ++q) {
+                        v[q][4 * u] = from(g[q], j.x);
+                        v[q][4 * u + 1] = from(g[q], j.y);
+                        v[q][4 * u + 2] = from(g[q], j.z);
+                        v[q][4 * u + 3] = from(g[q], j.w);
                     }
                 }
             }
-            // a pad adds 0 times an entry, which is 0 unless that is not finite: then
-            // the sum without the pads
 #pragma unroll
-            for (int q = 0; q < NV; ++q) {
-                if (!isfinite(acc[q])) {
-                    const int32_t i = (XS ? x0r : y0r) + li;
-                    const int32_t len = (XS ? a.t_rp : a.a_rp)[i + 1] - (XS ? a.t_rp : a.a_rp)[i];
-                    A x = A(0);
-                    for (int32_t k = 4 * qb; k < 4 * qb + len; ++k)
-                        x = fma((A)(XS ? vx : vy)[k], (A)from(g[q], (XS ? jx : jy)[k]), x);
-                    acc[q] = x;
+            for (int u = 0; u < QF; ++u) {
+                if (u == 0 || q0 + u < qe) {
+                    T w[4];
+                    load_quad<T>((XS ? vx : vy) + 4 * (size_t)(q0 + u), w);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+#pragma unroll
+                        for (int q = 0; q < NV; ++q) acc[q] = fma((A)w[e], (A)v[q][4 * u + e], acc[q]);
                 }
+            }
+        }
+        // a pad adds 0 times an entry, which is 0 unless that is not finite: then
+        // the sum without the pads
+#pragma unroll
+        for (int q = 0; q < NV; ++q) {
+            if (!isfinite(acc[q])) {
+                const int32_t i = (XS ? x0r : y0r) + li;
+                const int32_t len = (XS ? a.t_rp : a.a_rp)[i + 1] - (XS ? a.t_rp : a.a_rp)[i];
+                A x = A(0);
+                for (int32_t k = 4 * qb; k < 4 * qb + len; ++k)
+                    x = fma((A)(XS ? vx : vy)[k], (A)from(g[q], (XS ? jx : jy)[k]), x);
+                acc[q] = x;
             }
         }
     };
@@ -2935,8 +2898,7 @@ __device__ __forceinline__ void persist_columns(const PersistArgs<T>& a, Persist
         const T* const gv[1] = {gY};
         for (int32_t i = tid; i < nxi; i += bs) {
             const int32_t li = i >> lw;
-            VarData d{MEM ? a.c[x0r + li] : dc[li], MEM ? a.xl[x0r + li] : dlo[li],
-                      MEM ? a.xu[x0r + li] : dhi[li]};
+            VarData d{dc[li], dlo[li], dhi[li]};
             if (kind == PDLPB_OBJ_UNIT) d.c = 0.0;
             if (li == var) {
                 if (kind == PDLPB_SET_LO) d.lo = dv;
@@ -2961,8 +2923,7 @@ __device__ __forceinline__ void persist_columns(const PersistArgs<T>& a, Persist
         const T* const gv[1] = {gXb};
         for (int32_t i = tid; i < nyi; i += bs) {
             const int32_t li = i >> lw;
-            const double l = MEM ? a.rl[y0r + li] : drl[li];
-            const double u = MEM ? a.ru[y0r + li] : dru[li];
+            const double l = drl[li], u = dru[li];
             const T yk = YK[i], yp = YP[i], yh = YH[i];
             T acc[1];
             products(One{}, Four{}, std::false_type{}, li, gv, acc);
@@ -3165,24 +3126,35 @@ void k_persist_group(PersistArgs<T> a) {
         }
     }
     if (P.member >= 0) {
-        // quads of the slice (rows padded to fours), for the size of its LDS image
-        __syncthreads();
-        if (tid == 0) S.sh[0] = S.sh[1] = 0;
-        __syncthreads();
-        int32_t qx = 0, qy = 0;
-        for (int32_t r = tid; r < P.nxr; r += blockDim.x)
-            qx += (a.t_rp[P.x0r + r + 1] - a.t_rp[P.x0r + r] + 3) / 4;
-        for (int32_t r = tid; r < P.nyr; r += blockDim.x)
-            qy += (a.a_rp[P.y0r + r + 1] - a.a_rp[P.y0r + r] + 3) / 4;
-        if (qx) atomicAdd(&S.sh[0], qx);
-        if (qy) atomicAdd(&S.sh[1], qy);
-        __syncthreads();
-        const int64_t need = STAGED ? persist_lds_column(n, m, P.nxr, P.nyr, (int64_t)S.sh[0] + S.sh[1],
-                                                         sizeof(T), 0)
-                                    : persist_lds(P.nxr, P.nyr, (int64_t)S.sh[0] + S.sh[1], W, sizeof(T));
-        const bool fits = need <= (int64_t)a.lds_bytes &&
-                          (!STAGED || persist_column_threads(P.nxr, P.nyr) <= (int32_t)blockDim.x);
-        for (;;) {
+        // The LDS holds the slices of a full group.  The larger ones of a group that
+        // closed short may not fit; it then takes no chunk, and its members agree on that.
+        bool fits = true;
+        if (nm < a.members) {
+            __syncthreads();
+            if (tid == 0) S.sh[0] = S.sh[1] = 0;
+            __syncthreads();
+            int32_t qx = 0, qy = 0;   // quads of this slice (rows padded to fours)
+            for (int32_t r = tid; r < P.nxr; r += blockDim.x)
+                qx += (a.t_rp[P.x0r + r + 1] - a.t_rp[P.x0r + r] + 3) / 4;
+            for (int32_t r = tid; r < P.nyr; r += blockDim.x)
+                qy += (a.a_rp[P.y0r + r + 1] - a.a_rp[P.y0r + r] + 3) / 4;
+            if (qx) atomicAdd(&S.sh[0], qx);
+            if (qy) atomicAdd(&S.sh[1], qy);
+            __syncthreads();
+            const int64_t q = (int64_t)S.sh[0] + S.sh[1];
+            const int64_t need = STAGED ? persist_lds_column(n, m, P.nxr, P.nyr, q, sizeof(T), 0)
+                                        : persist_lds(P.nxr, P.nyr, q, W, sizeof(T));
+            if (tid == 0 && (need > (int64_t)a.lds_bytes ||
+                             (STAGED && persist_column_threads(P.nxr, P.nyr) > (int32_t)blockDim.x)))
+                __hip_atomic_fetch_or(&P.line->unfit, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            group_arrive<false>(P);
+            group_wait<false>(P);
+            if (tid == 0) S.sh[3] = (int32_t)agent_load(&P.line->unfit);
+            __syncthreads();
+            fits = S.sh[3] == 0;
+            __syncthreads();
+        }
+        while (fits) {
             if (P.member == 0 && tid == 0)
                 agent_store(&P.line->chunk, __hip_atomic_fetch_add(&a.gc->next, 1u, __ATOMIC_RELAXED,
                                                                    __HIP_MEMORY_SCOPE_AGENT));
@@ -3192,23 +3164,25 @@ void k_persist_group(PersistArgs<T> a) {
             __syncthreads();
             const int32_t chunk = S.sh[3];
             if (chunk >= nchunks) break;
-            if (!fits) persist_columns<T, true>(a, P, chunk, ncols, S, persist_mem);
-            else if constexpr (STAGED) persist_column<T, false>(a, P, chunk, ncols, S, persist_mem);
-            else persist_columns<T, false>(a, P, chunk, ncols, S, persist_mem);
+            if constexpr (STAGED) persist_column<T, false>(a, P, chunk, ncols, S, persist_mem);
+            else persist_columns<T>(a, P, chunk, ncols, S, persist_mem);
             __syncthreads();   // the next chunk reuses the LDS
         }
     }
-    // the last workgroup to leave clears the groups for the next launch
+    // The last workgroup to leave clears the groups for the next launch.  A group that
+    // works takes chunks until none is left, so all are done unless no group did.
     __syncthreads();
     if (tid == 0) {
         const uint32_t done = __hip_atomic_fetch_add(&a.gc->exited, 1u, __ATOMIC_RELAXED,
                                                      __HIP_MEMORY_SCOPE_AGENT);
         if (done == gridDim.x - 1) {
+            if (agent_load(&a.gc->next) == 0) a.g->held = 1;
             for (int x = 0; x < PERSIST_XCC; ++x) {
                 agent_store(&a.gc->line[x].joined, 0u);
                 agent_store(&a.gc->line[x].size, 0u);
                 agent_store(&a.gc->line[x].chunk, 0u);
                 agent_store(&a.gc->line[x].arrived, 0u);
+                agent_store(&a.gc->line[x].unfit, 0u);
             }
             agent_store(&a.gc->next, 0u);
             agent_store(&a.gc->exited, 0u);
@@ -4091,8 +4065,9 @@ hipError_t launch_persist(const PersistArgs<T>& a, int mode, int threads, hipStr
         hipLaunchKernelGGL(k_persist_solo<T>, dim3(a.ncols), dim3(threads), a.lds_bytes, s, a);
         return hipGetLastError();
     }
-    if ((1 << a.lw) > PERSIST_W || a.members < 1 || a.members > PERSIST_MEMBERS) return hipErrorInvalidValue;
-    const dim3 grid(PERSIST_GROUPS * a.members);
+    if ((1 << a.lw) > PERSIST_W || a.members < 1 || a.members > PERSIST_MEMBERS || a.launched < 1)
+        return hipErrorInvalidValue;
+    const dim3 grid(PERSIST_GROUPS * a.launched);
     if (mode == PERSIST_STAGED)
         hipLaunchKernelGGL((k_persist_group<T, true>), grid, dim3(threads), a.lds_bytes, s, a);
     else

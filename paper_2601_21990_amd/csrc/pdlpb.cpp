@@ -179,8 +179,10 @@ struct pdlpb_ctx {
     GroupCtl* ps_ctl = nullptr;
     void* ps_work = nullptr;
     double* ps_sum = nullptr;
+    int32_t ps_launched = 0;        // workgroups launched per group at most (0: as planned)
     size_t cap_ps_work = 0, cap_ps_sum = 0;   // bytes
     int32_t* h_pinned = nullptr;    // n_active read-back
+    int32_t seen_t0 = 0;            // Globals::t0 as last read back
     // serving: the plan of the last admission's compaction (Globals, then up to
     // max_batch retire entries), read by the next serve_wait
     int32_t* h_adm_pin = nullptr;
@@ -826,6 +828,7 @@ int enqueue_persist(pdlpb_ctx* x, int32_t blocks) {
     a.ncols = x->live;
     a.lw = plan.lw;
     a.members = plan.members;
+    a.launched = x->ps_launched > 0 ? std::min(x->ps_launched, plan.members) : plan.members;
     a.lds_bytes = (int32_t)plan.lds;
     a.a_rp = x->a_rp; a.a_ci = x->a_ci; a.t_rp = x->t_rp; a.t_ci = x->t_ci;
     if constexpr (sizeof(T) == 8) {
@@ -1011,6 +1014,7 @@ int enqueue_counts(pdlpb_ctx* x, int s) {
 
 int wait_counts(pdlpb_ctx* x, int s, int32_t* n_active, int32_t* n_cols) {
     HIP_TRY(x, hipEventSynchronize(x->cnt_ev[s]));
+    x->seen_t0 = x->h_pinned[8 + 4 * s];      // Globals::t0
     *n_active = x->h_pinned[8 + 4 * s + 1];   // Globals::n_active
     *n_cols = x->h_pinned[8 + 4 * s + 3];     // Globals::n_cols
     return PDLPB_OK;
@@ -1020,6 +1024,7 @@ int read_counts(pdlpb_ctx* x, int32_t* n_active, int32_t* n_cols) {
     HIP_TRY(x, hipMemcpyAsync(x->h_pinned, x->g, 4 * sizeof(int32_t), hipMemcpyDeviceToHost,
                               x->stream));
     HIP_TRY(x, hipStreamSynchronize(x->stream));
+    x->seen_t0 = x->h_pinned[0];  // Globals::t0
     *n_active = x->h_pinned[1];   // Globals::n_active
     *n_cols = x->h_pinned[3];     // Globals::n_cols
     return PDLPB_OK;
@@ -1346,6 +1351,7 @@ int run_solve(pdlpb_ctx* x, double tol, int32_t max_iters) {
     bool in_flight = false;   // a block whose counts have not been read
     int in_slot = 0, next_slot = 0;
     int64_t launched = 0;
+    int32_t step_blocks = 0;  // blocks to run on step launches before the next grouped one
     // no block outlives the call: other entry points write device state with
     // copies that do not wait for the context's (non-blocking) stream
     struct Drain {
@@ -1408,9 +1414,10 @@ int run_solve(pdlpb_ctx* x, double tol, int32_t max_iters) {
                 tune_now = !hit && !x->timing && !(x->tp.rows && x->td.rows);
             }
         }
-        const bool persist = persist_plan(x, x->live).mode != PERSIST_NONE;
+        const bool persist = step_blocks == 0 && persist_plan(x, x->live).mode != PERSIST_NONE;
         if (persist && !in_flight) {
             const int32_t blocks = std::max(1, PERSIST_ITERS / x->opt.eval_every);
+            const int32_t t0 = x->seen_t0;
             rc = ensure_persist(x, x->live);
             if (rc) return rc;
             {
@@ -1421,7 +1428,9 @@ int run_solve(pdlpb_ctx* x, double tol, int32_t max_iters) {
             }
             if (!rc) rc = read_counts(x, &n_active, &n_cols);
             if (rc) return rc;
-            launched += blocks;
+            // no group of workgroups found the room: as many blocks of step launches
+            if (x->seen_t0 == t0) step_blocks = blocks;
+            else launched += blocks;
             continue;
         }
         const bool ahead = !persist && use_graphs && !tune_now && launched >= RUN_AHEAD_AFTER &&
@@ -1434,6 +1443,7 @@ int run_solve(pdlpb_ctx* x, double tol, int32_t max_iters) {
             continue;
         }
         ++launched;
+        if (step_blocks > 0) --step_blocks;
         if (tune_now) {
             rc = tune_epoch<T>(x);
             if (rc) return rc;
@@ -3239,6 +3249,14 @@ int pdlpb_kernel_times(pdlpb_ctx* x, int64_t counts[5], double total_ms[5]) {
         if (counts) counts[q] = x->t_counts[q];
         if (total_ms) total_ms[q] = x->t_ms[q];
     }
+    return PDLPB_OK;
+}
+
+int pdlpb_group_launch(pdlpb_ctx* x, int32_t workgroups) {
+    if (!x) return PDLPB_EINVAL;
+    if (workgroups < 0) return x->fail(PDLPB_EINVAL, "workgroups must be >= 0");
+    x->drop_graph();
+    x->ps_launched = workgroups;
     return PDLPB_OK;
 }
 

@@ -91,7 +91,7 @@ struct Globals {
                          //    running LP starts a restart cycle or reaches its last iteration)
     int32_t n_fresh;     // compaction plan: running LPs below n_cols_next that restarted at
                          //    this evaluation (their anchor and dual iterate become z~)
-    int32_t pad;
+    int32_t held;        // 1: the persistent launch before this control pass iterated nothing
     double  tol;
     double  eta;
     double  r0;          // BATCH_AVG shared r(z^{n,0})
@@ -280,7 +280,8 @@ struct GroupLine {              // one group's words, a cache line of their own
     uint32_t size;              // members, once closed
     uint32_t chunk;             // chunk being worked on
     uint32_t arrived;           // arrivals at the group's barriers
-    uint32_t pad[28];
+    uint32_t unfit;             // nonzero: a member's slice does not fit its LDS
+    uint32_t pad[27];
 };
 struct GroupCtl {               // all zero between launches
     GroupLine line[PERSIST_XCC];
@@ -301,6 +302,7 @@ struct PersistArgs {
     int32_t ncols;             // columns covered: slots [0, min(ncols, live count))
     int32_t lw;                // a chunk holds 1 << lw columns (solo: 0)
     int32_t members;           // workgroups wanted per group
+    int32_t launched;          // workgroups launched per group
     int32_t lds_bytes;         // dynamic LDS of the launch
     const int32_t* a_rp; const int32_t* a_ci; const T* a_v;    // A (m x n)
     const int32_t* t_rp; const int32_t* t_ci; const T* t_v;    // A' (n x m)
@@ -347,19 +349,17 @@ __host__ __device__ inline int32_t persist_column_threads(int32_t rx, int32_t ry
     return t < 128 ? 128 : t;
 }
 // Work vectors of a chunk, rows per column, each with a row of zeros: Xbar, Xt, DX (n),
-// Y, Yt, DY, its barrier projection (m); a member's slice that does not fit in LDS
-// (2 n + 4 m)
+// Y, Yt, DY, its barrier projection (m)
 __host__ __device__ inline size_t persist_stride(int32_t rows) {   // with the row of zeros
     return ((size_t)rows + 4) & ~(size_t)3;
 }
 __host__ __device__ inline size_t persist_work_rows(int32_t n, int32_t m) {
-    return 5 * persist_stride(n) + 8 * persist_stride(m);
+    return 3 * persist_stride(n) + 4 * persist_stride(m);
 }
-// Sums of a chunk: panel sums, their reductions, the columns' step sizes and states,
-// the chain sums of members without LDS
+// Sums of a chunk: panel sums, their reductions, the columns' step sizes and states
 __host__ __device__ inline size_t persist_sum_doubles(int32_t npx, int32_t npy, int32_t W) {
     return (size_t)(npx + npy) * NTERM * W + 2 * NTERM * PERSIST_W +
-           (sizeof(PersistCol) / 8 + 2) * PERSIST_W + (size_t)(npx + npy) * 4 * NTERM * W;
+           (sizeof(PersistCol) / 8 + 2) * PERSIST_W;
 }
 
 // ---- shared start ------------------------------------------------------------
@@ -506,3 +506,8 @@ hipError_t launch_scale(double* x, int32_t len, const double* nrm2sq, hipStream_
 hipError_t launch_fill(double* x, int32_t len, double v, hipStream_t s);
 
 }  // namespace pdlpb
+
+// Workgroups that a grouped persistent launch gives each group at most (0: as many
+// as planned), for tests of groups that close short.  Not part of the interface.
+struct pdlpb_ctx;
+extern "C" int pdlpb_group_launch(pdlpb_ctx* x, int32_t workgroups);

@@ -4,6 +4,8 @@ results, statuses, iteration counts, restart logs and last iterates.  Kernel tim
 runs a solve on the step launches, which is the reference here."""
 from __future__ import annotations
 
+import ctypes as C
+
 import numpy as np
 import pytest
 
@@ -94,6 +96,61 @@ def test_grouped_structured(P, make, B):
     inst = make()
     D = obbt_deltas(choose_vars(inst.n, B // 2, seed=B))
     _same(inst, D, 1e-4, 500, scaling=1, dual_tol=1e-8)
+
+
+class _NanAllocator:
+    """Device memory of a caller's allocator, every word a NaN (FP64 and FP32)."""
+
+    def __init__(self, P):
+        import torch
+        self.live = {}
+
+        def alloc(nbytes, _user):
+            t = torch.full((int(nbytes),), 255, dtype=torch.uint8, device="cuda:0")
+            torch.cuda.synchronize()
+            self.live[t.data_ptr()] = t
+            return t.data_ptr()
+
+        def free(ptr, nbytes, _user):
+            del self.live[int(ptr)]
+
+        self.c_alloc, self.c_free = P.DEV_ALLOC(alloc), P.DEV_FREE(free)
+
+    def install(self, opts):
+        opts.dev_alloc = C.cast(self.c_alloc, C.c_void_p).value
+        opts.dev_free = C.cast(self.c_free, C.c_void_p).value
+        opts.alloc_user = None
+
+
+@pytest.mark.parametrize("prec", ["fp64", "fp32"])
+@pytest.mark.parametrize("m, n, B, sizes", [
+    (2001, 5000, 64, (1, 15, 17, 31)),    # larger slices than the LDS holds; odd rows
+    (1037, 2611, 9, (1, 12, 14, 18)),     # ... that still fit in larger groups
+    (300, 701, 30, (1, 5, 11)),           # ... in most
+    (2000, 5000, 1, (1, 13, 15)),         # one column: members of more rows than threads
+    (1037, 2611, 3, (1, 5, 11, 15)),
+])
+def test_short_groups(P, m, n, B, sizes, prec):
+    """Groups that close with fewer workgroups than planned (as beside other work on
+    the device), on memory that holds NaN before its first use: the step launches'
+    bits, whether the groups work or leave the iterations to step launches."""
+    inst = make_cfg2(m=m, n=n)
+    D = obbt_deltas(choose_vars(n, (B + 1) // 2, seed=B))[:B]
+    precision = P.MIXED32 if prec == "fp32" else P.FP64
+    fn = P.lib.pdlpb_group_launch
+    fn.argtypes, fn.restype = [C.c_void_p, C.c_int32], C.c_int
+    with make_ctx(inst, precision=precision, eval_every=32, stop_every=8) as ctx:
+        ref, rt = _solve(ctx, D, 1e-4, 150, True)
+    with make_ctx(inst, precision=precision, eval_every=32, stop_every=8, allocator=_NanAllocator(P)) as ctx:
+        for size in sizes:
+            assert fn(ctx._h, size) == P.OK
+            print(f"short group m={m} n={n} B={B} {prec} size={size}", flush=True)
+            got, gt = _solve(ctx, D, 1e-4, 150, False)
+            for key in ref:
+                assert np.array_equal(ref[key], got[key], equal_nan=True), (size, key)
+            for x, y in zip(rt, gt):
+                assert np.array_equal(x["x_iter"], y["x_iter"]) and np.array_equal(x["y_iter"], y["y_iter"])
+                assert x["w"] == y["w"] and x["restart_log"] == y["restart_log"]
 
 
 def test_two_contexts_at_once(P):
