@@ -751,6 +751,25 @@ struct PersistPlan {
 // over the XCDs: staged while every XCD has at most one column and a whole vector
 // fits, else row segments of up to 16 columns.  Where nothing fits the step launches
 // are used: they stream the matrix from the caches of the whole chip.
+//
+// A chunk of W columns gathers a line per entry (padded to quads) and half of an
+// iteration with the 32 CUs of one XCD, whatever W, where a step launch gathers with
+// 256 CUs; so narrow chunks of larger matrices are slower than step launches although
+// they fit.  COLUMN_QUADS bounds the quads of a member at W = 1, 2, 4 (at 8 and 16 the
+// LDS does, as at 4).  us per iteration, chunks / step launches, FP64 and FP32, at
+// (quads of a member):
+//   W = 1:  4000 x 10000, 4 entries per column (713), 1 LP 6.5 / 9.1 and 6.1 / 8.5,
+//           8 LPs 7.4 / 9.7 and 7.2 / 8.7;  5000 x 12500, 4 (879), 2 LPs 7.7 / 9.0 and
+//           8.1 / 8.3;  8000 x 16000, 3 (1024), 2 LPs 8.8 / 8.7 and 8.6 / 8.1;
+//           10000 x 20000, 4 (1436), 2 LPs 9.6 / 9.3 and 10.2 / 8.2
+//   W = 2:  4000 x 10000, 8 (1364), 16 LPs 11.0 / 12.9 and 10.7 / 11.3;  10000 x 22000, 4
+//           (1531), 16 LPs, FP32 11.6 / 13.2;  6000 x 12500, 8 (1699), 16 LPs 13.2 / 13.6
+//           and 12.7 / 12.2
+//   W = 4:  6000 x 12500, 8 (1699), 32 LPs, FP32 13.0 / 14.7
+// Solo needs no such rule: 200 x 500, 1 / 256 / 1000 / 4096 LPs 1.8 / 2.4 / 8.5 / 33 us
+// against 8.2 / 9.4 / 16 / 45 on step launches.
+constexpr int64_t COLUMN_QUADS[] = {900, 1600, 2300, 2300, 2300};
+static_assert(1 << (sizeof(COLUMN_QUADS) / sizeof(COLUMN_QUADS[0]) - 1) == PERSIST_W, "chunk widths");
 PersistPlan persist_plan(const pdlpb_ctx* x, int32_t shape) {
     PersistPlan p;
     if (x->m < 1 || x->nnz < 1 || x->opt.restart_scope != PDLPB_RESTART_PER_LP || x->timing ||
@@ -789,7 +808,7 @@ PersistPlan persist_plan(const pdlpb_ctx* x, int32_t shape) {
         }
     }
     while ((PERSIST_GROUPS << p.lw) < shape) p.lw += 1;
-    if ((1 << p.lw) > PERSIST_W) return p;
+    if ((1 << p.lw) > PERSIST_W || x->ps_q32 > COLUMN_QUADS[p.lw]) return p;
     p.members = PERSIST_MEMBERS;
     const int32_t rx = std::min(n, persist_rows(n, p.members)), ry = std::min(m, persist_rows(m, p.members));
     p.lds = persist_lds(rx, ry, x->ps_q32, (int64_t)1 << p.lw, esz);

@@ -98,6 +98,23 @@ def test_grouped_structured(P, make, B):
     _same(inst, D, 1e-4, 500, scaling=1, dual_tol=1e-8)
 
 
+@pytest.mark.parametrize("m, n, B, grouped", [
+    (3200, 6500, 2, True), (3200, 6500, 12, True),      # row segments of one and two columns
+    (6000, 10000, 2, False), (6000, 10000, 8, False),   # they fit, but the step launches are faster
+    (6000, 10000, 12, True),                            # chunks of two columns are worth it again
+])
+def test_grouped_where_faster(P, m, n, B, grouped):
+    """Grouped launches where they beat the step launches (only they take work vectors)."""
+    inst = make_cfg2(m=m, n=n)
+    D = obbt_deltas(choose_vars(n, B // 2, seed=B))
+    with make_ctx(inst, eval_every=32) as ctx:
+        ctx.set_batch(D)
+        before = ctx.device_bytes
+        ctx.solve(tol=0.0, max_iters=33)
+        assert (ctx.device_bytes > before) == grouped
+    _same(inst, D, 1e-4, 100, eval_every=32)
+
+
 class _NanAllocator:
     """Device memory of a caller's allocator, every word a NaN (FP64 and FP32)."""
 
