@@ -3979,9 +3979,6 @@ hipError_t launch_rows(const StepArgs<T>& a, int lanes, int vec, hipStream_t s) 
     if (lanes == 8 && vec == 1) return launch_rows_gv<T, 8, 1, PRIMAL>(a, s);
     if (lanes == 8 && vec == 2) return launch_rows_gv<T, 8, 2, PRIMAL>(a, s);
     if (lanes == 8 && vec == V) return launch_rows_gv<T, 8, V, PRIMAL>(a, s);
-    if (lanes == 4 * V && vec == 2) return launch_rows_gv<T, 4 * V, 2, PRIMAL>(a, s);
-    if (lanes == 8 * V && vec == 1) return launch_rows_gv<T, 8 * V, 1, PRIMAL>(a, s);
-    if (lanes == 16 && vec == 1) return launch_rows_gv<T, 16, 1, PRIMAL>(a, s);
     return hipErrorInvalidValue;
 }
 

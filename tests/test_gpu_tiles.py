@@ -88,6 +88,29 @@ def test_row_kernel(P, make, B, prec):
 
 
 @pytest.mark.parametrize("prec", ["fp64", "fp32"])
+@pytest.mark.parametrize("B", [7, 9, 15, 17, 19, 29, 31, 33])
+def test_row_kernel_odd_widths(P, B, prec):
+    """Odd batches on the row kernel, the row stride padded to what a lane loads (blocks
+    of that size, beside two result blocks a side): the bits of the kernels of any
+    launch shape."""
+    inst = make_cfg2(m=4001, n=12001)
+    D = _deltas(inst.n, B)
+    kw = dict(precision=P.MIXED32 if prec == "fp32" else P.FP64, eval_every=32)
+    pad = 1 if B < 9 else 4 if prec == "fp32" and B > 16 else 2
+    out, held = [], []
+    for shape in ({}, dict(tile_lanes=8, tile_vec=1)):
+        with make_ctx(inst, **kw, **shape) as ctx:
+            ctx.set_kernel_timing(True)
+            before = ctx.device_bytes
+            out.append(_solve(ctx, D, 70))
+            held.append(ctx.device_bytes - before)
+    for key in out[0]:
+        assert np.array_equal(out[0][key], out[1][key], equal_nan=True), key
+    ld = -(-B // pad) * pad
+    assert held[0] >= (4 * ld + 2 * B) * (inst.m + inst.n) * (4 if prec == "fp32" else 8)
+
+
+@pytest.mark.parametrize("prec", ["fp64", "fp32"])
 @pytest.mark.parametrize("m, n", [(63, 143), (64, 129), (1000, 2500), (33000, 66000)])
 def test_row_evaluations(P, m, n, prec):
     """Evaluations with a lane per row (4 and 8 rows per chain, groups that end inside
