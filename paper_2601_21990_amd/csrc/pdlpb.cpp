@@ -453,6 +453,20 @@ bool lane_rows_serve(const pdlpb_ctx* x, bool primal, int32_t w, int lanes) {
     return w <= 4 && rows >= LANE_ROWS * w && (lanes > 1 || x->nnz <= LANE_MEAN * rows);
 }
 
+// Small launches last as long as their chain of dependent loads, which is one load
+// shorter in k_primal / k_dual (the ELL head has a row's indices at a known place) than
+// in the row kernel (row pointers, then entries): those serve, a column per lane, while
+// nonzeros times groups of 32 columns stay below these bounds.  us per iteration,
+// k_primal / k_dual against the row kernel: FP32, 32 LPs 1000 x 2500, 6 entries per
+// column 10.1 / 11.1, 2000 x 5000, 8 11.8 / 12.0, 5000 x 12500, 5 14.4 / 13.9, 64 LPs
+// 1000 x 2500 10.7 / 11.5;  FP64, 32 LPs 200 x 500, 5 8.5 / 9.2, 600 x 1500, 6 9.6 / 9.8,
+// 1000 x 2500 10.7 / 10.0, 64 LPs 300 x 700, 6 9.2 / 9.2;  16 LPs 200 x 500 8.2 / 8.9,
+// 1000 x 2500 9.6 / 9.4;  8 LPs 50 x 100, 3 6.7 / 7.1.
+bool small_launch(const pdlpb_ctx* x, int32_t ncols) {
+    const int64_t most = ncols > 16 ? (x->fp32 ? 50000 : 10000) : ncols > 8 ? 10000 : x->fp32 ? 1000 : 2500;
+    return x->nnz * ((ncols + 31) / 32) <= most;
+}
+
 // default tile for `ncols` live columns: a row group covers the W = lanes * vec
 // slots of one storage tile (128 bytes of a row; fewer when the batch is
 // narrower), 16 bytes per lane once the batch is that wide; vec never exceeds
@@ -470,7 +484,8 @@ Tile heuristic_tile(const pdlpb_ctx* x, int32_t ncols, bool primal) {
     }
     const int32_t tile = x->fp32 ? block_tile<float>() : block_tile<double>();
     const int32_t w = std::min<int32_t>(tile, next_pow2(ncols > 0 ? ncols : 1));
-    if (rows_kernel_serves(x, primal)) {
+    const bool rows = rows_kernel_serves(x, primal), small = rows && small_launch(x, ncols);
+    if (rows && !small) {
         // 16 bytes per lane where the width allows it (ld_for pads for that), 8 lanes at
         // least unless a lane takes a row
         Tile t;
@@ -485,13 +500,14 @@ Tile heuristic_tile(const pdlpb_ctx* x, int32_t ncols, bool primal) {
         t.blocks = DEFAULT_MAX_BLOCKS;
         return t;
     }
-    int vec = w >= tile ? (x->fp32 ? 4 : 2) : 1;
+    int vec = w >= tile && !small ? (x->fp32 ? 4 : 2) : 1;
     if (x->opt.tile_vec > 0) vec = x->opt.tile_vec;
     if (vec > x->vec_ld) vec = x->vec_ld;
     // at least 8 lanes per row group: a narrow batch (few live LPs) still spreads
     // its rows over many waves (the idle lanes return at once), which is what
     // keeps the latency-bound iterations of a shrinking batch short
     int lanes = std::max(8, (int)(w / vec));
+    if (small && ncols > w && ncols <= 32) lanes = 32;   // both tiles of an FP64 row
     if (lanes > 64) lanes = 64;
     if (x->opt.tile_lanes > 0) lanes = x->opt.tile_lanes;
     Tile t;

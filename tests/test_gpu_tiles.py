@@ -111,6 +111,22 @@ def test_row_kernel_odd_widths(P, B, prec):
 
 
 @pytest.mark.parametrize("prec", ["fp64", "fp32"])
+@pytest.mark.parametrize("make, B", [
+    (lambda: make_cfg2(m=20000, n=12001), 3),           # empty rows
+    (lambda: make_cfg2(m=20000, n=12001), 16),
+    (lambda: make_cfg2(m=20000, n=12001), 32),
+    (lambda: make_facility(F=16, C=4000, k=4), 33),     # columns and rows of 1000 entries among short ones
+    (lambda: make_cfg2(m=4001, n=9999), 17),            # either side of the bound on small launches (FP32)
+    (lambda: make_cfg2(m=4001, n=10001), 17),
+    (lambda: make_cfg2(m=801, n=1999), 13),             # ... (FP64)
+    (lambda: make_cfg2(m=801, n=2001), 13),
+], ids=["empty3", "empty16", "empty32", "spill", "9999", "10001", "1999", "2001"])
+def test_row_kernel_not_small(P, make, B, prec):
+    """The row kernel where launches are not small, and at the line."""
+    test_row_kernel(P, make, B, prec)
+
+
+@pytest.mark.parametrize("prec", ["fp64", "fp32"])
 @pytest.mark.parametrize("m, n", [(63, 143), (64, 129), (1000, 2500), (33000, 66000)])
 def test_row_evaluations(P, m, n, prec):
     """Evaluations with a lane per row (4 and 8 rows per chain, groups that end inside
