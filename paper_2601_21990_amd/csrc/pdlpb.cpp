@@ -837,6 +837,12 @@ PersistPlan persist_plan(const pdlpb_ctx* x, int32_t shape) {
 
 // Work vectors and panel sums of the chunks for `shape` columns (grouped only).
 int ensure_bytes(pdlpb_ctx* x, void** p, size_t* cap, size_t bytes);
+void free_persist(pdlpb_ctx* x) {
+    if (x->ps_work || x->ps_sum) x->drop_graph();
+    x->release(x->ps_work, 0);
+    x->release(x->ps_sum, 0);
+    x->cap_ps_work = x->cap_ps_sum = 0;
+}
 int ensure_persist(pdlpb_ctx* x, int32_t shape) {
     const PersistPlan p = persist_plan(x, shape);
     if (p.mode != PERSIST_STAGED && p.mode != PERSIST_COLUMNS) return PDLPB_OK;
@@ -847,6 +853,7 @@ int ensure_persist(pdlpb_ctx* x, int32_t shape) {
     if (work > x->cap_ps_work || sum > x->cap_ps_sum) x->drop_graph();
     int rc = ensure_bytes(x, &x->ps_work, &x->cap_ps_work, work);
     if (!rc) rc = ensure_bytes(x, reinterpret_cast<void**>(&x->ps_sum), &x->cap_ps_sum, sum);
+    if (rc) free_persist(x);
     return rc;
 }
 
@@ -1386,6 +1393,7 @@ int run_solve(pdlpb_ctx* x, double tol, int32_t max_iters) {
     int in_slot = 0, next_slot = 0;
     int64_t launched = 0;
     int32_t step_blocks = 0;  // blocks to run on step launches before the next grouped one
+    bool scratch = true;      // false: no memory for grouped launches; step launches to the end
     // no block outlives the call: other entry points write device state with
     // copies that do not wait for the context's (non-blocking) stream
     struct Drain {
@@ -1448,11 +1456,16 @@ int run_solve(pdlpb_ctx* x, double tol, int32_t max_iters) {
                 tune_now = !hit && !x->timing && !(x->tp.rows && x->td.rows);
             }
         }
-        const bool persist = step_blocks == 0 && persist_plan(x, x->live).mode != PERSIST_NONE;
+        const bool persist = scratch && step_blocks == 0 && persist_plan(x, x->live).mode != PERSIST_NONE;
         if (persist && !in_flight) {
             const int32_t blocks = std::max(1, PERSIST_ITERS / x->opt.eval_every);
             const int32_t t0 = x->seen_t0;
             rc = ensure_persist(x, x->live);
+            if (rc == PDLPB_ENOMEM) {
+                (void)hipGetLastError();   // not the next launch's
+                scratch = false;
+                continue;
+            }
             if (rc) return rc;
             {
                 GroupTurn turn(x);

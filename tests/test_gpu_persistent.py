@@ -116,13 +116,17 @@ def test_grouped_where_faster(P, m, n, B, grouped):
 
 
 class _NanAllocator:
-    """Device memory of a caller's allocator, every word a NaN (FP64 and FP32)."""
+    """Device memory of a caller's allocator, every word a NaN (FP64 and FP32); none
+    while `full` is set."""
 
     def __init__(self, P):
         import torch
         self.live = {}
+        self.full = False
 
         def alloc(nbytes, _user):
+            if self.full:
+                return None
             t = torch.full((int(nbytes),), 255, dtype=torch.uint8, device="cuda:0")
             torch.cuda.synchronize()
             self.live[t.data_ptr()] = t
@@ -168,6 +172,28 @@ def test_short_groups(P, m, n, B, sizes, prec):
             for x, y in zip(rt, gt):
                 assert np.array_equal(x["x_iter"], y["x_iter"]) and np.array_equal(x["y_iter"], y["y_iter"])
                 assert x["w"] == y["w"] and x["restart_log"] == y["restart_log"]
+
+
+@pytest.mark.parametrize("B", [1, 40])
+def test_no_memory_for_grouped(P, B):
+    """A device with no memory left for the work vectors: the solve runs on step
+    launches, and on grouped ones once there is memory again."""
+    inst = make_cfg2(m=2000, n=5000)
+    D = obbt_deltas(choose_vars(inst.n, (B + 1) // 2, seed=B))[:B]
+    alloc = _NanAllocator(P)
+    with make_ctx(inst, eval_every=32, allocator=alloc) as ctx:
+        ref, _ = _solve(ctx, D, 1e-4, 200, True)
+        before = ctx.device_bytes
+        ctx.set_kernel_timing(False)
+        for full in (True, False):
+            alloc.full = full
+            ctx.set_batch(D)
+            ctx.solve(tol=1e-4, max_iters=200)
+            alloc.full = False
+            got = ctx.get_batch()
+            assert (ctx.device_bytes > before) != full
+            for key in got:
+                assert np.array_equal(ref[key], got[key], equal_nan=True), (full, key)
 
 
 def test_two_contexts_at_once(P):
