@@ -482,7 +482,8 @@ int pdlpb_kernel_columns(pdlpb_ctx* ctx, int64_t cols[5]);
  * and 80 (n + m) K bytes of evaluation terms; pdlpb_serve_begin releases
  * both.  One whose small matrix pdlpb_solve iterates with the workgroups of
  * an XCD per chunk of columns keeps 3 (n + 4) + 4 (m + 4) elements and
- * 0.65 (n + m) + 24 doubles per column of its widest such batch (at most 128). */
+ * 0.65 (n + m) + 384 doubles at most per column of its widest such batch (at most 128);
+ * pdlpb_serve_begin releases those too. */
 int64_t pdlpb_device_bytes(const pdlpb_ctx* ctx);
 
 /* Number of blocks of C iterations (small matrices: launches of several

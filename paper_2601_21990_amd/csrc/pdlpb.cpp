@@ -2745,11 +2745,12 @@ int pdlpb_serve_begin(pdlpb_ctx* x, int32_t result_capacity) {
         return x->fail(PDLPB_EINVAL, "result_capacity out of range");
     HIP_TRY(x, hipSetDevice(x->device));
     HIP_TRY(x, hipStreamSynchronize(x->stream));
-    // a session holds only what its LPs need: no narrow copies or shared-start
-    // buffers of a batch
+    // a session holds only what its LPs need: no narrow copies, shared-start buffers
+    // or work vectors of grouped launches of a batch
     x->drop_graph();
     free_narrow(x);
     free_shared_start(x);
+    free_persist(x);
     // storage starts at one column and one result row and grows with the LPs
     // submitted (pdlpb_serve_footprint, pdlpb_serve_trim)
     x->n_cols = 0;

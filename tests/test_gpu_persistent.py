@@ -196,6 +196,21 @@ def test_no_memory_for_grouped(P, B):
                 assert np.array_equal(ref[key], got[key], equal_nan=True), (full, key)
 
 
+def test_serving_releases_the_work_vectors(P):
+    """A serving session holds none of a batch's grouped launches, whose scratch its own
+    launches cannot use; a later batch gets them again."""
+    inst = make_cfg2(m=2000, n=5000)
+    D = obbt_deltas(choose_vars(inst.n, 20, seed=1))
+    with make_ctx(inst, eval_every=32) as ctx, make_ctx(inst, eval_every=32) as fresh:
+        a, _ = _solve(ctx, D, 1e-4, 100, False)
+        for c in (ctx, fresh):
+            c.serve_begin(64)
+        assert ctx.device_bytes == fresh.device_bytes
+        b, _ = _solve(ctx, D, 1e-4, 100, False)
+    for key in a:
+        assert np.array_equal(a[key], b[key], equal_nan=True), key
+
+
 def test_two_contexts_at_once(P):
     """Two threads solve on grouped launches of one device: each gets its results."""
     import threading
