@@ -788,7 +788,7 @@ static_assert(1 << (sizeof(COLUMN_QUADS) / sizeof(COLUMN_QUADS[0]) - 1) == PERSI
 PersistPlan persist_plan(const pdlpb_ctx* x, int32_t shape) {
     PersistPlan p;
     if (x->m < 1 || x->nnz < 1 || x->opt.restart_scope != PDLPB_RESTART_PER_LP || x->timing ||
-        x->opt.tile_lanes > 0 || x->opt.tile_vec > 0 || shape < 1 || x->pw_x != 4 || x->pw_y != 4)
+        x->opt.tile_lanes > 0 || x->opt.tile_vec > 0 || x->opt.max_blocks > 0 || shape < 1 || x->pw_x != 4 || x->pw_y != 4)
         return p;
     const int32_t n = x->n, m = x->m;
     const int64_t esz = x->fp32 ? sizeof(float) : sizeof(double);

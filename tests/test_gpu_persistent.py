@@ -196,6 +196,23 @@ def test_no_memory_for_grouped(P, B):
                 assert np.array_equal(ref[key], got[key], equal_nan=True), (full, key)
 
 
+def test_workgroup_cap(P):
+    """A cap on the workgroups of a launch (max_blocks) holds for small matrices too:
+    step launches, with the same bits."""
+    inst = make_cfg2(m=2000, n=5000)
+    D = obbt_deltas(choose_vars(inst.n, 20, seed=1))
+    out = []
+    for cap in (0, 16):
+        with make_ctx(inst, eval_every=32, max_blocks=cap) as ctx:
+            ctx.set_batch(D)
+            before = ctx.device_bytes
+            ctx.solve(tol=1e-4, max_iters=100)
+            assert (ctx.device_bytes > before) == (cap == 0)
+            out.append(ctx.get_batch())
+    for key in out[0]:
+        assert np.array_equal(out[0][key], out[1][key], equal_nan=True), key
+
+
 def test_serving_releases_the_work_vectors(P):
     """A serving session holds none of a batch's grouped launches, whose scratch its own
     launches cannot use; a later batch gets them again."""
