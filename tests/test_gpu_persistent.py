@@ -196,6 +196,38 @@ def test_no_memory_for_grouped(P, B):
                 assert np.array_equal(ref[key], got[key], equal_nan=True), (full, key)
 
 
+@pytest.mark.parametrize("prec", ["fp64", "fp32"])
+@pytest.mark.parametrize("m, n, B", [
+    (150, 400, 5),                                      # solo
+    (1500, 3701, 3), (1500, 3701, 20),                  # staged; row segments
+    (4001, 12001, 20),                                  # the row kernel
+])
+def test_not_finite(P, m, n, B, prec):
+    """Iterates that overflow within a block of iterations (a step size far too large,
+    some free variables among boxed ones): pads and empty slots of the persistent
+    blocks and the row kernel add nothing to a sum that gathers infinities or NaN."""
+    inst = make_cfg2(m=m, n=n)
+    inst.l[::40], inst.u[::40] = -np.inf, np.inf
+    D = obbt_deltas(choose_vars(n, (B + 1) // 2, seed=B))[:B]
+    kw = dict(precision=P.MIXED32 if prec == "fp32" else P.FP64, eval_every=64,
+              step_size=1e8 if prec == "fp64" else 1e3)
+    budgets = (3, 4, 5, 6, 7, 8, 9, 10, 12, 16, 18, 19, 20, 21, 22, 24, 40)
+    out = []
+    for timing, shape in ((True, dict(tile_lanes=8, tile_vec=1)), (True, {}), (False, {})):
+        with make_ctx(inst, **kw, **shape) as ctx:
+            out.append([_solve(ctx, D, 1e-9, K, timing) for K in budgets])
+    # some of the budgets end while part of the coordinates is finite
+    bad = [np.mean(~np.isfinite(ref["X"])) for ref, _ in out[0]]
+    assert bad[0] == 0.0 and bad[-1] > 0.0 and any(0.0 < b < 1.0 for b in bad), bad
+    for run in out[1:]:
+        for K, (ref, rt), (got, gt) in zip(budgets, out[0], run):
+            for key in ref:
+                assert np.array_equal(ref[key], got[key], equal_nan=True), (K, key)
+            for x, y in zip(rt, gt):
+                assert np.array_equal(x["x_iter"], y["x_iter"], equal_nan=True), K
+                assert np.array_equal(x["y_iter"], y["y_iter"], equal_nan=True), K
+
+
 def test_workgroup_cap(P):
     """A cap on the workgroups of a launch (max_blocks) holds for small matrices too:
     step launches, with the same bits."""
@@ -226,6 +258,39 @@ def test_serving_releases_the_work_vectors(P):
         b, _ = _solve(ctx, D, 1e-4, 100, False)
     for key in a:
         assert np.array_equal(a[key], b[key], equal_nan=True), key
+
+
+def test_beside_other_work(P):
+    """Grouped solves while another thread's context holds compute units with solo
+    blocks and step launches: groups may close short, results do not change."""
+    import threading
+    inst, other = make_cfg2(m=1500, n=3701), make_cfg2(m=200, n=500)
+    D, E = obbt_deltas(choose_vars(3701, 20, seed=1)), obbt_deltas(choose_vars(500, 150, seed=2))
+    stop, errors = threading.Event(), []
+    with make_ctx(inst, eval_every=32) as ctx, make_ctx(other, eval_every=32) as busy:
+        ref, _ = _solve(ctx, D, 1e-4, 400, True)
+        want, _ = _solve(busy, E, 0.0, 900, True)
+
+        def work():
+            try:
+                while not stop.is_set():
+                    for timing in (False, True):
+                        got, _ = _solve(busy, E, 0.0, 900, timing)
+                        assert all(np.array_equal(want[k], got[k], equal_nan=True) for k in want)
+            except Exception as e:      # noqa: BLE001 (reported by the main thread)
+                errors.append(e)
+
+        th = threading.Thread(target=work)
+        th.start()
+        try:
+            for _ in range(10):
+                got, _ = _solve(ctx, D, 1e-4, 400, False)
+                for key in ref:
+                    assert np.array_equal(ref[key], got[key], equal_nan=True), key
+        finally:
+            stop.set()
+            th.join()
+    assert not errors, errors
 
 
 def test_two_contexts_at_once(P):
