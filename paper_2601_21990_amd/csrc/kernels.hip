@@ -1222,8 +1222,8 @@ __global__ __launch_bounds__(256) void k_eval_narrow(EvalArgs<T> a) {
     }
 }
 
-// The same for small panels (4 pw <= 64 rows, both sides of a matrix up to 131072
-// rows), where a wave of k_eval_narrow has pw rows for its 64 lanes.  A wave owns 64
+// The same for small panels (4 pw <= 64 rows), where a wave of k_eval_narrow has pw
+// rows for its 64 lanes.  A wave owns 64
 // consecutive rows, 64 / (4 pw) whole panels, of one slot, a lane per row; the
 // chains, four per panel, then add their rows' terms in order, every lane another
 // (chain, term), and the panels add their four chains.  Bound by the chain of
@@ -4011,18 +4011,25 @@ hipError_t launch_dual(const StepArgs<T>& a, int lanes, int vec, hipStream_t s) 
 // absent ones idle.  From 9 columns on k_eval_rows serves while rows times columns
 // stay below 2^18, or where only some LPs are evaluated (the others' waves leave at
 // once).  All LPs, FP64, k_eval_rows / k_eval: 12011 x 30011, 8 LPs 33 / 47 us,
-// 16 LPs 54 / 47; 5000 x 12000, 16 LPs 28 / 28; 1000 x 2500, 16 LPs 14 / 19.  Larger
-// panels (k_eval_narrow): strong branching of 512 LPs at 200k x 500k takes 29.5 ms
-// with it up to 16 columns, 30.0 up to 8.
+// 16 LPs 54 / 47; 5000 x 12000, 16 LPs 28 / 28; 1000 x 2500, 16 LPs 14 / 19.
+// k_eval_rows serves panels of up to 32 rows (both sides up to 65536 rows).  A wave of
+// k_eval_narrow has 16 rows of a 64-row panel, and k_eval_rows is faster there only
+// where four columns fill its workgroups.  All LPs, FP64 and FP32, k_eval_rows /
+// k_eval_narrow: 32000 x 64000, 4 entries per column, 1 LP 13.4 / 17.3 and 12.7 / 12.8 us,
+// 5 LPs 44 / 63 and 35 / 43; 64000 x 128000 1 LP 20.5 / 19.9 and 19.7 / 15.7, 4 LPs
+// 45 / 61 and 42 / 46, 5 LPs 90 / 76 and 77 / 57, 8 LPs 80 / 117 and 79 / 86.  Larger
+// panels: strong branching of 512 LPs at 200k x 500k takes 29.5 ms with k_eval_narrow up
+// to 16 columns, 30.0 up to 8.
 constexpr int32_t EVAL_NARROW_COLS = 16;
 
 template <typename T>
 hipError_t launch_eval(const EvalArgs<T>& a, hipStream_t s) {
-    const bool small = a.pw_x <= 16 && a.pw_y <= 16;
+    const int32_t pw = max(a.pw_x, a.pw_y);
+    const bool small = pw <= 16, rows = pw <= 8 || (small && a.full && a.ncols % 4 == 0);
     const bool narrow = a.ncols <= EVAL_NARROW_COLS / 2 ||
                         (a.ncols <= EVAL_NARROW_COLS &&
                          (!small || !a.full || ((int64_t)a.n + a.m) * a.ncols <= (1 << 18)));
-    if (narrow && small) {
+    if (narrow && rows) {
         const int64_t groups = (((int64_t)a.n + 63) / 64 + ((int64_t)a.m + 63) / 64 + 7) / 8 * 8 * ((a.ncols + 3) / 4);
         if (groups <= 0) return hipSuccess;
         if (a.kkt_only) hipLaunchKernelGGL((k_eval_rows<T, true>), dim3((uint32_t)groups), dim3(256), 0, s, a);

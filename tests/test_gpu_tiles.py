@@ -140,3 +140,19 @@ def test_row_evaluations(P, m, n, prec):
             part = _solve(ctx, D[i:j], 33)
             for key in whole:
                 assert np.array_equal(whole[key][i:j], part[key], equal_nan=True), (key, i)
+
+
+@pytest.mark.parametrize("prec", ["fp64", "fp32"])
+@pytest.mark.parametrize("m, n", [(33000, 66000), (66000, 33000), (65536, 65536)])
+def test_evaluations_of_large_panels(P, m, n, prec):
+    """Panels of 64 and 32 rows at widths that fill the row kernel's workgroups (four
+    columns) and that leave it to the panel kernel, with stopping tests in between."""
+    inst = make_cfg2(m=m, n=n)
+    D = _deltas(inst.n, 40)
+    with make_ctx(inst, precision=P.MIXED32 if prec == "fp32" else P.FP64, eval_every=8, stop_every=4) as ctx:
+        ctx.set_kernel_timing(True)
+        whole = _solve(ctx, D, 33)
+        for i, j in ((0, 3), (3, 7), (7, 15), (15, 28)):
+            part = _solve(ctx, D[i:j], 33)
+            for key in whole:
+                assert np.array_equal(whole[key][i:j], part[key], equal_nan=True), (key, i)
