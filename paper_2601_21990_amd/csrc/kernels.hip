@@ -1094,11 +1094,16 @@ __global__ __launch_bounds__(256) void k_eval(EvalArgs<T> a) {
     }
 }
 
-// Terms of row i of one side for slot s.  N nonzeros at a time: their indices, then
-// their gathers, are in flight together, without a branch (past the row's end the
-// last one again, whose products are dropped); the sums add them in CSR order.
-template <typename T, bool KKT, int N>
-__device__ __forceinline__ void eval_row(const EvalArgs<T>& a, bool xside, int32_t i, int32_t s, int32_t varkind,
+// Terms of row i of one side for slot s (xside: a bool, or its constant where a kernel
+// has code of its own for each side).  N nonzeros at a time: their indices, then their
+// gathers, are in flight together; the sums add them in CSR order.  Past the row's end
+// PAD loads the last entry again, whose products are dropped, instead of branching
+// around the load, which costs gathers where rows are shorter than N.  Without PAD, and
+// with code for each side, k_eval_narrow keeps its registers (FP32 58, 94 otherwise) and
+// its waves per SIMD: 131000 x 60000, 4 entries per column, 5 LPs in FP32 38 us, 46 with
+// the code of k_eval_rows; 64000 x 128000 58 and 66.
+template <typename T, bool KKT, int N, bool PAD, typename Side>
+__device__ __forceinline__ void eval_row(const EvalArgs<T>& a, Side xside, int32_t i, int32_t s, int32_t varkind,
                                          double* tq) {
     const int32_t* const ci = xside ? a.t_ci : a.a_ci;
     const T* const av = xside ? a.t_v : a.a_v;
@@ -1119,30 +1124,38 @@ __device__ __forceinline__ void eval_row(const EvalArgs<T>& a, bool xside, int32
         T vv[N], zv[N], dv[N];
 #pragma unroll
         for (int u = 0; u < N; ++u) {
-            const int32_t k = min(k0 + u, ke - 1);
-            jj[u] = ci[k];
-            vv[u] = av[k];
+            jj[u] = 0;
+            vv[u] = T(0);
+            if (PAD || k0 + u < ke) {
+                const int32_t k = PAD ? min(k0 + u, ke - 1) : k0 + u;
+                jj[u] = ci[k];
+                vv[u] = av[k];
+            }
         }
 #pragma unroll
         for (int u = 0; u < N; ++u) {
-            const size_t f = (size_t)jj[u] * gs;
-            zv[u] = zt[f];
-            if constexpr (!KKT) {
-                dv[u] = dz[f];
-                cd[u] = xside ? a.rcode[jj[u]] : 0;
+            if (PAD || k0 + u < ke) {
+                const size_t f = (size_t)jj[u] * gs;
+                zv[u] = zt[f];
+                if constexpr (!KKT) {
+                    dv[u] = dz[f];
+                    cd[u] = xside ? a.rcode[jj[u]] : 0;
+                }
             }
         }
 #pragma unroll
         for (int u = 0; u < N; ++u) {
             const bool in = k0 + u < ke;
-            const double w = (double)vv[u];
-            const double g1 = fma(w, (double)zv[u], g);
-            g = in ? g1 : g;
-            if constexpr (!KKT) {
-                const double d = (double)dv[u];
-                const double h1 = fma(w, d, h), p1 = fma(w, barrier_code(d, cd[u]), pdy);
-                h = in ? h1 : h;
-                pdy = in ? p1 : pdy;
+            if (PAD || in) {
+                const double w = (double)vv[u];
+                const double g1 = fma(w, (double)zv[u], g);
+                g = in ? g1 : g;
+                if constexpr (!KKT) {
+                    const double d = (double)dv[u];
+                    const double h1 = fma(w, d, h), p1 = fma(w, barrier_code(d, cd[u]), pdy);
+                    h = in ? h1 : h;
+                    pdy = in ? p1 : pdy;
+                }
             }
         }
     }
@@ -1202,7 +1215,8 @@ __global__ __launch_bounds__(256) void k_eval_narrow(EvalArgs<T> a) {
         const int32_t i = rb + lane;
         if (i < r1) {
             double tq[NTERM];
-            eval_row<T, KKT, NCH>(a, xside, i, s, varkind, tq);
+            if (xside) eval_row<T, KKT, NCH, false>(a, std::true_type{}, i, s, varkind, tq);
+            else eval_row<T, KKT, NCH, false>(a, std::false_type{}, i, s, varkind, tq);
 #pragma unroll
             for (int q = 0; q < NTERM; ++q) terms[wave][lane][q] = tq[q];
         }
@@ -1256,7 +1270,7 @@ __global__ __launch_bounds__(256) void k_eval_rows(EvalArgs<T> a) {
     const int32_t cnt = min(64, rows - r0);
     if (lane < cnt) {
         double tq[NTERM];
-        eval_row<T, KKT, EVAL_RCH>(a, xside, r0 + lane, s, key.varkind, tq);
+        eval_row<T, KKT, EVAL_RCH, true>(a, xside, r0 + lane, s, key.varkind, tq);
 #pragma unroll
         for (int q = 0; q < NTERM; ++q) terms[lane][q] = tq[q];
     }
