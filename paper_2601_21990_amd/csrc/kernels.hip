@@ -4026,6 +4026,11 @@ hipError_t launch_dual(const StepArgs<T>& a, int lanes, int vec, hipStream_t s) 
 // stay below 2^18, or where only some LPs are evaluated (the others' waves leave at
 // once).  All LPs, FP64, k_eval_rows / k_eval: 12011 x 30011, 8 LPs 33 / 47 us,
 // 16 LPs 54 / 47; 5000 x 12000, 16 LPs 28 / 28; 1000 x 2500, 16 LPs 14 / 19.
+// Launches of few rows and columns last as long as a wave: k_eval_narrow's panel then
+// takes 64 / pw times the waves and each a shorter chain.  200 x 500, 8 LPs, FP64 and
+// FP32, k_eval_rows / k_eval_narrow: 9.7 / 7.5 and 9.4 / 7.0 us; 1000 x 2500, 4 LPs
+// 11.5 / 9.1 and 10.8 / 7.9, 8 LPs 11.9 / 12.2 and 11.3 / 9.8; 2000 x 5000, 4 LPs
+// 12.9 / 13.0 and 11.9 / 10.1, 8 LPs 12.3 / 20 and 12 / 13.9.
 // k_eval_rows serves panels of up to 32 rows (both sides up to 65536 rows).  A wave of
 // k_eval_narrow has 16 rows of a 64-row panel, and k_eval_rows is faster there only
 // where four columns fill its workgroups.  All LPs, FP64 and FP32, k_eval_rows /
@@ -4039,10 +4044,13 @@ constexpr int32_t EVAL_NARROW_COLS = 16;
 template <typename T>
 hipError_t launch_eval(const EvalArgs<T>& a, hipStream_t s) {
     const int32_t pw = max(a.pw_x, a.pw_y);
-    const bool small = pw <= 16, rows = pw <= 8 || (small && a.full && a.ncols % 4 == 0);
+    const int64_t work = ((int64_t)a.n + a.m) * a.ncols;
+    const bool few = sizeof(T) == 4 ? work <= 30000 && (a.ncols > 2 || a.n + a.m <= 5000)
+                                    : work <= 20000 && a.ncols > 2;
+    const bool small = pw <= 16, rows = !few && (pw <= 8 || (small && a.full && a.ncols % 4 == 0));
     const bool narrow = a.ncols <= EVAL_NARROW_COLS / 2 ||
                         (a.ncols <= EVAL_NARROW_COLS &&
-                         (!small || !a.full || ((int64_t)a.n + a.m) * a.ncols <= (1 << 18)));
+                         (!small || !a.full || work <= (1 << 18)));
     if (narrow && rows) {
         const int64_t groups = (((int64_t)a.n + 63) / 64 + ((int64_t)a.m + 63) / 64 + 7) / 8 * 8 * ((a.ncols + 3) / 4);
         if (groups <= 0) return hipSuccess;

@@ -156,3 +156,19 @@ def test_evaluations_of_large_panels(P, m, n, prec):
             part = _solve(ctx, D[i:j], 33)
             for key in whole:
                 assert np.array_equal(whole[key][i:j], part[key], equal_nan=True), (key, i)
+
+
+@pytest.mark.parametrize("prec", ["fp64", "fp32"])
+@pytest.mark.parametrize("m, n", [(63, 143), (600, 1399), (601, 1400), (1000, 2500), (1500, 3500), (1501, 3501)])
+def test_evaluations_of_few_rows(P, m, n, prec):
+    """Either side of the line between the panel kernel and the row kernel: one to 16
+    columns, with stopping tests in between."""
+    inst = make_cfg2(m=m, n=n)
+    D = _deltas(inst.n, 40)
+    with make_ctx(inst, precision=P.MIXED32 if prec == "fp32" else P.FP64, eval_every=8, stop_every=2) as ctx:
+        ctx.set_kernel_timing(True)
+        whole = _solve(ctx, D, 33)
+        for i, j in ((0, 1), (1, 3), (3, 7), (7, 12), (12, 22), (22, 38)):
+            part = _solve(ctx, D[i:j], 33)
+            for key in whole:
+                assert np.array_equal(whole[key][i:j], part[key], equal_nan=True), (key, i)
