@@ -767,28 +767,36 @@ struct PersistPlan {
 // fits, else row segments of up to 16 columns.  Where nothing fits the step launches
 // are used: they stream the matrix from the caches of the whole chip.
 //
-// A chunk of W columns gathers a line per entry (padded to quads) and half of an
-// iteration with the 32 CUs of one XCD, whatever W, where a step launch gathers with
-// 256 CUs; so narrow chunks of larger matrices are slower than step launches although
-// they fit.  COLUMN_QUADS bounds the quads of a member at W = 1, 2, 4 (at 8 and 16 the
-// LDS does, as at 4).  us per iteration, chunks / step launches, FP64 and FP32, at
-// (quads of a member):
-//   W = 1:  4000 x 10000, 4 entries per column (713), 1 LP 6.5 / 9.1 and 6.1 / 8.5,
-//           8 LPs 7.4 / 9.7 and 7.2 / 8.7;  5000 x 12500, 4 (879), 2 LPs 7.7 / 9.0 and
-//           8.1 / 8.3;  8000 x 16000, 3 (1024), 2 LPs 8.8 / 8.7 and 8.6 / 8.1;
-//           10000 x 20000, 4 (1436), 2 LPs 9.6 / 9.3 and 10.2 / 8.2
-//   W = 2:  4000 x 10000, 8 (1364), 16 LPs 11.0 / 12.9 and 10.7 / 11.3;  10000 x 22000, 4
-//           (1531), 16 LPs, FP32 11.6 / 13.2;  6000 x 12500, 8 (1699), 16 LPs 13.2 / 13.6
-//           and 12.7 / 12.2
-//   W = 4:  6000 x 12500, 8 (1699), 32 LPs, FP32 13.0 / 14.7
-// Solo needs no such rule: 200 x 500, 1 / 256 / 1000 / 4096 LPs 1.8 / 2.4 / 8.5 / 33 us
-// against 8.2 / 9.4 / 16 / 45 on step launches.
-constexpr int64_t COLUMN_QUADS[] = {900, 1600, 2300, 2300, 2300};
-static_assert(1 << (sizeof(COLUMN_QUADS) / sizeof(COLUMN_QUADS[0]) - 1) == PERSIST_W, "chunk widths");
+// Solo needs no other rule: 200 x 500, 1 / 256 / 1000 / 4096 LPs 1.8 / 2.4 / 8.5 / 33 us
+// per iteration against 8.2 / 9.4 / 16 / 45 on step launches.
+
+// Whether chunks of 1 << lw columns are faster than step launches.  A chunk gathers a
+// line per entry (padded to quads) in half an iteration with the 32 CUs of one XCD,
+// whatever its width, and its members update their rows; a step launch gathers with 256
+// CUs.  Its cost follows the quads of a member and, less, its rows; that of a step
+// launch the launch itself up to 8 columns, and its rows beyond.  us per iteration,
+// chunks / step launches, FP64 and FP32, at (quads of a member, rows):
+//   2 LPs:   3549 x 9474, 5 entries per column (1045, 13023) 8.0 / 9.0 and 7.9 / 8.6;
+//            8000 x 16000, 3 (1024, 24000) 8.4 / 8.7 and 8.5 / 8.1;  7000 x 15000, 4 (1066,
+//            22000) 9.4 / 8.8 and 8.0 / 8.2;  10000 x 20000, 4 (1436, 30000) 10.4 / 9.4 and
+//            10.5 / 8.3
+//   8 LPs:   6500 x 16500, 4 (1158, 23000) 9.7 / 11.0 and 9.3 / 9.5;  10000 x 20000 11.0 /
+//            12.1 and 10.5 / 10.1;  8000 x 12000, 8 (1674, 20000) 11.6 / 11.2 and 10.7 / 9.5
+//   16 LPs:  8000 x 12000 12.5 / 13.6 and 12.2 / 11.9, 9 LPs 12.7 / 12.5 and 11.9 / 10.5;
+//            10000 x 25000, 4 (1729, 35000) in FP32 12.8 / 14.1
+//   32 LPs:  6000 x 12500, 8 (1699, 18500) in FP32 13.0 / 14.7; more does not fit
+bool columns_pay(const pdlpb_ctx* x, int32_t shape, int32_t lw) {
+    const int64_t rows = (int64_t)x->n + x->m, size = x->ps_q32 + rows / 160;
+    if (lw >= 2) return true;
+    if (lw == 1) return !x->fp32 || x->ps_q32 <= 1200 + rows / 45;
+    return size <= (shape > 4 ? (x->fp32 ? 1230 : 1500) : (x->fp32 ? 1170 : 1240));
+}
+
 PersistPlan persist_plan(const pdlpb_ctx* x, int32_t shape) {
     PersistPlan p;
     if (x->m < 1 || x->nnz < 1 || x->opt.restart_scope != PDLPB_RESTART_PER_LP || x->timing ||
-        x->opt.tile_lanes > 0 || x->opt.tile_vec > 0 || x->opt.max_blocks > 0 || shape < 1 || x->pw_x != 4 || x->pw_y != 4)
+        x->opt.tile_lanes > 0 || x->opt.tile_vec > 0 || x->opt.max_blocks > 0 || shape < 1 ||
+        x->pw_x != 4 || x->pw_y != 4)
         return p;
     const int32_t n = x->n, m = x->m;
     const int64_t esz = x->fp32 ? sizeof(float) : sizeof(double);
@@ -823,7 +831,7 @@ PersistPlan persist_plan(const pdlpb_ctx* x, int32_t shape) {
         }
     }
     while ((PERSIST_GROUPS << p.lw) < shape) p.lw += 1;
-    if ((1 << p.lw) > PERSIST_W || x->ps_q32 > COLUMN_QUADS[p.lw]) return p;
+    if ((1 << p.lw) > PERSIST_W || !columns_pay(x, shape, p.lw)) return p;
     p.members = PERSIST_MEMBERS;
     const int32_t rx = std::min(n, persist_rows(n, p.members)), ry = std::min(m, persist_rows(m, p.members));
     p.lds = persist_lds(rx, ry, x->ps_q32, (int64_t)1 << p.lw, esz);

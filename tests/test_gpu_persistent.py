@@ -100,13 +100,15 @@ def test_grouped_structured(P, make, B):
 
 @pytest.mark.parametrize("m, n, B, grouped", [
     (3200, 6500, 2, True), (3200, 6500, 12, True),      # row segments of one and two columns
-    (6000, 10000, 2, False), (6000, 10000, 8, False),   # they fit, but the step launches are faster
-    (6000, 10000, 12, True),                            # chunks of two columns are worth it again
+    (5000, 9000, 3, True),
+    (7000, 11000, 1, False), (7000, 11000, 4, False),   # the slices fit, but step launches are faster;
+    (7000, 11000, 5, True), (7000, 11000, 12, True),    # not so with more columns
+    (8000, 12000, 8, False),
 ])
 def test_grouped_where_faster(P, m, n, B, grouped):
     """Grouped launches where they beat the step launches (only they take work vectors)."""
     inst = make_cfg2(m=m, n=n)
-    D = obbt_deltas(choose_vars(n, B // 2, seed=B))
+    D = obbt_deltas(choose_vars(n, (B + 1) // 2, seed=B))[:B]
     with make_ctx(inst, eval_every=32) as ctx:
         ctx.set_batch(D)
         before = ctx.device_bytes
