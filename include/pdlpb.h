@@ -131,9 +131,9 @@ typedef struct pdlpb_options {
                                  Section 6 check dual feasibility at 1e-8 before trusting a dual bound */
     int32_t max_blocks;       /* cap on the workgroups of one step launch; their waves loop over the rows
                                  (a cap, like tile_lanes or tile_vec, selects the step kernels that take
-                                 any launch shape).  0 (default): the row kernels uncapped where rows have
-                                 at most 24 entries on average, else 16384 (64 4-wave workgroups per
-                                 compute unit) */
+                                 any launch shape, for small matrices too).  0 (default): the row kernels
+                                 uncapped where rows have at most 24 entries on average and launches are
+                                 not small, else 16384 (64 4-wave workgroups per compute unit) */
     int32_t scaling;          /* diagonal preconditioning of A at create: 0 (default) none; 1 ten Ruiz
                                  equilibration passes then one Pock-Chambolle pass (alpha = 1).  The
                                  solver then works on D_r A D_c (the stopping and infeasibility tests

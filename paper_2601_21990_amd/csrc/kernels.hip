@@ -2137,10 +2137,10 @@ __global__ __launch_bounds__(TAIL_THREADS) void k_tail(TailArgs<T> a) {
 //   What bounds it now: solo the dependent chain of a half (gather from LDS, sum,
 // update, barrier: ~1000 cycles), staged two barriers and the copies of the two
 // vectors (2900 of ~9600 cycles), columns the gathers' cache lines (~3000 cycles a
-// half at 25000 nonzeros over 32 CUs) and the barriers.  Measured against the step
-// launches, FP64: one LP 50 x 100 0.87 us per iteration (5.2-6.9 us before), one LP
-// 2000 x 5000 3.8 us (8.9), 16 LPs 200 x 500 to convergence 1.9 ms (9.1), 64 LPs 2000 x
-// 5000 6.9 ms (11.4).
+// half at 25000 nonzeros over 32 CUs) and the barriers.  us per iteration against the
+// step launches, every LP running, an evaluation each 64, FP64: one LP 50 x 100 1.2 (7.4),
+// 16 LPs 200 x 500 2.0 (8.3), one LP 2000 x 5000, 5 entries per column 4.1 (8.6), 64 LPs
+// 7.6 (12.1).
 //   Products, updates, terms, chains and reduction trees are those of the batched
 // kernels in the same order, and the tests are control_slot's, so an LP's results
 // are the batched path's, bit for bit.  A stopped LP keeps its column, no longer

@@ -82,7 +82,8 @@ constexpr int32_t TINY_LD = 4;
 constexpr double NARROW_MIN_BLOCK_BYTES = 256e6;   // one block pair (x rows + y rows)
 // largest matrix whose LPs the persistent tail iterates with one workgroup each
 constexpr int64_t TAIL_MAX_NNZ = 65536;
-// persistent blocks: iterations of one launch at most (a few milliseconds)
+// persistent blocks: iterations of one launch at most (about 10 ms; where other work
+// leaves room for one group of eight, up to eight times that)
 constexpr int32_t PERSIST_ITERS = 1024;
 constexpr int64_t RUN_AHEAD_AFTER = 8;      // blocks of a solve before replays run ahead of the host
 constexpr double RUN_AHEAD_BYTES = 32e6;    // ... and only while one launch moves less than this
