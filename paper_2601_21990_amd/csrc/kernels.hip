@@ -3977,7 +3977,7 @@ hipError_t launch_rows_gv(StepArgs<T> a, hipStream_t s) {
         if (G == 1 && a.short_rows) return go(k_primal_rows<T, G, VEC, 64 / G, 8>, k_dual_rows<T, G, VEC, 64 / G, 8>, 64 / G);
         return go(k_primal_rows<T, G, VEC, 64 / G, 16>, k_dual_rows<T, G, VEC, 64 / G, 16>, 64 / G);
     } else {
-        const bool few = ((int64_t)a.rows + 15) / 16 * tiles < ROWS_WAVES;
+        const bool few = a.split || ((int64_t)a.rows + 15) / 16 * tiles < ROWS_WAVES;
         if (few) return go(k_primal_rows<T, G, VEC, 8, 4>, k_dual_rows<T, G, VEC, 8, 4>, 8);
         return go(k_primal_rows<T, G, VEC, 16, 8>, k_dual_rows<T, G, VEC, 16, 8>, 16);
     }

@@ -177,6 +177,9 @@ struct pdlpb_ctx {
     // A' and A together, and the most in a member's slices at the group sizes 16 and
     // 32; control words; work vectors of the chunks
     int64_t ps_q = 0, ps_q16 = 0, ps_q32 = 0;
+    // longest rows of A' and A: the longest, and the longest two that are the longest of
+    // the two halves of 16 consecutive rows, together
+    int64_t long8[2] = {0, 0}, long16[2] = {0, 0};
     GroupCtl* ps_ctl = nullptr;
     void* ps_work = nullptr;
     double* ps_sum = nullptr;
@@ -454,6 +457,20 @@ bool lane_rows_serve(const pdlpb_ctx* x, bool primal, int32_t w, int lanes) {
     return w <= 4 && rows >= LANE_ROWS * w && (lanes > 1 || x->nnz <= LANE_MEAN * rows);
 }
 
+// Long rows side by side (facility location): a launch lasts as long as a wave's chain
+// of gathers over its rows, about 0.14 us an entry, where that exceeds the time of all
+// gathers, about a line in 6 ps.  A wave of the row kernel then takes 8 rows, which are
+// in flight together, not 16 in two turns (StepArgs::split), and FP32 batches of up to 32
+// columns stay with k_primal / k_dual, whose waves hold fewer rows.  11100 x 10100, rows
+// and columns of 161 entries among short ones, us per iteration, FP64 64 / 512 LPs 54 /
+// 122 with 8 rows, 81 / 141 with 16, 59 / 114 with k_primal / k_dual; FP32 1 / 16 LPs
+// 37 / 41 with those, 43 / 49 with the row kernel (18200 x 16200, 32 LPs 39 and 43).
+bool long_chain(const pdlpb_ctx* x, bool primal, int32_t ncols) {
+    const int32_t tile = x->fp32 ? block_tile<float>() : block_tile<double>();
+    const int64_t l16 = x->long16[primal ? 0 : 1], l8 = x->long8[primal ? 0 : 1];
+    return l16 >= 128 && 4 * l16 >= 5 * l8 && 23000 * l16 > x->nnz * ((ncols + tile - 1) / tile);
+}
+
 // Small launches last as long as their chain of dependent loads, which is one load
 // shorter in k_primal / k_dual (the ELL head has a row's indices at a known place) than
 // in the row kernel (row pointers, then entries): those serve, a column per lane, while
@@ -485,7 +502,9 @@ Tile heuristic_tile(const pdlpb_ctx* x, int32_t ncols, bool primal) {
     }
     const int32_t tile = x->fp32 ? block_tile<float>() : block_tile<double>();
     const int32_t w = std::min<int32_t>(tile, next_pow2(ncols > 0 ? ncols : 1));
-    const bool rows = rows_kernel_serves(x, primal), small = rows && small_launch(x, ncols);
+    const bool rows = rows_kernel_serves(x, primal);
+    const bool small = rows && (small_launch(x, ncols) ||
+                                (x->fp32 && ncols <= 32 && long_chain(x, primal, ncols)));
     if (rows && !small) {
         // 16 bytes per lane where the width allows it (ld_for pads for that), 8 lanes at
         // least unless a lane takes a row
@@ -579,6 +598,7 @@ StepArgs<T> step_args(pdlpb_ctx* x, bool primal, int32_t it, int32_t eval, int32
     a.max_blocks = primal ? x->tp.blocks : x->td.blocks;
     a.rows_kernel = (primal ? x->tp.rows : x->td.rows) ? 1 : 0;
     a.short_rows = x->nnz <= 6 * (int64_t)(primal ? x->n : x->m) ? 1 : 0;
+    a.split = long_chain(x, primal, x->live) ? 1 : 0;
     if (primal) {
         a.G = b[4];   // Y
         a.Z = b[0]; a.Z0 = b[1]; a.Zt = b[2]; a.DZ = b[3];
@@ -2245,6 +2265,18 @@ int pdlpb_create(pdlpb_ctx** out, int32_t m, int32_t n, int64_t nnz, const int64
             }
             return most;
         };
+        auto longest = [](const auto& rp, int32_t rows, int64_t* l8, int64_t* l16) {
+            int64_t half[2] = {0, 0};
+            for (int32_t r = 0; r < rows; ++r) {
+                const int h = (r >> 3) & 1;
+                if ((r & 15) == 0) half[0] = half[1] = 0;
+                half[h] = std::max<int64_t>(half[h], rp[r + 1] - rp[r]);
+                *l8 = std::max(*l8, half[h]);
+                *l16 = std::max(*l16, half[0] + half[1]);
+            }
+        };
+        longest(h_trp, n, &x->long8[0], &x->long16[0]);
+        longest(h_arp, m, &x->long8[1], &x->long16[1]);
         x->ps_q = quads(1);
         x->ps_q16 = quads(PERSIST_STAGED_MEMBERS);
         x->ps_q32 = quads(PERSIST_MEMBERS);

@@ -175,6 +175,7 @@ struct StepArgs {
     int32_t gx;          // row blocks per column tile when tiles are dealt to XCDs (set at launch), 0: grid y is the tile
     int32_t rows_kernel; // 1: k_primal_rows / k_dual_rows
     int32_t short_rows;  // 1: at most 6 entries per row on average
+    int32_t split;       // 1: a wave of the row kernel takes no more rows than it has in flight
     int32_t max_blocks;  // > 0: cap on the workgroups of the launch (waves then loop over rows)
 };
 

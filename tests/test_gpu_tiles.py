@@ -116,11 +116,14 @@ def test_row_kernel_odd_widths(P, B, prec):
     (lambda: make_cfg2(m=20000, n=12001), 16),
     (lambda: make_cfg2(m=20000, n=12001), 32),
     (lambda: make_facility(F=16, C=4000, k=4), 33),     # columns and rows of 1000 entries among short ones
+    (make_facility, 20),                                # long rows side by side: 8 rows a wave,
+    (make_facility, 33),                                # or the kernels of any launch shape (FP32)
+    (make_facility, 130),
     (lambda: make_cfg2(m=4001, n=9999), 17),            # either side of the bound on small launches (FP32)
     (lambda: make_cfg2(m=4001, n=10001), 17),
     (lambda: make_cfg2(m=801, n=1999), 13),             # ... (FP64)
     (lambda: make_cfg2(m=801, n=2001), 13),
-], ids=["empty3", "empty16", "empty32", "spill", "9999", "10001", "1999", "2001"])
+], ids=["empty3", "empty16", "empty32", "spill", "long20", "long33", "long130", "9999", "10001", "1999", "2001"])
 def test_row_kernel_not_small(P, make, B, prec):
     """The row kernel where launches are not small, and at the line."""
     test_row_kernel(P, make, B, prec)
