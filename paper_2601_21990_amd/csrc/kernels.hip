@@ -4031,6 +4031,12 @@ hipError_t launch_dual(const StepArgs<T>& a, int lanes, int vec, hipStream_t s) 
 // FP32, k_eval_rows / k_eval_narrow: 9.7 / 7.5 and 9.4 / 7.0 us; 1000 x 2500, 4 LPs
 // 11.5 / 9.1 and 10.8 / 7.9, 8 LPs 11.9 / 12.2 and 11.3 / 9.8; 2000 x 5000, 4 LPs
 // 12.9 / 13.0 and 11.9 / 10.1, 8 LPs 12.3 / 20 and 12 / 13.9.
+// Where long rows lie side by side (EvalArgs::chain) k_eval takes them one after another
+// and k_eval_narrow a lane each: 10530 x 9030, rows and columns of 444 entries among short
+// ones, 16 LPs, k_eval / k_eval_narrow 197 / 91 us (FP64) and 173 / 81; k_eval_rows, whose
+// lanes wait for 8 gathers at a time, is faster for one or two LPs (41 / 76) and beyond
+// 160000 rows times columns (18200 x 16200, 130 entries, 8 LPs 44 / 56), not between (4 LPs
+// 84 / 78).
 // k_eval_rows serves panels of up to 32 rows (both sides up to 65536 rows).  A wave of
 // k_eval_narrow has 16 rows of a 64-row panel, and k_eval_rows is faster there only
 // where four columns fill its workgroups.  All LPs, FP64 and FP32, k_eval_rows /
@@ -4045,12 +4051,13 @@ template <typename T>
 hipError_t launch_eval(const EvalArgs<T>& a, hipStream_t s) {
     const int32_t pw = max(a.pw_x, a.pw_y);
     const int64_t work = ((int64_t)a.n + a.m) * a.ncols;
-    const bool few = sizeof(T) == 4 ? work <= 30000 && (a.ncols > 2 || a.n + a.m <= 5000)
+    const bool few = sizeof(T) == 4 ? work <= 30000 && (a.ncols > 2 || (a.n + a.m <= 5000 && !a.chain))
                                     : work <= 20000 && a.ncols > 2;
-    const bool small = pw <= 16, rows = !few && (pw <= 8 || (small && a.full && a.ncols % 4 == 0));
+    const bool chain = a.chain && (a.ncols > EVAL_NARROW_COLS / 2 || (a.ncols > 2 && work <= 160000));
+    const bool small = pw <= 16, rows = !few && !chain && (pw <= 8 || (small && a.full && a.ncols % 4 == 0));
     const bool narrow = a.ncols <= EVAL_NARROW_COLS / 2 ||
                         (a.ncols <= EVAL_NARROW_COLS &&
-                         (!small || !a.full || work <= (1 << 18)));
+                         (!small || !a.full || chain || work <= (1 << 18)));
     if (narrow && rows) {
         const int64_t groups = (((int64_t)a.n + 63) / 64 + ((int64_t)a.m + 63) / 64 + 7) / 8 * 8 * ((a.ncols + 3) / 4);
         if (groups <= 0) return hipSuccess;

@@ -639,6 +639,7 @@ EvalArgs<T> eval_args(pdlpb_ctx* x, int32_t it, int32_t full) {
     a.sl = x->sl;
     a.g = x->g;
     a.pw_x = x->pw_x; a.pw_y = x->pw_y; a.npx = x->npx; a.npy = x->npy;
+    a.chain = long_chain(x, true, x->live) || long_chain(x, false, x->live) ? 1 : 0;
     a.part_x = x->part;
     a.part_y = x->part + (size_t)x->npx * NTERM * x->ld;
     return a;

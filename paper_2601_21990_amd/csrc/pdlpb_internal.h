@@ -191,6 +191,7 @@ struct EvalArgs {
     const Globals* g;        // live column count
     int32_t pw_x, pw_y;      // rows per wave on the x side / y side
     int32_t npx, npy;        // row panels (4 waves each) on each side
+    int32_t chain;           // 1: a launch lasts as long as its longest rows
     double* part_x;          // [NTERM][ld][npx]
     double* part_y;          // [NTERM][ld][npy]
     int32_t it;              // iteration index inside the block; global t = g->t0 + it

@@ -175,3 +175,18 @@ def test_evaluations_of_few_rows(P, m, n, prec):
             part = _solve(ctx, D[i:j], 33)
             for key in whole:
                 assert np.array_equal(whole[key][i:j], part[key], equal_nan=True), (key, i)
+
+
+@pytest.mark.parametrize("prec", ["fp64", "fp32"])
+@pytest.mark.parametrize("F, C", [(20, 200), (100, 1000), (200, 2000)])
+def test_evaluations_of_long_rows(P, F, C, prec):
+    """Long rows side by side: the widths that each of the evaluation kernels takes."""
+    inst = make_facility(F=F, C=C, k=8)
+    D = _deltas(inst.n, 40)
+    with make_ctx(inst, precision=P.MIXED32 if prec == "fp32" else P.FP64, eval_every=8, stop_every=4) as ctx:
+        ctx.set_kernel_timing(True)
+        whole = _solve(ctx, D, 33)
+        for i, j in ((0, 1), (1, 3), (3, 7), (7, 15), (15, 31)):
+            part = _solve(ctx, D[i:j], 33)
+            for key in whole:
+                assert np.array_equal(whole[key][i:j], part[key], equal_nan=True), (key, i)
