@@ -9,7 +9,7 @@ import numpy as np
 import pytest
 
 from gpu_common import make_ctx
-from workloads import choose_vars, make_cfg1, make_cfg2, make_facility, obbt_deltas
+from workloads import choose_vars, make_cfg1, make_cfg2, make_facility, make_packing, obbt_deltas
 
 pytestmark = pytest.mark.gpu
 
@@ -190,3 +190,21 @@ def test_evaluations_of_long_rows(P, F, C, prec):
             part = _solve(ctx, D[i:j], 33)
             for key in whole:
                 assert np.array_equal(whole[key][i:j], part[key], equal_nan=True), (key, i)
+
+
+@pytest.mark.parametrize("prec", ["fp64", "fp32"])
+@pytest.mark.parametrize("B", [16, 17, 20, 21, 33, 36, 40, 41, 49, 64, 65])
+def test_dense_rows(P, B, prec):
+    """Columns of 40 and rows of 100 entries, past what the row kernel takes: batches whose
+    last storage tile
+    is up to a quarter full and just past that, against narrow row groups, bit for bit."""
+    inst = make_packing(m=200, n=500, k=40)
+    D = _deltas(inst.n, B)
+    kw = dict(precision=P.MIXED32 if prec == "fp32" else P.FP64, eval_every=32)
+    out = []
+    for shape in ({}, dict(tile_lanes=8, tile_vec=1)):
+        with make_ctx(inst, **kw, **shape) as ctx:
+            ctx.set_kernel_timing(True)
+            out.append(_solve(ctx, D, 70))
+    for key in out[0]:
+        assert np.array_equal(out[0][key], out[1][key], equal_nan=True), key
