@@ -145,8 +145,9 @@ typedef struct pdlpb_options {
                                  launch with one workgroup per LP, which computes the same bits as
                                  the batched kernels (Section 5: the LPs left once most have stopped).
                                  One CU then streams the whole matrix every iteration: it is faster
-                                 than the batched kernels only on matrices of a few thousand
-                                 nonzeros, so it is left to the caller */
+                                 than step launches only on matrices of a few thousand nonzeros,
+                                 where persistent blocks (the default) are as fast or faster, so it
+                                 is left to the caller */
     int32_t stop_every;       /* S: the stopping test (eq:stopping at z~) also runs every S
                                  iterations between the evaluations of eval_every (Section 4 leaves
                                  the schedule open); it tests nothing else, so the iterates are
