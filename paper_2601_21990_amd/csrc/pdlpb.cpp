@@ -520,14 +520,17 @@ Tile heuristic_tile(const pdlpb_ctx* x, int32_t ncols, bool primal) {
         t.blocks = DEFAULT_MAX_BLOCKS;
         return t;
     }
-    // A row group spans two or four storage tiles where the last would be at most a
-    // quarter full: tile by tile the matrix is read once more for those few columns.
-    // us per iteration, spanning / tile by tile: FP64, 3000 x 3000, 60 entries per row,
-    // 17 LPs 27.6 / 31.7, 33 LPs 31.7 / 37.8;  FP32, 10000 x 40000, 30 per column, 33 LPs
-    // 64.4 / 70.7, 40 LPs 66.1 / 71.4. From about half a tile on there is no difference.
-    const bool spans = !small && ncols > tile && ncols <= 64 && (ncols - 1) % tile < tile / 4;
-    const int32_t span = spans || (small && ncols > w && ncols <= 32)   // both tiles of an FP64 row
-                             ? next_pow2(ncols) : w;
+    // A row group spans the storage tiles of up to 32 FP64 columns, a column per lane, and
+    // two or four tiles of up to 64 where the last would be at most a quarter full: tile by
+    // tile the matrix is read once more for the last one's columns. us per iteration,
+    // spanning / tile by tile: FP64, 3000 x 3000, 60 entries per row, 17 LPs 27.5 / 31.7,
+    // 33 LPs 31.5 / 37.8, 1000 x 1000, 100 per row, 24 LPs 31.9 / 33.3, 32 LPs 32.4 / 34.6,
+    // 10000 x 10000, 40 per row, 32 LPs 42.2 / 44.0;  FP32, 10000 x 40000, 30 per column,
+    // 33 LPs 64.8 / 70.7, 40 LPs 66.1 / 71.4. Past a quarter of a tile it no
+    // longer gains (3000 x 3000, FP64, 40 LPs 31.3 / 31.6, 10000 x 10000 48.7 / 46.1).
+    const bool spans = !small && ncols > tile &&
+                       (ncols <= 32 || (ncols <= 64 && (ncols - 1) % tile < tile / 4));
+    const int32_t span = spans || (small && ncols > w && ncols <= 32) ? next_pow2(ncols) : w;
     int vec = small || w < tile || (spans && span < 64) ? 1 : v;
     if (x->opt.tile_vec > 0) vec = x->opt.tile_vec;
     if (vec > x->vec_ld) vec = x->vec_ld;

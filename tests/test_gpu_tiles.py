@@ -193,7 +193,7 @@ def test_evaluations_of_long_rows(P, F, C, prec):
 
 
 @pytest.mark.parametrize("prec", ["fp64", "fp32"])
-@pytest.mark.parametrize("B", [16, 17, 20, 21, 33, 36, 40, 41, 49, 64, 65])
+@pytest.mark.parametrize("B", [16, 17, 20, 21, 32, 33, 36, 40, 41, 49, 64, 65])
 def test_dense_rows(P, B, prec):
     """Columns of 40 and rows of 100 entries, past what the row kernel takes: batches whose
     last storage tile
